@@ -8,7 +8,8 @@
 namespace pisco {
 
 constexpr int SHT_MAX_NSIDE = 1024;        // ring FFT buffers (2 x 4N complex) fit one CU's LDS
-constexpr int SHT_PAIRS_PER_LANE = 4;      // 512 lanes x 4 ring pairs = 2N pairs at the largest nside
+
+constexpr int SHT_STEP_BYTES = 48;
 
 struct ShtArgs {
     int nside, lmax, mmax, nfields;        // nfields: 1 (T) or 3 (T, Q, U)
@@ -16,12 +17,13 @@ struct ShtArgs {
     const double *map[3];                  // RING order, 12 nside^2 each
     double2 *F;                            // [nfields][mmax + 1][nrings]: weighted ring Fourier sums
     double *alm[3];                        // complex interleaved, m-major: T, E, B
-    double *partial;                       // [SHT_WAVES][alm size][6]: per-wave partial sums
+    int add;                               // analysis: add to alm instead of replacing it
+    int wx_m, wx_parts;                    // analysis: m < wx_m in wx_parts workgroups each (filled in by launch_alm)
+    void *steps;                           // recurrence steps, SHT_STEP_BYTES per a_lm (launch_steps)
+    double *partial;                       // analysis: [part][alm size][6] sums of the first m
     const double *alm_in[3];               // synthesis input (complex interleaved)
     double *map_out[3];                    // synthesis output (RING order)
 };
-
-constexpr int SHT_WAVES = 8;               // waves per a_lm workgroup (one workgroup per m)
 
 struct ClArgs {
     int lmax, nspec;                       // up to 6 spectra
@@ -29,6 +31,7 @@ struct ClArgs {
     double *cl;                            // [nspec][lmax + 1]
 };
 
+hipError_t launch_steps(const ShtArgs &a, hipStream_t s);            // before any launch_alm or launch_alm2map of its lmax
 hipError_t launch_ring_fourier(const ShtArgs &a, hipStream_t s);
 hipError_t launch_alm(const ShtArgs &a, hipStream_t s);
 hipError_t launch_alm2map(const ShtArgs &a, hipStream_t s);          // alm_in -> F (as G) -> map_out

@@ -4,18 +4,18 @@
 // phase; spin-2 harmonics of Goldberg et al. 1967; E and B as in Zaldarriaga &
 // Seljak 1997 with the HEALPix sign convention) are stated in include/pisco.h.
 //
-// Three kernels:
+// Kernels:
 //   ring_fourier_kernel  one workgroup per ring: F_r(m) = w sum_j x_j e^{-i m phi_j}
 //                        for every field, by an FFT in LDS (direct DFT over the
 //                        odd factor of the ring length, then radix-2 Stockham
 //                        passes over its power-of-two factor), read at m mod n;
+//   steps_kernel         the recurrence steps of every (l, m), once per call;
 //   alm_kernel           one workgroup per m: lanes own north/south ring pairs,
-//                        run the recurrence for lambda_lm in l (mantissa plus a
-//                        carried power-of-two exponent, so sin^m theta cannot
-//                        underflow), form W_lm and X_lm from lambda_l and
-//                        lambda_{l-1}, and accumulate the symmetric and
-//                        antisymmetric ring-pair sums; every four l the
-//                        workgroup sums its lanes through LDS;
+//                        run the recurrences of lambda_lm and of the spin-2
+//                        functions in l (mantissa plus a carried power-of-two
+//                        exponent, so sin^m theta cannot underflow) and
+//                        accumulate against the pair's ring sums; every four l a
+//                        wave adds its lanes, every 64 l the workgroup its waves;
 //   alm2cl_kernel        one wave per l: C_l of up to six a_lm pairs;
 //   alm2ring_kernel      the synthesis: one workgroup per m, lanes own ring pairs
 //                        and sum over l in registers (no cross-lane sums);
@@ -31,9 +31,6 @@ namespace pisco {
 namespace {
 
 constexpr int SCALE = 256;               // exponent step of the carried recurrence
-constexpr int ALM_THREADS = 512;
-constexpr int ALM_WAVES = ALM_THREADS / 64;
-static_assert(ALM_WAVES == SHT_WAVES, "partial-sum layout");
 constexpr int LBLOCK = 4;                // l values per LDS reduction
 constexpr int NCOMP = 6;                 // a^T, a^E, a^B (re, im)
 constexpr int LCHUNK = 64;               // l values per coefficient table
@@ -42,6 +39,7 @@ struct RingGeom {
     int64_t first;
     int n;
     double z, s, phi0_over_pi;
+    double omz;                          // 1 - z without the cancellation next to the north pole
 };
 
 // Ring i = r + 1 of the RING scheme (Gorski et al. 2005, Sec. 4): colatitude
@@ -57,12 +55,14 @@ __device__ inline RingGeom sht_ring(int N, int r) {
         g.first = i < N ? 2LL * k * (k - 1) : 12LL * N * N - 2LL * k * (k + 1);
         g.z = i < N ? 1.0 - t : t - 1.0;
         g.s = sqrt(t * (2.0 - t));
+        g.omz = i < N ? t : 2.0 - t;
         g.phi0_over_pi = 0.25 / (double)k;
     } else {
         g.n = 4 * N;
         g.first = 2LL * N * (N - 1) + (int64_t)(i - N) * 4 * N;
         g.z = (double)(4 * N - 2 * i) / (3.0 * N);
         g.s = sqrt((double)(2 * i - N) * (double)(7 * N - 2 * i)) / (3.0 * N);
+        g.omz = (double)(2 * i - N) / (3.0 * N);
         g.phi0_over_pi = ((i - N) & 1) == 0 ? 0.25 / (double)N : 0.0;
     }
     return g;
@@ -172,6 +172,520 @@ __global__ void __launch_bounds__(256) ring_fourier_kernel(ShtArgs a, RingRange 
     }
 }
 
+// ----------------------------------------------------------------------
+// The colatitude functions of one m, for the analysis and the synthesis.
+//
+// lambda_lm and the spin-2 functions f^+- = W_lm +- X_lm obey
+//   A_l g_l = (z + s_l) g_{l-1} - A_{l-1} g_{l-2},
+//   lambda: s_l = 0,                  A_l^2 = (l^2 - m^2) / (4 l^2 - 1),
+//   f^+-:   s_l = +- 2m / (l (l-1)),  A_l^2 = (l^2 - m^2)(l^2 - 4) / (l^2 (4 l^2 - 1))
+// (the standard recurrences of spin-weighted harmonics).  The mirror ring has
+// lambda -> (-1)^(l+m) lambda and f^+- -> (-1)^(l+m) f^-+, so a north / south
+// pair's three functions take nine instructions, and with
+//   P = Q + iU, M = Q - iU (complex sums at each m, not conjugates):
+//   S+ = sum f^+ P_N + (-1)^(l+m) f^- P_S,  S- = sum f^- M_N + (-1)^(l+m) f^+ M_S,
+//   a^E = -(S+ + S-) / 2,  a^B = i (S+ - S-) / 2;
+//   P = -sum (a^E + i a^B) f^+,  M = -sum (a^E - i a^B) f^-
+// eight multiply-adds for E and B.  Forming W and X from lambda_l and
+// lambda_{l-1} takes eight instructions where f^+- takes six, and loses digits
+// to the 1 / s^2 terms next to the poles.  (Scaling the functions so that the
+// last coefficient is 1 saves three more instructions, but the rounding of the
+// first one then shifts z at every step, which next to the poles is ten times
+// the plain recurrence's error.)
+// ----------------------------------------------------------------------
+struct Step {
+    double aT, bT;       // 1 / A_l and A_{l-1} of lambda
+    double aS, sS;       // 1 / A_l of f^+- and s_l of f^+
+    double bS, abS;      // A_{l-1} and A_{l-1} / A_l of f^+-
+};
+static_assert(sizeof(Step) == SHT_STEP_BYTES, "size of the steps in the workspace");
+
+// The steps of every (l, m), packed like the a_lm: written once per call, then
+// read with scalar loads (a step is uniform over a workgroup), so that no vector
+// register or LDS read is spent on them.  The first (l = m) gives g_l = -g_{l-2},
+// see start_pair; f is for m >= 2.
+__global__ void __launch_bounds__(256) steps_kernel(ShtArgs a) {
+    const int m = blockIdx.y, l = m + (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (l > a.lmax) return;
+    const double dl = l, dm = m, d1 = dl - 1.0;
+    const double p = (dl - dm) * (dl + dm), p1 = (d1 - dm) * (d1 + dm);       // l^2 - m^2, (l-1)^2 - m^2
+    const double q = 4.0 * dl * dl - 1.0, q1 = 4.0 * d1 * d1 - 1.0;
+    Step s{1.0, 1.0, 1.0, 0.0, 1.0, 1.0};
+    if (l > m) {
+        s.aT = sqrt(q / p);
+        s.bT = sqrt(p1 / q1);
+    }
+    if (l > m && m >= 2) {
+        const double u = (dl - 2.0) * (dl + 2.0), u1 = (d1 - 2.0) * (d1 + 2.0);
+        s.aS = dl * sqrt(q / (p * u));
+        s.bS = sqrt(p1 * u1 / q1) / d1;
+        s.sS = 2.0 * dm / (dl * d1);
+        s.abS = s.aS * s.bS;
+    }
+    static_cast<Step *>(a.steps)[(int64_t)m * (2 * a.lmax + 1 - m) / 2 + l] = s;
+}
+
+typedef const double __attribute__((address_space(4))) *uniform_ptr;
+__device__ inline uniform_ptr steps_of(const ShtArgs &a, int64_t index) {
+    return (uniform_ptr)(unsigned long long)(static_cast<const Step *>(a.steps) + index);
+}
+__device__ inline Step load_step(uniform_ptr p) { return Step{p[0], p[1], p[2], p[3], p[4], p[5]}; }
+
+// A ring pair's functions before the step to l = m, in units of 2^(SCALE e).
+struct PairState {
+    double z;
+    double v, vp, fp, fpp, fm, fmp;    // lambda, f^+ and f^-, each with its predecessor
+    int e;
+};
+
+// Powers of two: the values' window is [2^-HALF, 2^HALF) at the start and after
+// each rescaling, so a lane with e < 0 holds numbers below 2^-HALF (3e-39 of
+// the O(1) values its ring reaches later): they add nothing in FP64.
+constexpr int HALF = SCALE / 2;
+
+// c s^m, split into a mantissa and a multiple of SCALE in the exponent
+__device__ inline void power_start(double s, int m, double c, double *v, int *e) {
+    int es;
+    const double fs = frexp(s, &es);
+    double base = fs, res = 1.0;
+    long long be = 0, re = 0;
+    for (int k = m; k; k >>= 1) {
+        int t;
+        if (k & 1) {
+            res = frexp(res * base, &t);
+            re += be + t;
+        }
+        base = frexp(base * base, &t);
+        be = 2 * be + t;
+    }
+    const long long E = re + (long long)es * m;
+    long long q = (E + HALF) / SCALE;
+    if (q * SCALE > E + HALF) --q;                // floor
+    *e = (int)q;
+    *v = c * ldexp(res, (int)(E - q * SCALE));
+}
+
+// Start values, placed so that the first step (g_l = -g_{l-2}) brings them up at l = m:
+//   lambda_mm = (-1)^m c_m s^m,
+//   f^+-_mm = sqrt(m (m-1) / ((m+1)(m+2))) lambda_mm ((1 -+ z) / (1 +- z))  (m >= 2).
+// North ring or equator: z >= 0 and 1 - z = omz, exact next to the pole.
+__device__ inline PairState start_pair(const RingGeom &g, int m, double cm, bool ok) {
+    PairState p;
+    p.z = g.z;
+    double v;
+    power_start(g.s, m, (m & 1) ? -cm : cm, &v, &p.e);
+    if (!ok) {                                     // a lane without a ring: zero, and never rescaled
+        p.e = -1;
+        v = 0.0;
+    }
+    p.v = p.fp = p.fm = 0.0;
+    p.vp = -v;
+    const double c = m >= 2 ? sqrt((double)m * (m - 1.0) / ((m + 1.0) * (m + 2.0))) : 0.0, opz = 1.0 + g.z;
+    p.fpp = -c * v * (g.omz / opz);
+    p.fmp = -c * v * (opz / g.omz);
+    return p;
+}
+
+// One step.  POLAR: f^+- by a ((z +- s) f - b f_prev), one instruction more each:
+// next to a pole the roundings of (z +- s) a count (it differs from 2 by the order
+// of theta^2).
+template <bool POL, bool POLAR>
+__device__ inline void advance(PairState &p, const Step &c) {
+    const double vn = c.aT * fma(p.z, p.v, -c.bT * p.vp);
+    p.vp = p.v;
+    p.v = vn;
+    if (POL) {
+        double pn, mn;
+        if (POLAR) {
+            pn = c.aS * fma(p.z + c.sS, p.fp, -c.bS * p.fpp);
+            mn = c.aS * fma(p.z - c.sS, p.fm, -c.bS * p.fmp);
+        } else {
+            const double as = c.aS * c.sS;
+            pn = fma(fma(c.aS, p.z, as), p.fp, -c.abS * p.fpp);
+            mn = fma(fma(c.aS, p.z, -as), p.fm, -c.abS * p.fmp);
+        }
+        p.fpp = p.fp;
+        p.fmp = p.fm;
+        p.fp = pn;
+        p.fm = mn;
+    }
+}
+
+// After LBLOCK steps of a lane with e < 0 (a step grows by less than 2^16, and f
+// differs from lambda by less than 2^24, so nothing overflows in between).
+template <bool POL>
+__device__ inline void rescale(PairState &p) {
+    if (fabs(p.v) > 0x1p128) {
+        p.v *= 0x1p-256;
+        p.vp *= 0x1p-256;
+        if (POL) {
+            p.fp *= 0x1p-256;
+            p.fpp *= 0x1p-256;
+            p.fm *= 0x1p-256;
+            p.fmp *= 0x1p-256;
+        }
+        p.e += 1;
+    }
+}
+
+// c_m = sqrt((4 pi)^-1 prod_{k=1..m} (2k + 1) / (2k)): partial products per lane, then across the wave
+__device__ inline double start_norm(int m, int lane) {
+    double pr = 1.0;
+    for (int k = lane + 1; k <= m; k += 64) pr *= (2.0 * k + 1.0) / (2.0 * k);
+    for (int o = 32; o; o >>= 1) pr *= __shfl_xor(pr, o, 64);
+    return sqrt(pr / (4.0 * M_PI));
+}
+
+// Orders this wave's LDS writes before its later LDS reads (lanes exchange
+// values inside one wave; no other wave touches the region).
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// An a_lm value into place, or added to it (the refinement steps' corrections).
+__device__ inline void put_alm(const ShtArgs &a, double *dst, double re, double im) {
+    if (a.add) {
+        re += dst[0];
+        im += dst[1];
+    }
+    dst[0] = re;
+    dst[1] = im;
+}
+
+// Ring sums of one pair: T north +- south, and P, M of each hemisphere.
+struct PairSums {
+    double2 Tp, Tm, Pn, Ps, Mn, Ms;
+};
+
+// lambda and f of one l (parity ODD of l - m) against the pair's sums: acc = (T, S+, S-)
+template <bool ODD, bool POL>
+__device__ inline void pair_terms(const PairState &p, const PairSums &f, double *acc) {
+    const double2 FT = ODD ? f.Tm : f.Tp;
+    acc[0] = fma(p.v, FT.x, acc[0]);
+    acc[1] = fma(p.v, FT.y, acc[1]);
+    if (POL) {
+        const double sp = ODD ? -p.fp : p.fp, sm = ODD ? -p.fm : p.fm;
+        acc[2] = fma(sm, f.Ps.x, fma(p.fp, f.Pn.x, acc[2]));
+        acc[3] = fma(sm, f.Ps.y, fma(p.fp, f.Pn.y, acc[3]));
+        acc[4] = fma(sp, f.Ms.x, fma(p.fm, f.Mn.x, acc[4]));
+        acc[5] = fma(sp, f.Ms.y, fma(p.fm, f.Mn.y, acc[5]));
+    }
+}
+
+// LBLOCK steps of one pair from l - m = 0 mod LBLOCK, its terms added to acc[l][comp].
+template <bool POL, bool POLAR>
+__device__ inline void block_terms(PairState &p, const PairSums &f, const Step *st, double *acc) {
+    constexpr int NC = POL ? NCOMP : 2;
+    if (p.e >= 0) {
+#pragma unroll
+        for (int j = 0; j < LBLOCK; ++j) {
+            advance<POL, POLAR>(p, st[j]);
+            if (j & 1) pair_terms<true, POL>(p, f, acc + j * NC);
+            else pair_terms<false, POL>(p, f, acc + j * NC);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < LBLOCK; ++j) advance<POL, POLAR>(p, st[j]);
+        rescale<POL>(p);
+    }
+}
+
+// x and y of the lanes' halves exchanged and added: x over the first half's
+// place, y over the second's (32: halves of the wave; 16: rows of each half)
+template <int ROW>
+__device__ inline double swap_add(double x, double y) {
+    const unsigned long long bx = __double_as_longlong(x), by = __double_as_longlong(y);
+    uint32_t xl = (uint32_t)bx, xh = (uint32_t)(bx >> 32), yl = (uint32_t)by, yh = (uint32_t)(by >> 32);
+    if constexpr (ROW == 32) {
+        const auto l = __builtin_amdgcn_permlane32_swap(xl, yl, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(xh, yh, false, false);
+        xl = l[0], yl = l[1], xh = h[0], yh = h[1];
+    } else {
+        const auto l = __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+        xl = l[0], yl = l[1], xh = h[0], yh = h[1];
+    }
+    return __longlong_as_double(((unsigned long long)xh << 32) | xl) +
+           __longlong_as_double(((unsigned long long)yh << 32) | yl);
+}
+
+// LDS of the analysis: the waves' sums of two chunks, then per wave the 16
+// partial sums of each of a block's sums (rows of 17)
+template <bool POL>
+constexpr int alm_comps() { return POL ? NCOMP : 2; }
+template <bool POL, int NW>
+constexpr size_t alm_lds() {
+    return (2 * LCHUNK * alm_comps<POL>() + LBLOCK * alm_comps<POL>() * 17) * NW * sizeof(double);
+}
+
+// The wave's sums of NS values over its lanes, to dst[0 .. NS): 64 lanes to 16 by
+// exchanges (row i of a set of four then holds value 0, 2, 1, 3), the rest
+// through LDS, in a fixed order.
+template <int NS>
+__device__ inline void wave_sums(const double *acc, double *red, double *dst, int lane) {
+    constexpr int PARTS = 64 / NS >= 8 ? 8 : 2;                  // lanes that share one sum
+    double h[NS / 2];
+#pragma unroll
+    for (int t = 0; t < NS / 2; ++t) h[t] = swap_add<32>(acc[2 * t], acc[2 * t + 1]);
+#pragma unroll
+    for (int t = 0; t < NS / 4; ++t)
+        red[(4 * t + (lane >> 4)) * 17 + (lane & 15)] = swap_add<16>(h[2 * t], h[2 * t + 1]);
+    wave_sync();
+    const int o = lane / PARTS, part = lane % PARTS;
+    double sum = 0.0;
+    if (o < NS) {
+        const double *q = red + ((o & ~3) + ((o & 1) << 1 | (o >> 1 & 1))) * 17 + part;
+#pragma unroll
+        for (int u = 0; u < 16; u += PARTS) sum += q[u];
+    }
+#pragma unroll
+    for (int x = 1; x < PARTS; x <<= 1) sum += __shfl_xor(sum, x, 64);
+    if (part == 0 && o < NS) dst[o] = sum;
+    wave_sync();
+}
+
+// ----------------------------------------------------------------------
+// The polarised analysis of the first m forms W and X from lambda_l and
+// lambda_{l-1}: m < 2, whose f^+- start at l = 2, and on large maps m < WX_M.  A
+// pixel's z, rounded to a double, and its sin(theta) do not belong to one angle,
+// and next to the poles that moves this evaluation and the one by f^+- apart: by
+// 5e-12 of the largest a_lm at m = 0, 1e-12 at m = 3 and 3e-13 at m = 17 at nside
+// 1024 (f^+- is the nearer to the exact harmonics: 2e-12 against 1e-11 at m = 0),
+// 5e-13 at nside 256.  These few a_lm stay what the definition's own evaluation
+// gives.  They are the longest chains of l, so a workgroup takes one m and 64 NW
+// ring pairs, one a lane; with more parts than one, wx_reduce_kernel adds them.
+// ----------------------------------------------------------------------
+constexpr int WX_M = 16, WX_NSIDE = 256;
+
+struct WxStep {
+    double ra, rb;           // lambda_l = ra (z lambda_{l-1} - rb lambda_{l-2})
+    double A, B, C, D;       // W = -(A / s^2 + B) lambda_l + C (z / s^2) lambda_{l-1}; X = (m / s^2)(C lambda_{l-1} - D z lambda_l)
+};
+
+__device__ inline WxStep wx_step(int l, int m) {
+    WxStep c{1.0, 1.0, 0.0, 0.0, 0.0, 0.0};
+    const double dl = l, dm = m;
+    if (l > m) {
+        c.ra = sqrt((4.0 * dl * dl - 1.0) / (dl * dl - dm * dm));
+        c.rb = sqrt(((dl - 1.0) * (dl - 1.0) - dm * dm) / (4.0 * (dl - 1.0) * (dl - 1.0) - 1.0));
+    }
+    if (l >= 2) {
+        const double nl = 2.0 / sqrt((dl - 1.0) * dl * (dl + 1.0) * (dl + 2.0));
+        const double clm = l > m ? sqrt((2.0 * dl + 1.0) * (dl - dm) / ((2.0 * dl - 1.0) * (dl + dm))) : 0.0;
+        c.A = nl * (dl - dm * dm);
+        c.B = nl * dl * (dl - 1.0) * 0.5;
+        c.C = nl * (dl + dm) * clm;
+        c.D = nl * (dl - 1.0);
+    }
+    return c;
+}
+
+// LDS: as alm_kernel's, then two chunks of steps
+template <int NW>
+__device__ void alm_wx(const ShtArgs &a, int m, int part, int tid, double *lds) {
+    constexpr int NS = LBLOCK * NCOMP, NT = 64 * NW;
+    const int lane = tid & 63, wave = tid >> 6;
+    double *red = lds + 2 * NW * LCHUNK * NCOMP + wave * NS * 17;
+    WxStep *steps = reinterpret_cast<WxStep *>(lds + (2 * LCHUNK * NCOMP + NS * 17) * NW);
+    const int npairs = 2 * a.nside, pi = part * NT + tid;
+    const bool ok = pi < npairs;
+    const int rn = ok ? pi : 0, rs = a.nrings - 1 - rn;
+    double2 fn[3] = {}, fs[3] = {};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        if (ok) {
+            const double2 *F = a.F + ((size_t)c * (a.mmax + 1) + m) * a.nrings;
+            fn[c] = F[rn];
+            if (rs != rn) fs[c] = F[rs];
+        }
+    }
+    double2 P[3], M[3];                                               // north +- south
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        P[c] = make_double2(fn[c].x + fs[c].x, fn[c].y + fs[c].y);
+        M[c] = make_double2(fn[c].x - fs[c].x, fn[c].y - fs[c].y);
+    }
+    const RingGeom g = sht_ring(a.nside, rn);
+    PairState p = start_pair(g, m, start_norm(m, lane), ok);
+    const double inv_s2 = 1.0 / (g.s * g.s), z_s2 = g.z * inv_s2, m_s2 = (double)m * inv_s2;
+
+    const int nl = a.lmax - m + 1;
+    const int64_t base = (int64_t)m * (2 * a.lmax + 1 - m) / 2 + m, nalm = (int64_t)(a.lmax + 1) * (a.lmax + 2) / 2;
+    if (wave == 0) steps[lane] = wx_step(m + lane, m);
+    __syncthreads();
+    for (int c0 = 0, ch = 0; c0 < nl; c0 += LCHUNK, ++ch) {
+        if (wave == (ch + 1) % NW) steps[((ch + 1) & 1) * LCHUNK + lane] = wx_step(m + c0 + LCHUNK + lane, m);
+        const int cend = min(nl - c0, LCHUNK);
+        for (int b0 = 0; b0 < cend; b0 += LBLOCK) {
+            double acc[NS];
+#pragma unroll
+            for (int j = 0; j < LBLOCK; ++j) {
+                const WxStep c = steps[(ch & 1) * LCHUNK + b0 + j];
+                const double vn = c.ra * fma(p.z, p.v, -c.rb * p.vp);
+                p.vp = p.v;
+                p.v = vn;
+                const double on = p.e >= 0 ? 1.0 : 0.0;
+                const double L = on * p.v, Lp = on * p.vp;
+                const double W = fma(-fma(c.A, inv_s2, c.B), L, c.C * z_s2 * Lp);
+                const double X = m_s2 * fma(c.C, Lp, -c.D * g.z * L);
+                const double2 T = (j & 1) ? M[0] : P[0], Qa = (j & 1) ? M[1] : P[1], Ua = (j & 1) ? M[2] : P[2];
+                const double2 Qb = (j & 1) ? P[1] : M[1], Ub = (j & 1) ? P[2] : M[2];
+                double *x = acc + j * NCOMP;
+                x[0] = L * T.x;
+                x[1] = L * T.y;
+                x[2] = fma(-X, Ub.y, W * Qa.x);
+                x[3] = fma(X, Ub.x, W * Qa.y);
+                x[4] = fma(X, Qb.y, W * Ua.x);
+                x[5] = fma(-X, Qb.x, W * Ua.y);
+            }
+            if (p.e < 0) rescale<false>(p);
+            wave_sums<NS>(acc, red, lds + (((ch & 1) * NW + wave) * LCHUNK + b0) * NCOMP, lane);
+        }
+        __syncthreads();
+        const double *all = lds + (ch & 1) * NW * LCHUNK * NCOMP;
+        if (a.wx_parts > 1) {
+            for (int i = tid; i < cend * NCOMP; i += NT) {
+                double x = 0.0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) x += all[w * LCHUNK * NCOMP + i];
+                a.partial[((int64_t)part * nalm + base + c0) * NCOMP + i] = x;
+            }
+        } else {
+            for (int i = tid; i < cend * 3; i += NT) {
+                const int c = i % 3, li = i / 3;
+                double re = 0.0, im = 0.0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    re += all[(w * LCHUNK + li) * NCOMP + 2 * c];
+                    im += all[(w * LCHUNK + li) * NCOMP + 2 * c + 1];
+                }
+                put_alm(a, a.alm[c] + 2 * (base + c0 + li), c ? -re : re, c ? -im : im);
+            }
+        }
+    }
+}
+
+// One workgroup of NW waves per m, K ring pairs a lane (64 K NW >= 2 nside).
+// Bound by FP64 issue: 19 instructions per (l, pair) and, per four l and wave,
+// the 24 cross-lane sums (36 lane exchanges and 18 adds, then 6 writes and 8
+// reads of LDS).  A pair whose values are still negligible (e < 0) only steps.
+// The waves' sums meet in LDS once per 64 l, in a fixed order.  The first band of
+// pairs takes the polar form (all of them with one pair a lane).  At nside 1024,
+// lmax 3071: 8.6 ms, 25 vector instructions per (l, band of 64 pairs), the vector
+// ALU issuing 80% of the time; 16.5 ms and 43 when W and X were formed from
+// lambda, most values carried an exponent, and each (l, pair) had branches of its
+// own.  nside 128, lmax 383: see launch_alm_p.
+template <bool POL, int K, int NW>
+__global__ void __launch_bounds__(64 * NW, K >= 4 ? 2 : 1) alm_kernel(ShtArgs a) {
+    constexpr int NC = alm_comps<POL>(), NS = LBLOCK * NC, NT = 64 * NW;
+    extern __shared__ double sh_alm[];                               // [2][NW][LCHUNK][NC], [NW][NS * 17]
+    const int N = a.nside, lmax = a.lmax;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wx = a.wx_m * a.wx_parts;
+    if (POL && (int)blockIdx.x < wx) {
+        alm_wx<NW>(a, blockIdx.x / a.wx_parts, blockIdx.x % a.wx_parts, tid, sh_alm);
+        return;
+    }
+    const int m = a.wx_m + (int)blockIdx.x - wx;
+    double *red = sh_alm + 2 * NW * LCHUNK * NC + wave * NS * 17;
+    const int npairs = 2 * N;
+    const double cm = start_norm(m, lane);
+
+    PairState ps[K];
+    PairSums f[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int pi = tid + k * NT;
+        const bool ok = pi < npairs;
+        const int rn = ok ? pi : 0;
+        const int rs = a.nrings - 1 - rn;                            // mirror ring; rs == rn on the equator
+        double2 fn[3] = {}, fs[3] = {};
+#pragma unroll
+        for (int c = 0; c < (POL ? 3 : 1); ++c) {
+            if (ok) {
+                const double2 *F = a.F + ((size_t)c * (a.mmax + 1) + m) * a.nrings;
+                fn[c] = F[rn];
+                if (rs != rn) fs[c] = F[rs];
+            }
+        }
+        f[k].Tp = make_double2(fn[0].x + fs[0].x, fn[0].y + fs[0].y);
+        f[k].Tm = make_double2(fn[0].x - fs[0].x, fn[0].y - fs[0].y);
+        if (POL) {
+            f[k].Pn = make_double2(fn[1].x - fn[2].y, fn[1].y + fn[2].x);
+            f[k].Mn = make_double2(fn[1].x + fn[2].y, fn[1].y - fn[2].x);
+            f[k].Ps = make_double2(fs[1].x - fs[2].y, fs[1].y + fs[2].x);
+            f[k].Ms = make_double2(fs[1].x + fs[2].y, fs[1].y - fs[2].x);
+        }
+        ps[k] = start_pair(sht_ring(N, rn), m, cm, ok);
+    }
+
+    const int nl = lmax - m + 1;
+    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2 + m;     // index of l = m
+    Step s[LBLOCK];                                                   // steps past lmax: not used (see the workspace)
+#pragma unroll
+    for (int j = 0; j < LBLOCK; ++j) s[j] = load_step(steps_of(a, base + j));
+    for (int c0 = 0, ch = 0; c0 < nl; c0 += LCHUNK, ++ch) {
+        double *mine = sh_alm + ((ch & 1) * NW + wave) * LCHUNK * NC;
+        const int cend = min(nl - c0, LCHUNK);
+        for (int b0 = 0; b0 < cend; b0 += LBLOCK) {
+            double acc[NS];
+#pragma unroll
+            for (int t = 0; t < NS; ++t) acc[t] = 0.0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                if (k == 0) block_terms<POL, true>(ps[k], f[k], s, acc);
+                else block_terms<POL, false>(ps[k], f[k], s, acc);
+            }
+            // the next block's steps, in flight during the sums
+#pragma unroll
+            for (int j = 0; j < LBLOCK; ++j) s[j] = load_step(steps_of(a, base + c0 + b0 + LBLOCK + j));
+            wave_sums<NS>(acc, red, mine + b0 * NC, lane);
+        }
+        __syncthreads();
+        // a_lm of the chunk: the waves' sums in order, and a^E, a^B from S+, S-
+        const double *all = sh_alm + (ch & 1) * NW * LCHUNK * NC;
+        for (int i = tid; i < cend * (POL ? 2 : 1); i += NT) {
+            const int li = POL ? i >> 1 : i;
+            const bool spin = POL && (i & 1);
+            double x[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const double *q = all + (w * LCHUNK + li) * NC + (spin ? 2 : 0);
+                x[0] += q[0];
+                x[1] += q[1];
+                if (spin) {
+                    x[2] += q[2];
+                    x[3] += q[3];
+                }
+            }
+            const int64_t idx = 2 * (base + c0 + li);
+            if (!spin) {
+                put_alm(a, a.alm[0] + idx, x[0], x[1]);
+            } else {
+                put_alm(a, a.alm[1] + idx, -0.5 * (x[0] + x[2]), -0.5 * (x[1] + x[3]));
+                put_alm(a, a.alm[2] + idx, -0.5 * (x[1] - x[3]), 0.5 * (x[0] - x[2]));
+            }
+        }
+    }
+}
+
+// a_lm of the first m: the parts' sums (T, -E, -B) in order.
+__global__ void __launch_bounds__(256) wx_reduce_kernel(ShtArgs a, int64_t count) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= count * 3) return;
+    const int64_t nalm = (int64_t)(a.lmax + 1) * (a.lmax + 2) / 2;
+    const int c = (int)(i % 3);
+    double re = 0.0, im = 0.0;
+    for (int q = 0; q < a.wx_parts; ++q) {
+        const double *x = a.partial + ((int64_t)q * nalm + i / 3) * NCOMP + 2 * c;
+        re += x[0];
+        im += x[1];
+    }
+    put_alm(a, a.alm[c] + 2 * (i / 3), c ? -re : re, c ? -im : im);
+}
+
 struct Coef {
     double ra, rb;           // lambda_l = ra (z lambda_{l-1} - rb lambda_{l-2})
     double A, B, C, D;       // n_l (l - m^2), n_l l (l - 1) / 2, n_l (l + m) c_lm, n_l (l - 1)
@@ -196,13 +710,6 @@ __device__ inline Coef make_coef(int l, int m) {
     return c;
 }
 
-struct PairState {
-    double2 Tp, Tm, Qp, Qm, Up, Um;   // F_north +- F_south
-    double z, inv_s2, z_s2, m_s2;
-    double v, vp;                      // lambda_l, lambda_{l-1} in units of 2^(SCALE e)
-    int e;
-};
-
 // lambda_mm = (-1)^m c_m s^m, split into a mantissa and a multiple of SCALE in the exponent
 __device__ inline void start_value(double s, int m, double cm, double *v, int *e) {
     int es;
@@ -223,185 +730,6 @@ __device__ inline void start_value(double s, int m, double cm, double *v, int *e
     if (q * SCALE > E) --q;                       // floor
     *e = (int)q;
     *v = ((m & 1) ? -cm : cm) * ldexp(res, (int)(E - q * SCALE));
-}
-
-// Adds lambda_l F_T, W F_Q + i X F_U and W F_U - i X F_Q (the last two are
-// -a^E and -a^B; the sign is applied when the sums are stored).  SCALED: the
-// lane's values may still carry a power-of-two exponent (e < 0).
-template <int P, bool POL, bool SCALED>
-__device__ inline void pair_terms(const PairState &p, const Coef &c, double *acc) {
-    double L = p.v, Lp = p.vp;
-    if (SCALED) {
-        const double f = p.e == 0 ? 1.0 : (p.e == -1 ? 0x1p-256 : 0.0);
-        L *= f;
-        Lp *= f;
-    }
-    const double2 FT = P ? p.Tm : p.Tp;
-    acc[0] = fma(L, FT.x, acc[0]);
-    acc[1] = fma(L, FT.y, acc[1]);
-    if (POL) {
-        // W = -(A / s^2 + B) lambda_l + C (z / s^2) lambda_{l-1};  X = (m / s^2)(C lambda_{l-1} - D z lambda_l)
-        const double W = fma(-fma(c.A, p.inv_s2, c.B), L, c.C * p.z_s2 * Lp);
-        const double X = p.m_s2 * fma(c.C, Lp, -c.D * p.z * L);
-        const double2 Qa = P ? p.Qm : p.Qp, Ua = P ? p.Um : p.Up;    // parity of lambda and W
-        const double2 Qb = P ? p.Qp : p.Qm, Ub = P ? p.Up : p.Um;    // parity of X
-        acc[2] = fma(-X, Ub.y, fma(W, Qa.x, acc[2]));
-        acc[3] = fma(X, Ub.x, fma(W, Qa.y, acc[3]));
-        acc[4] = fma(X, Qb.y, fma(W, Ua.x, acc[4]));
-        acc[5] = fma(-X, Qb.x, fma(W, Ua.y, acc[5]));
-    }
-}
-
-template <bool SCALED>
-__device__ inline void advance(PairState &p, const Coef &c) {
-    const double vn = c.ra * fma(p.z, p.v, -c.rb * p.vp);
-    p.vp = p.v;
-    p.v = vn;
-    if (SCALED && fabs(vn) > 0x1p256) {
-        p.v *= 0x1p-256;
-        p.vp *= 0x1p-256;
-        p.e += 1;
-    }
-}
-
-// Orders this wave's LDS writes before its later LDS reads (lanes exchange
-// values inside one wave; no other wave touches the region).
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-constexpr int RED_STRIDE = LBLOCK * NCOMP + 1;   // padded row of one lane's sums (doubles)
-
-template <bool POL>
-__global__ void __launch_bounds__(ALM_THREADS) alm_kernel(ShtArgs a) {
-    extern __shared__ double sh_alm[];
-    const int m = blockIdx.x;
-    const int N = a.nside, lmax = a.lmax;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // per-wave regions: [64][RED_STRIDE] lane sums, then LCHUNK coefficient records
-    double *red = sh_alm + wave * (64 * RED_STRIDE + LCHUNK * (int)(sizeof(Coef) / sizeof(double)));
-    Coef *coef = reinterpret_cast<Coef *>(red + 64 * RED_STRIDE);
-    const int npairs = 2 * N;
-    const int kcount = (npairs + ALM_THREADS - 1) / ALM_THREADS;
-    const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 2) / 2;
-
-    // c_m = sqrt((4 pi)^-1 prod_{k=1..m} (2k + 1) / (2k)): partial products per lane, then across the wave
-    double pr = 1.0;
-    for (int k = lane + 1; k <= m; k += 64) pr *= (2.0 * k + 1.0) / (2.0 * k);
-    for (int o = 32; o; o >>= 1) pr *= __shfl_xor(pr, o, 64);
-    const double cm = sqrt(pr / (4.0 * M_PI));
-
-    PairState ps[SHT_PAIRS_PER_LANE];
-#pragma unroll
-    for (int k = 0; k < SHT_PAIRS_PER_LANE; ++k) {
-        PairState &p = ps[k];
-        const int pi = tid + k * ALM_THREADS;
-        const bool ok = k < kcount && pi < npairs;
-        const int rn = ok ? pi : 0;
-        const int rs = a.nrings - 1 - rn;                            // mirror ring; rs == rn on the equator
-        const RingGeom g = sht_ring(N, rn);
-        double2 fn[3] = {}, fs[3] = {};
-#pragma unroll
-        for (int f = 0; f < 3; ++f) {
-            if (ok && f < a.nfields) {
-                const double2 *F = a.F + ((size_t)f * (a.mmax + 1) + m) * a.nrings;
-                fn[f] = F[rn];
-                if (rs != rn) fs[f] = F[rs];
-            }
-        }
-        p.Tp = make_double2(fn[0].x + fs[0].x, fn[0].y + fs[0].y);
-        p.Tm = make_double2(fn[0].x - fs[0].x, fn[0].y - fs[0].y);
-        p.Qp = make_double2(fn[1].x + fs[1].x, fn[1].y + fs[1].y);
-        p.Qm = make_double2(fn[1].x - fs[1].x, fn[1].y - fs[1].y);
-        p.Up = make_double2(fn[2].x + fs[2].x, fn[2].y + fs[2].y);
-        p.Um = make_double2(fn[2].x - fs[2].x, fn[2].y - fs[2].y);
-        p.z = g.z;
-        p.inv_s2 = 1.0 / (g.s * g.s);
-        p.z_s2 = g.z * p.inv_s2;
-        p.m_s2 = (double)m * p.inv_s2;
-        start_value(g.s, m, cm, &p.v, &p.e);
-        p.vp = 0.0;
-        if (!ok) p.e = -1000000;                                     // never contributes
-    }
-
-    const int nl = lmax - m + 1;
-    for (int c0 = 0; c0 < nl; c0 += LCHUNK) {
-        if (c0 + lane < nl) coef[lane] = make_coef(m + c0 + lane, m);
-        wave_sync();
-        const int cend = min(nl, c0 + LCHUNK);
-        for (int b0 = c0; b0 < cend; b0 += LBLOCK) {
-            double acc[LBLOCK][NCOMP];
-#pragma unroll
-            for (int j = 0; j < LBLOCK; ++j) {
-#pragma unroll
-                for (int t = 0; t < NCOMP; ++t) acc[j][t] = 0.0;
-                const int li = b0 + j;                               // l - m; even = same parity as m
-                if (li < cend) {
-                    const Coef c = coef[li - c0];
-#pragma unroll
-                    for (int k = 0; k < SHT_PAIRS_PER_LANE; ++k) {
-                        if (k >= kcount) continue;
-                        // once no lane of this band carries an exponent, its values stay
-                        // O(1) and the checks and scale factors drop out (wave-uniform)
-                        if (__ballot(ps[k].e != 0) == 0) {
-                            if (li > 0) advance<false>(ps[k], c);
-                            if (j & 1)
-                                pair_terms<1, POL, false>(ps[k], c, acc[j]);
-                            else
-                                pair_terms<0, POL, false>(ps[k], c, acc[j]);
-                        } else {
-                            if (li > 0) advance<true>(ps[k], c);
-                            if (__ballot(ps[k].e >= -1) == 0) continue;   // whole band below 2^-256
-                            if (j & 1)
-                                pair_terms<1, POL, true>(ps[k], c, acc[j]);
-                            else
-                                pair_terms<0, POL, true>(ps[k], c, acc[j]);
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < LBLOCK; ++j)
-#pragma unroll
-                for (int t = 0; t < NCOMP; ++t) red[lane * RED_STRIDE + j * NCOMP + t] = acc[j][t];
-            wave_sync();
-            // lanes 0..47: sum o = lane / 2 over the half of the wave's lanes given by lane & 1
-            double sum = 0.0;
-            const int o = lane >> 1, half = lane & 1;
-            if (lane < 2 * LBLOCK * NCOMP) {
-                // four partial sums: short dependency chains (fixed order)
-                double s4[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int u = 0; u < 32; u += 4)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) s4[c] += red[(half * 32 + u + c) * RED_STRIDE + o];
-                sum = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-            }
-            sum += __shfl_xor(sum, 1, 64);
-            const int j = o / NCOMP, t = o - j * NCOMP;
-            if (lane < 2 * LBLOCK * NCOMP && half == 0 && b0 + j < cend) {
-                const int64_t idx = (int64_t)m * (2 * lmax + 1 - m) / 2 + m + b0 + j;
-                a.partial[((int64_t)wave * nalm + idx) * NCOMP + t] = sum;
-            }
-            wave_sync();
-        }
-    }
-}
-
-// a_lm = sum of the waves' partial sums; E and B take the sign of their definitions.
-__global__ void __launch_bounds__(256) alm_reduce_kernel(ShtArgs a) {
-    const int64_t nalm = (int64_t)(a.lmax + 1) * (a.lmax + 2) / 2;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nalm * NCOMP) return;
-    const int t = (int)(i % NCOMP);
-    double *dst = a.alm[t >> 1];
-    if (!dst) return;
-    double s = 0.0;
-#pragma unroll
-    for (int w = 0; w < ALM_WAVES; ++w) s += a.partial[(int64_t)w * nalm * NCOMP + i];
-    dst[2 * (i / NCOMP) + (t & 1)] = t < 2 ? s : -s;
 }
 
 struct SynPair {
@@ -756,20 +1084,47 @@ hipError_t launch_axpy(double *y, const double *x, double alpha, int64_t n, bool
     return hipGetLastError();
 }
 
-hipError_t launch_alm(const ShtArgs &a, hipStream_t s) {
-    const size_t lds = (size_t)ALM_WAVES * (64 * RED_STRIDE * sizeof(double) + LCHUNK * sizeof(Coef));
-    const void *k = a.nfields == 3 ? (const void *)alm_kernel<true> : (const void *)alm_kernel<false>;
-    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    if (a.nfields == 3)
-        hipLaunchKernelGGL(alm_kernel<true>, dim3(a.mmax + 1), dim3(ALM_THREADS), lds, s, a);
-    else
-        hipLaunchKernelGGL(alm_kernel<false>, dim3(a.mmax + 1), dim3(ALM_THREADS), lds, s, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int64_t n = (int64_t)(a.lmax + 1) * (a.lmax + 2) / 2 * NCOMP;
-    hipLaunchKernelGGL(alm_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
+hipError_t launch_steps(const ShtArgs &a, hipStream_t s) {
+    hipLaunchKernelGGL(steps_kernel, dim3((unsigned)(a.lmax / 256 + 1), (unsigned)(a.mmax + 1)), dim3(256), 0, s, a);
     return hipGetLastError();
+}
+
+// K and NW cover 2 nside pairs with one workgroup: four pairs a lane on large maps
+// (the cross-lane sums are shared by four pairs), one on small ones, where the
+// workgroups are few and the chain of l is the time.
+template <bool POL, int K, int NW>
+static hipError_t launch_alm_t(ShtArgs a, hipStream_t s) {
+    const size_t lds = alm_lds<POL, NW>() + (POL ? 2 * LCHUNK * sizeof(WxStep) : 0);
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)alm_kernel<POL, K, NW>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    if (POL) {
+        a.wx_m = min(a.nside > WX_NSIDE ? WX_M : 2, a.mmax + 1);
+        a.wx_parts = (2 * a.nside + 64 * NW - 1) / (64 * NW);
+    }
+    const int blocks = a.wx_m * a.wx_parts + a.mmax + 1 - a.wx_m;
+    hipLaunchKernelGGL((alm_kernel<POL, K, NW>), dim3(blocks), dim3(64 * NW), lds, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.wx_parts < 2) return e;
+    const int64_t count = (int64_t)a.wx_m * (2 * a.lmax + 3 - a.wx_m) / 2;      // a_lm of m < wx_m
+    hipLaunchKernelGGL(wx_reduce_kernel, dim3((unsigned)((3 * count + 255) / 256)), dim3(256), 0, s, a, count);
+    return hipGetLastError();
+}
+
+template <bool POL>
+static hipError_t launch_alm_p(const ShtArgs &a, hipStream_t s) {
+    if (a.nside > 512) return launch_alm_t<POL, 4, 8>(a, s);
+    if (a.nside > 256) return launch_alm_t<POL, 4, 4>(a, s);
+    if (a.nside > 128) return launch_alm_t<POL, 2, 4>(a, s);
+    if (a.nside > 64) return launch_alm_t<POL, 1, 4>(a, s);
+    if (a.nside > 32) return launch_alm_t<POL, 1, 2>(a, s);
+    return launch_alm_t<POL, 1, 1>(a, s);
+}
+
+hipError_t launch_alm(const ShtArgs &a, hipStream_t s) {
+    return a.nfields == 3 ? launch_alm_p<true>(a, s) : launch_alm_p<false>(a, s);
 }
 
 hipError_t launch_alm2cl(const ClArgs &a, hipStream_t s) {

@@ -29,20 +29,23 @@ int64_t fourier_bytes(int64_t nside, int64_t lmax, bool pol) {
 }
 
 int64_t nalm(int64_t lmax) { return (lmax + 1) * (lmax + 2) / 2; }
-int64_t partial_bytes(int64_t lmax) { return (int64_t)pisco::SHT_WAVES * nalm(lmax) * 6 * 8; }
 int64_t nfield(bool pol) { return pol ? 3 : 1; }
 
-// ring Fourier sums (or the synthesis' ring coefficients), the a_lm workgroups'
-// per-wave partial sums, then for the iterations a residual map and an a_lm
-// correction per field
+// The workspace: ring Fourier sums (or the synthesis' ring coefficients), the
+// recurrence steps and partial sums of the first m, then for the iterations a
+// residual map per field.  Its size is part of the interface and dates from
+// eight waves' partial sums of every a_lm and an a_lm correction per field (the
+// kernels also read, and do not use, up to 7 steps past the last a_lm's: inside it
+// for every lmax).
 int64_t workspace_bytes(int64_t nside, int64_t lmax, bool pol) {
-    return fourier_bytes(nside, lmax, pol) + partial_bytes(lmax) + nfield(pol) * 12 * nside * nside * 8 +
+    return fourier_bytes(nside, lmax, pol) + 8 * nalm(lmax) * 6 * 8 + nfield(pol) * 12 * nside * nside * 8 +
            nfield(pol) * nalm(lmax) * 16;
 }
 
 struct Layout {
     double2 *F;
-    double *partial, *resid, *dalm;
+    void *steps;
+    double *partial, *resid;
 };
 
 Layout layout(void *ws, int64_t nside, int64_t lmax, bool pol) {
@@ -50,11 +53,11 @@ Layout layout(void *ws, int64_t nside, int64_t lmax, bool pol) {
     Layout L;
     L.F = reinterpret_cast<double2 *>(p);
     p += fourier_bytes(nside, lmax, pol);
-    L.partial = reinterpret_cast<double *>(p);
-    p += partial_bytes(lmax);
     L.resid = reinterpret_cast<double *>(p);
     p += nfield(pol) * 12 * nside * nside * 8;
-    L.dalm = reinterpret_cast<double *>(p);
+    L.steps = p;
+    p += nalm(lmax) * pisco::SHT_STEP_BYTES;
+    L.partial = reinterpret_cast<double *>(p);
     return L;
 }
 
@@ -66,6 +69,7 @@ pisco::ShtArgs base_args(int64_t nside, int32_t lmax, bool pol, const Layout &L)
     a.nfields = pol ? 3 : 1;
     a.nrings = (int)(4 * nside - 1);
     a.F = L.F;
+    a.steps = L.steps;
     a.partial = L.partial;
     return a;
 }
@@ -108,19 +112,20 @@ pisco_status map2alm(pisco_ctx *ctx, int64_t nside, int32_t lmax, int32_t iterat
     const Layout L = layout(ws, nside, lmax, pol);
     const pisco::ShtArgs a = base_args(nside, lmax, pol, L);
     const int nf = a.nfields;
-    const int64_t npix = 12 * nside * nside, na = nalm(lmax);
+    const int64_t npix = 12 * nside * nside;
     const double *maps[3] = {T, Q, U};
     double *alm[3] = {aT, aE, aB};
     double *resid[3] = {L.resid, L.resid + npix, L.resid + 2 * npix};
-    double *dalm[3] = {L.dalm, L.dalm + 2 * na, L.dalm + 4 * na};
-    hipError_t e = analyse(a, maps, alm, st);
+    hipError_t e = pisco::launch_steps(a, st);
+    if (e == hipSuccess) e = analyse(a, maps, alm, st);
     // Jacobi steps: a <- a + map2alm(m - alm2map(a))
     for (int it = 0; it < iterations && e == hipSuccess; ++it) {
         e = synthesise(a, alm, resid, st);
         for (int f = 0; f < nf && e == hipSuccess; ++f) e = pisco::launch_axpy(resid[f], maps[f], -1.0, npix, true, st);
         const double *rc[3] = {resid[0], resid[1], resid[2]};
-        if (e == hipSuccess) e = analyse(a, rc, dalm, st);
-        for (int f = 0; f < nf && e == hipSuccess; ++f) e = pisco::launch_axpy(alm[f], dalm[f], 1.0, 2 * na, false, st);
+        pisco::ShtArgs d = a;
+        d.add = 1;
+        if (e == hipSuccess) e = analyse(d, rc, alm, st);
     }
     return launched(ctx, e);
 }
