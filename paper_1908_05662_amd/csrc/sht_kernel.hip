@@ -17,7 +17,7 @@
 //                        accumulate against the pair's ring sums; every four l a
 //                        wave adds its lanes, every 64 l the workgroup its waves;
 //   alm2cl_kernel        one wave per l: C_l of up to six a_lm pairs;
-//   alm2ring_kernel      the synthesis: one workgroup per m, lanes own ring pairs
+//   alm2ring_kernel      the synthesis: the same recurrences, lanes own ring pairs
 //                        and sum over l in registers (no cross-lane sums);
 //   ring_synth_kernel    one workgroup per ring: the m sums folded onto the ring
 //                        length, then the same LDS FFT as the analysis.
@@ -31,7 +31,6 @@ namespace pisco {
 namespace {
 
 constexpr int SCALE = 256;               // exponent step of the carried recurrence
-constexpr int LBLOCK = 4;                // l values per LDS reduction
 constexpr int NCOMP = 6;                 // a^T, a^E, a^B (re, im)
 constexpr int LCHUNK = 64;               // l values per coefficient table
 
@@ -203,7 +202,7 @@ static_assert(sizeof(Step) == SHT_STEP_BYTES, "size of the steps in the workspac
 // The steps of every (l, m), packed like the a_lm: written once per call, then
 // read with scalar loads (a step is uniform over a workgroup), so that no vector
 // register or LDS read is spent on them.  The first (l = m) gives g_l = -g_{l-2},
-// see start_pair; f is for m >= 2.
+// see start_pair.
 __global__ void __launch_bounds__(256) steps_kernel(ShtArgs a) {
     const int m = blockIdx.y, l = m + (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (l > a.lmax) return;
@@ -215,7 +214,7 @@ __global__ void __launch_bounds__(256) steps_kernel(ShtArgs a) {
         s.aT = sqrt(q / p);
         s.bT = sqrt(p1 / q1);
     }
-    if (l > m && m >= 2) {
+    if (l > max(m, 2)) {
         const double u = (dl - 2.0) * (dl + 2.0), u1 = (d1 - 2.0) * (d1 + 2.0);
         s.aS = dl * sqrt(q / (p * u));
         s.bS = sqrt(p1 * u1 / q1) / d1;
@@ -230,6 +229,29 @@ __device__ inline uniform_ptr steps_of(const ShtArgs &a, int64_t index) {
     return (uniform_ptr)(unsigned long long)(static_cast<const Step *>(a.steps) + index);
 }
 __device__ inline Step load_step(uniform_ptr p) { return Step{p[0], p[1], p[2], p[3], p[4], p[5]}; }
+
+// Small maps have few waves to hide the scalar loads' misses behind (a step is a
+// new cache line every 1.3 l, 480 clocks per l at nside 128): there a workgroup
+// copies the steps (or the a_lm) of 64 l at a time into LDS, fetched while the
+// 64 before are used.
+template <int NT, int W>                 // W doubles per l
+struct Staged {
+    static constexpr int PER = (LCHUNK * W + NT - 1) / NT;
+    double r[PER];
+    // values first .. first + LCHUNK W of an array, as far as it has `count`
+    __device__ inline void fetch(const double *src, int64_t first, int64_t count, int tid) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int64_t at = first + i * NT + tid;
+            r[i] = i * NT + tid < LCHUNK * W && at < count ? src[at] : 0.0;
+        }
+    }
+    __device__ inline void put(double *dst, int tid) const {
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (i * NT + tid < LCHUNK * W) dst[i * NT + tid] = r[i];
+    }
+};
 
 // A ring pair's functions before the step to l = m, in units of 2^(SCALE e).
 struct PairState {
@@ -311,8 +333,8 @@ __device__ inline void advance(PairState &p, const Step &c) {
     }
 }
 
-// After LBLOCK steps of a lane with e < 0 (a step grows by less than 2^16, and f
-// differs from lambda by less than 2^24, so nothing overflows in between).
+// After up to eight steps of a lane with e < 0 (a step grows by less than 2^16, and
+// f differs from lambda by less than 2^24, so nothing overflows in between).
 template <bool POL>
 __device__ inline void rescale(PairState &p) {
     if (fabs(p.v) > 0x1p128) {
@@ -374,20 +396,20 @@ __device__ inline void pair_terms(const PairState &p, const PairSums &f, double 
     }
 }
 
-// LBLOCK steps of one pair from l - m = 0 mod LBLOCK, its terms added to acc[l][comp].
-template <bool POL, bool POLAR>
+// LB steps of one pair, its terms added to acc[l][comp].
+template <bool POL, bool POLAR, int LB>
 __device__ inline void block_terms(PairState &p, const PairSums &f, const Step *st, double *acc) {
     constexpr int NC = POL ? NCOMP : 2;
     if (p.e >= 0) {
 #pragma unroll
-        for (int j = 0; j < LBLOCK; ++j) {
+        for (int j = 0; j < LB; ++j) {
             advance<POL, POLAR>(p, st[j]);
             if (j & 1) pair_terms<true, POL>(p, f, acc + j * NC);
             else pair_terms<false, POL>(p, f, acc + j * NC);
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < LBLOCK; ++j) advance<POL, POLAR>(p, st[j]);
+        for (int j = 0; j < LB; ++j) advance<POL, POLAR>(p, st[j]);
         rescale<POL>(p);
     }
 }
@@ -415,36 +437,49 @@ __device__ inline double swap_add(double x, double y) {
 // partial sums of each of a block's sums (rows of 17)
 template <bool POL>
 constexpr int alm_comps() { return POL ? NCOMP : 2; }
-template <bool POL, int NW>
+template <bool POL, int NW, int LB>
 constexpr size_t alm_lds() {
-    return (2 * LCHUNK * alm_comps<POL>() + LBLOCK * alm_comps<POL>() * 17) * NW * sizeof(double);
+    return (2 * LCHUNK * alm_comps<POL>() + LB * alm_comps<POL>() * 17) * NW * sizeof(double);
 }
 
-// The wave's sums of NS values over its lanes, to dst[0 .. NS): 64 lanes to 16 by
-// exchanges (row i of a set of four then holds value 0, 2, 1, 3), the rest
-// through LDS, in a fixed order.
+// The wave's sums of NS values over its lanes: 64 lanes to 16 by exchanges (row i
+// of a set of four then holds value 0, 2, 1, 3) into LDS, the rest from there, in a
+// fixed order.  The second half is left to the next block: its LDS reads are
+// issued before that block's arithmetic and added after it.
 template <int NS>
-__device__ inline void wave_sums(const double *acc, double *red, double *dst, int lane) {
-    constexpr int PARTS = 64 / NS >= 8 ? 8 : 2;                  // lanes that share one sum
-    double h[NS / 2];
+struct WaveSums {
+    static constexpr int PARTS = NS > 32 ? 1 : 64 / NS >= 8 ? 8 : 64 / NS >= 4 ? 4 : 2;   // lanes that share one sum
+    static_assert(NS % 4 == 0 && NS * PARTS <= 64, "one sum a lane group");
+    double q[16 / PARTS];
+    double *dst;            // where the values in LDS belong; null: none
+    __device__ inline void push(const double *acc, double *red, int lane, double *to) {
+        double h[NS / 2];
 #pragma unroll
-    for (int t = 0; t < NS / 2; ++t) h[t] = swap_add<32>(acc[2 * t], acc[2 * t + 1]);
+        for (int t = 0; t < NS / 2; ++t) h[t] = swap_add<32>(acc[2 * t], acc[2 * t + 1]);
 #pragma unroll
-    for (int t = 0; t < NS / 4; ++t)
-        red[(4 * t + (lane >> 4)) * 17 + (lane & 15)] = swap_add<16>(h[2 * t], h[2 * t + 1]);
-    wave_sync();
-    const int o = lane / PARTS, part = lane % PARTS;
-    double sum = 0.0;
-    if (o < NS) {
-        const double *q = red + ((o & ~3) + ((o & 1) << 1 | (o >> 1 & 1))) * 17 + part;
-#pragma unroll
-        for (int u = 0; u < 16; u += PARTS) sum += q[u];
+        for (int t = 0; t < NS / 4; ++t)
+            red[(4 * t + (lane >> 4)) * 17 + (lane & 15)] = swap_add<16>(h[2 * t], h[2 * t + 1]);
+        wave_sync();
+        dst = to;
     }
+    __device__ inline void load(const double *red, int lane) {
+        const int o = min(lane / PARTS, NS - 1), part = lane % PARTS;
+        const double *p = red + ((o & ~3) + ((o & 1) << 1 | (o >> 1 & 1))) * 17 + part;
 #pragma unroll
-    for (int x = 1; x < PARTS; x <<= 1) sum += __shfl_xor(sum, x, 64);
-    if (part == 0 && o < NS) dst[o] = sum;
-    wave_sync();
-}
+        for (int u = 0; u < 16 / PARTS; ++u) q[u] = p[u * PARTS];
+    }
+    __device__ inline void store(int lane) {
+#pragma unroll
+        for (int w = 8 / PARTS; w; w >>= 1)
+#pragma unroll
+            for (int u = 0; u < w; ++u) q[u] += q[u + w];
+        double sum = q[0];
+#pragma unroll
+        for (int x = 1; x < PARTS; x <<= 1) sum += __shfl_xor(sum, x, 64);
+        if (lane % PARTS == 0 && lane / PARTS < NS) dst[lane / PARTS] = sum;
+        wave_sync();
+    }
+};
 
 // ----------------------------------------------------------------------
 // The polarised analysis of the first m forms W and X from lambda_l and
@@ -483,9 +518,9 @@ __device__ inline WxStep wx_step(int l, int m) {
 }
 
 // LDS: as alm_kernel's, then two chunks of steps
-template <int NW>
+template <int NW, int LB>
 __device__ void alm_wx(const ShtArgs &a, int m, int part, int tid, double *lds) {
-    constexpr int NS = LBLOCK * NCOMP, NT = 64 * NW;
+    constexpr int NS = LB * NCOMP, NT = 64 * NW;
     const int lane = tid & 63, wave = tid >> 6;
     double *red = lds + 2 * NW * LCHUNK * NCOMP + wave * NS * 17;
     WxStep *steps = reinterpret_cast<WxStep *>(lds + (2 * LCHUNK * NCOMP + NS * 17) * NW);
@@ -515,13 +550,15 @@ __device__ void alm_wx(const ShtArgs &a, int m, int part, int tid, double *lds) 
     const int64_t base = (int64_t)m * (2 * a.lmax + 1 - m) / 2 + m, nalm = (int64_t)(a.lmax + 1) * (a.lmax + 2) / 2;
     if (wave == 0) steps[lane] = wx_step(m + lane, m);
     __syncthreads();
+    WaveSums<NS> ws;
     for (int c0 = 0, ch = 0; c0 < nl; c0 += LCHUNK, ++ch) {
         if (wave == (ch + 1) % NW) steps[((ch + 1) & 1) * LCHUNK + lane] = wx_step(m + c0 + LCHUNK + lane, m);
         const int cend = min(nl - c0, LCHUNK);
-        for (int b0 = 0; b0 < cend; b0 += LBLOCK) {
+        for (int b0 = 0; b0 < cend; b0 += LB) {
             double acc[NS];
+            if (b0) ws.load(red, lane);
 #pragma unroll
-            for (int j = 0; j < LBLOCK; ++j) {
+            for (int j = 0; j < LB; ++j) {
                 const WxStep c = steps[(ch & 1) * LCHUNK + b0 + j];
                 const double vn = c.ra * fma(p.z, p.v, -c.rb * p.vp);
                 p.vp = p.v;
@@ -541,8 +578,11 @@ __device__ void alm_wx(const ShtArgs &a, int m, int part, int tid, double *lds) 
                 x[5] = fma(-X, Qb.x, W * Ua.y);
             }
             if (p.e < 0) rescale<false>(p);
-            wave_sums<NS>(acc, red, lds + (((ch & 1) * NW + wave) * LCHUNK + b0) * NCOMP, lane);
+            if (b0) ws.store(lane);
+            ws.push(acc, red, lane, lds + (((ch & 1) * NW + wave) * LCHUNK + b0) * NCOMP);
         }
+        ws.load(red, lane);
+        ws.store(lane);
         __syncthreads();
         const double *all = lds + (ch & 1) * NW * LCHUNK * NCOMP;
         if (a.wx_parts > 1) {
@@ -568,24 +608,25 @@ __device__ void alm_wx(const ShtArgs &a, int m, int part, int tid, double *lds) 
 }
 
 // One workgroup of NW waves per m, K ring pairs a lane (64 K NW >= 2 nside).
-// Bound by FP64 issue: 19 instructions per (l, pair) and, per four l and wave,
-// the 24 cross-lane sums (36 lane exchanges and 18 adds, then 6 writes and 8
-// reads of LDS).  A pair whose values are still negligible (e < 0) only steps.
+// Bound by FP64 issue: 19 instructions per (l, pair) and, per LB l and wave,
+// the 6 LB cross-lane sums (at LB = 4: 36 lane exchanges and 18 adds, then 6 writes
+// and 8 reads of LDS).  A pair whose values are still negligible (e < 0) only steps.
 // The waves' sums meet in LDS once per 64 l, in a fixed order.  The first band of
 // pairs takes the polar form (all of them with one pair a lane).  At nside 1024,
 // lmax 3071: 8.6 ms, 25 vector instructions per (l, band of 64 pairs), the vector
 // ALU issuing 80% of the time; 16.5 ms and 43 when W and X were formed from
 // lambda, most values carried an exponent, and each (l, pair) had branches of its
-// own.  nside 128, lmax 383: see launch_alm_p.
-template <bool POL, int K, int NW>
+// own.  Small maps: see launch_alm_t.
+template <bool POL, int K, int NW, int LB>
 __global__ void __launch_bounds__(64 * NW, K >= 4 ? 2 : 1) alm_kernel(ShtArgs a) {
-    constexpr int NC = alm_comps<POL>(), NS = LBLOCK * NC, NT = 64 * NW;
-    extern __shared__ double sh_alm[];                               // [2][NW][LCHUNK][NC], [NW][NS * 17]
+    constexpr int NC = alm_comps<POL>(), NS = LB * NC, NT = 64 * NW;
+    constexpr bool STAGE = K == 1;
+    extern __shared__ double sh_alm[];                               // [2][NW][LCHUNK][NC], [NW][NS * 17], 2 chunks of steps
     const int N = a.nside, lmax = a.lmax;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wx = a.wx_m * a.wx_parts;
     if (POL && (int)blockIdx.x < wx) {
-        alm_wx<NW>(a, blockIdx.x / a.wx_parts, blockIdx.x % a.wx_parts, tid, sh_alm);
+        alm_wx<NW, LB>(a, blockIdx.x / a.wx_parts, blockIdx.x % a.wx_parts, tid, sh_alm);
         return;
     }
     const int m = a.wx_m + (int)blockIdx.x - wx;
@@ -623,26 +664,51 @@ __global__ void __launch_bounds__(64 * NW, K >= 4 ? 2 : 1) alm_kernel(ShtArgs a)
 
     const int nl = lmax - m + 1;
     const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2 + m;     // index of l = m
-    Step s[LBLOCK];                                                   // steps past lmax: not used (see the workspace)
+    constexpr int SD = sizeof(Step) / sizeof(double);
+    const int64_t nsteps = (int64_t)(lmax + 1) * (lmax + 2) / 2 * SD;
+    const double *steps = static_cast<const double *>(a.steps);
+    double *staged = sh_alm + (2 * LCHUNK * NC + NS * 17) * NW;
+    Staged<NT, SD> sg;
+    Step s[LB];                                                   // steps past lmax: not used (see the workspace)
+    if constexpr (STAGE) {
+        sg.fetch(steps, base * SD, nsteps, tid);
+        sg.put(staged, tid);
+        __syncthreads();
+    } else {
 #pragma unroll
-    for (int j = 0; j < LBLOCK; ++j) s[j] = load_step(steps_of(a, base + j));
+        for (int j = 0; j < LB; ++j) s[j] = load_step(steps_of(a, base + j));
+    }
+    WaveSums<NS> ws;
     for (int c0 = 0, ch = 0; c0 < nl; c0 += LCHUNK, ++ch) {
+        const Step *st = reinterpret_cast<const Step *>(staged) + (ch & 1) * LCHUNK;
+        if constexpr (STAGE) sg.fetch(steps, (base + c0 + LCHUNK) * SD, nsteps, tid);
         double *mine = sh_alm + ((ch & 1) * NW + wave) * LCHUNK * NC;
         const int cend = min(nl - c0, LCHUNK);
-        for (int b0 = 0; b0 < cend; b0 += LBLOCK) {
+        for (int b0 = 0; b0 < cend; b0 += LB) {
             double acc[NS];
 #pragma unroll
             for (int t = 0; t < NS; ++t) acc[t] = 0.0;
+            if (b0) ws.load(red, lane);
+            if constexpr (STAGE) {
+#pragma unroll
+                for (int j = 0; j < LB; ++j) s[j] = st[b0 + j];
+            }
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                if (k == 0) block_terms<POL, true>(ps[k], f[k], s, acc);
-                else block_terms<POL, false>(ps[k], f[k], s, acc);
+                if (k == 0) block_terms<POL, true, LB>(ps[k], f[k], s, acc);
+                else block_terms<POL, false, LB>(ps[k], f[k], s, acc);
             }
-            // the next block's steps, in flight during the sums
+            if constexpr (!STAGE) {
+                // the next block's steps, in flight during the sums
 #pragma unroll
-            for (int j = 0; j < LBLOCK; ++j) s[j] = load_step(steps_of(a, base + c0 + b0 + LBLOCK + j));
-            wave_sums<NS>(acc, red, mine + b0 * NC, lane);
+                for (int j = 0; j < LB; ++j) s[j] = load_step(steps_of(a, base + c0 + b0 + LB + j));
+            }
+            if (b0) ws.store(lane);
+            ws.push(acc, red, lane, mine + b0 * NC);
         }
+        ws.load(red, lane);
+        ws.store(lane);
+        if constexpr (STAGE) sg.put(staged + ((ch + 1) & 1) * LCHUNK * SD, tid);
         __syncthreads();
         // a_lm of the chunk: the waves' sums in order, and a^E, a^B from S+, S-
         const double *all = sh_alm + (ch & 1) * NW * LCHUNK * NC;
@@ -686,198 +752,253 @@ __global__ void __launch_bounds__(256) wx_reduce_kernel(ShtArgs a, int64_t count
     put_alm(a, a.alm[c] + 2 * (i / 3), c ? -re : re, c ? -im : im);
 }
 
-struct Coef {
-    double ra, rb;           // lambda_l = ra (z lambda_{l-1} - rb lambda_{l-2})
-    double A, B, C, D;       // n_l (l - m^2), n_l l (l - 1) / 2, n_l (l + m) c_lm, n_l (l - 1)
-};
-
-__device__ inline Coef make_coef(int l, int m) {
-    Coef c{};
-    const double dl = l, dm = m;
-    if (l == m + 1) c.ra = sqrt(2.0 * dm + 3.0);
-    if (l >= m + 2) {
-        c.ra = sqrt((4.0 * dl * dl - 1.0) / (dl * dl - dm * dm));
-        c.rb = sqrt(((dl - 1.0) * (dl - 1.0) - dm * dm) / (4.0 * (dl - 1.0) * (dl - 1.0) - 1.0));
-    }
-    if (l >= 2) {
-        const double nl = 2.0 / sqrt((dl - 1.0) * dl * (dl + 1.0) * (dl + 2.0));
-        const double clm = l > m ? sqrt((2.0 * dl + 1.0) * (dl - dm) / ((2.0 * dl - 1.0) * (dl + dm))) : 0.0;
-        c.A = nl * (dl - dm * dm);
-        c.B = nl * dl * (dl - 1.0) * 0.5;
-        c.C = nl * (dl + dm) * clm;
-        c.D = nl * (dl - 1.0);
-    }
-    return c;
-}
-
-// lambda_mm = (-1)^m c_m s^m, split into a mantissa and a multiple of SCALE in the exponent
-__device__ inline void start_value(double s, int m, double cm, double *v, int *e) {
-    int es;
-    const double fs = frexp(s, &es);
-    double base = fs, res = 1.0;
-    long long be = 0, re = 0;
-    for (int k = m; k; k >>= 1) {
-        int t;
-        if (k & 1) {
-            res = frexp(res * base, &t);
-            re += be + t;
-        }
-        base = frexp(base * base, &t);
-        be = 2 * be + t;
-    }
-    const long long E = re + (long long)es * m;
-    long long q = E / SCALE;
-    if (q * SCALE > E) --q;                       // floor
-    *e = (int)q;
-    *v = ((m & 1) ? -cm : cm) * ldexp(res, (int)(E - q * SCALE));
-}
-
-struct SynPair {
-    double z, inv_s2, z_s2, m_s2;
-    double v, vp;
-    int e;
-    double2 acc[3][2];                 // [field][class]: north-ring sums split by their south sign
-};
-
-// Adds one l to the pair's sums: lambda and W terms go to class P = (l + m) & 1
-// (south value (-1)^(l+m) times the north one), X terms to class 1 - P.
-template <int P, bool POL, bool SCALED>
-__device__ inline void syn_terms(SynPair &p, const Coef &c, const double *al) {
-    double L = p.v, Lp = p.vp;
-    if (SCALED) {
-        const double f = p.e == 0 ? 1.0 : (p.e == -1 ? 0x1p-256 : 0.0);
-        L *= f;
-        Lp *= f;
-    }
-    const double2 aT = make_double2(al[0], al[1]);
-    p.acc[0][P].x = fma(L, aT.x, p.acc[0][P].x);
-    p.acc[0][P].y = fma(L, aT.y, p.acc[0][P].y);
-    if (POL) {
-        const double2 aE = make_double2(al[2], al[3]), aB = make_double2(al[4], al[5]);
-        const double W = fma(-fma(c.A, p.inv_s2, c.B), L, c.C * p.z_s2 * Lp);
-        const double X = p.m_s2 * fma(c.C, Lp, -c.D * p.z * L);
-        // Q: -(aE W + i aB X);  U: -(aB W - i aE X)
-        p.acc[1][P].x = fma(-W, aE.x, p.acc[1][P].x);
-        p.acc[1][P].y = fma(-W, aE.y, p.acc[1][P].y);
-        p.acc[1][1 - P].x = fma(X, aB.y, p.acc[1][1 - P].x);
-        p.acc[1][1 - P].y = fma(-X, aB.x, p.acc[1][1 - P].y);
-        p.acc[2][P].x = fma(-W, aB.x, p.acc[2][P].x);
-        p.acc[2][P].y = fma(-W, aB.y, p.acc[2][P].y);
-        p.acc[2][1 - P].x = fma(-X, aE.y, p.acc[2][1 - P].x);
-        p.acc[2][1 - P].y = fma(X, aE.x, p.acc[2][1 - P].y);
-    }
-}
-
-template <bool SCALED>
-__device__ inline void syn_advance(SynPair &p, const Coef &c) {
-    const double vn = c.ra * fma(p.z, p.v, -c.rb * p.vp);
-    p.vp = p.v;
-    p.v = vn;
-    if (SCALED && fabs(vn) > 0x1p256) {
-        p.v *= 0x1p-256;
-        p.vp *= 0x1p-256;
-        p.e += 1;
-    }
-}
-
-// Synthesis workgroups: 12 waves of up to three ring pairs per lane (2304 >= 2N
-// at the largest nside), three waves per SIMD.
-constexpr int SYN_THREADS = 768;
-constexpr int SYN_PAIRS = 3;
-static_assert(SYN_THREADS * SYN_PAIRS >= 2 * SHT_MAX_NSIDE, "ring pairs per workgroup");
-
+// ----------------------------------------------------------------------
+// Synthesis: the sums over l of each ring pair, G_m = sum_l a_lm lambda_lm and
+// P_m, M_m (see above), in the lane's registers: no cross-lane sums.
+// ----------------------------------------------------------------------
+// The a_lm of one l (uniform over the workgroup: scalar loads), T then E, B.
+typedef const double __attribute__((address_space(4))) *uniform_alm;
 template <bool POL>
-__global__ void __launch_bounds__(SYN_THREADS) alm2ring_kernel(ShtArgs a) {
-    extern __shared__ double sh_syn[];
+struct SynAlm {
+    double t[2], e[2], b[2];
+    __device__ inline void load(const ShtArgs &a, int64_t i) {
+        const uniform_alm T = (uniform_alm)(unsigned long long)(a.alm_in[0] + 2 * i);
+        t[0] = T[0];
+        t[1] = T[1];
+        if (POL) {
+            const uniform_alm E = (uniform_alm)(unsigned long long)(a.alm_in[1] + 2 * i);
+            const uniform_alm B = (uniform_alm)(unsigned long long)(a.alm_in[2] + 2 * i);
+            e[0] = E[0];
+            e[1] = E[1];
+            b[0] = B[0];
+            b[1] = B[1];
+        }
+    }
+};
+
+// Sums of one pair: T split by the parity of l - m (the south takes the odd ones
+// with a minus sign), and -P, -M of each hemisphere.
+struct SynSums {
+    double2 Te, To, Pn, Ps, Mn, Ms;
+};
+
+template <bool POL, bool POLAR, int LB>
+__device__ inline void syn_block(PairState &p, SynSums &f, const Step *st, const SynAlm<POL> *al) {
+    if (p.e >= 0) {
+#pragma unroll
+        for (int j = 0; j < LB; ++j) {
+            advance<POL, POLAR>(p, st[j]);
+            double2 &T = (j & 1) ? f.To : f.Te;
+            T.x = fma(p.v, al[j].t[0], T.x);
+            T.y = fma(p.v, al[j].t[1], T.y);
+            if (POL) {
+                // a^E + i a^B with f^+, a^E - i a^B with f^-; the south's exchanged, times (-1)^(l+m)
+                const double px = al[j].e[0] - al[j].b[1], py = al[j].e[1] + al[j].b[0];
+                const double mx = al[j].e[0] + al[j].b[1], my = al[j].e[1] - al[j].b[0];
+                const double sp = (j & 1) ? -p.fp : p.fp, sm = (j & 1) ? -p.fm : p.fm;
+                f.Pn.x = fma(p.fp, px, f.Pn.x);
+                f.Pn.y = fma(p.fp, py, f.Pn.y);
+                f.Ps.x = fma(sm, px, f.Ps.x);
+                f.Ps.y = fma(sm, py, f.Ps.y);
+                f.Mn.x = fma(p.fm, mx, f.Mn.x);
+                f.Mn.y = fma(p.fm, my, f.Mn.y);
+                f.Ms.x = fma(sp, mx, f.Ms.x);
+                f.Ms.y = fma(sp, my, f.Ms.y);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < LB; ++j) advance<POL, POLAR>(p, st[j]);
+        rescale<POL>(p);
+    }
+}
+
+// One l of either parity, for the ends of the loop.
+template <bool POL>
+__device__ inline void syn_one(PairState &p, SynSums &f, const Step &st, const SynAlm<POL> &al, bool odd) {
+    advance<POL, true>(p, st);
+    if (p.e < 0) {
+        rescale<POL>(p);
+        return;
+    }
+    const double s = odd ? -1.0 : 1.0;
+    double2 &T = odd ? f.To : f.Te;
+    T.x = fma(p.v, al.t[0], T.x);
+    T.y = fma(p.v, al.t[1], T.y);
+    if (POL) {
+        const double px = al.e[0] - al.b[1], py = al.e[1] + al.b[0], mx = al.e[0] + al.b[1], my = al.e[1] - al.b[0];
+        f.Pn.x = fma(p.fp, px, f.Pn.x);
+        f.Pn.y = fma(p.fp, py, f.Pn.y);
+        f.Ps.x = fma(s * p.fm, px, f.Ps.x);
+        f.Ps.y = fma(s * p.fm, py, f.Ps.y);
+        f.Mn.x = fma(p.fm, mx, f.Mn.x);
+        f.Mn.y = fma(p.fm, my, f.Mn.y);
+        f.Ms.x = fma(s * p.fp, mx, f.Ms.x);
+        f.Ms.y = fma(s * p.fp, my, f.Ms.y);
+    }
+}
+
+// m < 2: f^+- start at l = 2, so that the step there (which gives -f_prev) yields
+//   f^+-_21 = -+ sqrt(5 / 16 pi) s (1 -+ z),  f^+-_20 = sqrt(15 / 32 pi) s^2;
+// none below.
+__device__ inline void late_start(PairState &p, const RingGeom &g, int m) {
+    const double c = m ? sqrt(5.0 / (16.0 * M_PI)) : sqrt(15.0 / (32.0 * M_PI));
+    p.fp = p.fm = 0.0;
+    p.fpp = m ? c * g.s * g.omz : -c * g.s * g.s;
+    p.fmp = m ? -c * g.s * (1.0 + g.z) : -c * g.s * g.s;
+}
+
+// One workgroup of NW waves per m, K ring pairs a lane, LB l a step of the loop.
+// Bound by FP64 issue: 19 instructions per (l, pair); at nside 128, lmax 383 by the
+// chain of l (1.5 waves a SIMD): 42 us, 114 with W and X in 768-lane workgroups.
+template <bool POL, int K, int NW, int LB>
+__global__ void __launch_bounds__(64 * NW, K >= 4 ? 2 : 1) alm2ring_kernel(ShtArgs a) {
+    constexpr int NT = 64 * NW;
     const int m = blockIdx.x;
     const int N = a.nside, lmax = a.lmax;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    constexpr int CW = (int)(sizeof(Coef) / sizeof(double));
-    double *al = sh_syn + wave * LCHUNK * (CW + NCOMP);             // per wave: [LCHUNK][6] a_lm values
-    Coef *coef = reinterpret_cast<Coef *>(al + LCHUNK * NCOMP);     // then [LCHUNK] coefficient records
+    const int tid = threadIdx.x, lane = tid & 63;
     const int npairs = 2 * N;
-    const int kcount = (npairs + SYN_THREADS - 1) / SYN_THREADS;
-
-    double pr = 1.0;
-    for (int k = lane + 1; k <= m; k += 64) pr *= (2.0 * k + 1.0) / (2.0 * k);
-    for (int o = 32; o; o >>= 1) pr *= __shfl_xor(pr, o, 64);
-    const double cm = sqrt(pr / (4.0 * M_PI));
-
-    SynPair ps[SYN_PAIRS];
+    const double cm = start_norm(m, lane);
+    PairState ps[K];
+    SynSums f[K];
 #pragma unroll
-    for (int k = 0; k < SYN_PAIRS; ++k) {
-        SynPair &p = ps[k];
-        const int pi = tid + k * SYN_THREADS;
-        const bool ok = k < kcount && pi < npairs;
-        const RingGeom g = sht_ring(N, ok ? pi : 0);
-        p.z = g.z;
-        p.inv_s2 = 1.0 / (g.s * g.s);
-        p.z_s2 = g.z * p.inv_s2;
-        p.m_s2 = (double)m * p.inv_s2;
-        start_value(g.s, m, cm, &p.v, &p.e);
-        p.vp = 0.0;
-        if (!ok) p.e = -1000000;
-#pragma unroll
-        for (int f = 0; f < 3; ++f) p.acc[f][0] = p.acc[f][1] = make_double2(0.0, 0.0);
+    for (int k = 0; k < K; ++k) {
+        const int pi = tid + k * NT;
+        const bool ok = pi < npairs;
+        ps[k] = start_pair(sht_ring(N, ok ? pi : 0), m, cm, ok);
+        f[k].Te = f[k].To = f[k].Pn = f[k].Ps = f[k].Mn = f[k].Ms = make_double2(0.0, 0.0);
     }
-
-    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;        // index of (l = 0, m) minus 0: + l
     const int nl = lmax - m + 1;
-    for (int c0 = 0; c0 < nl; c0 += LCHUNK) {
-        if (c0 + lane < nl) {
-            const int l = m + c0 + lane;
-            coef[lane] = make_coef(l, m);
+    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2 + m;     // index of l = m
+    int li = 0;                                                       // l - m
+    if (POL && m < 2) {
+        // up to l = 3, one by one
+        for (; li <= 3 - m && li < nl; ++li) {
+            const Step s = load_step(steps_of(a, base + li));
+            SynAlm<POL> al;
+            al.load(a, base + li);
 #pragma unroll
-            for (int f = 0; f < 3; ++f) {
-                const double *src = a.alm_in[f];
-                const bool use = src && (f == 0 || POL);
-                al[lane * NCOMP + 2 * f] = use ? src[2 * (base + l)] : 0.0;
-                al[lane * NCOMP + 2 * f + 1] = use ? src[2 * (base + l) + 1] : 0.0;
+            for (int k = 0; k < K; ++k) {
+                const int pi = tid + k * NT;
+                if (m + li < 2) ps[k].fp = ps[k].fm = ps[k].fpp = ps[k].fmp = 0.0;
+                if (m + li == 2 && pi < npairs) late_start(ps[k], sht_ring(N, pi), m);
+                syn_one<POL>(ps[k], f[k], s, al, li & 1);
             }
         }
-        wave_sync();
-        const int cend = min(nl, c0 + LCHUNK);
-        for (int b0 = c0; b0 < cend; b0 += 2) {
+        if ((li & 1) && li < nl) {                                    // to an even l - m
+            const Step s = load_step(steps_of(a, base + li));
+            SynAlm<POL> al;
+            al.load(a, base + li);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int li = b0 + j;                                // l - m; even = class 0
-                if (li >= cend) break;
-                const Coef c = coef[li - c0];
-                const double *A = al + (li - c0) * NCOMP;
+            for (int k = 0; k < K; ++k) syn_one<POL>(ps[k], f[k], s, al, true);
+            ++li;
+        }
+    }
+    if constexpr (K == 1) {
+        // 64 l at a time from LDS
+        constexpr int SD = sizeof(Step) / sizeof(double);
+        __shared__ double st[2][LCHUNK * SD], al[POL ? 3 : 1][2][LCHUNK * 2];
+        const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 2) / 2;
+        Staged<NT, SD> gs;
+        Staged<NT, 2> ga[POL ? 3 : 1];
+        auto fetch = [&](int from) {
+            gs.fetch(static_cast<const double *>(a.steps), (base + from) * SD, nalm * SD, tid);
 #pragma unroll
-                for (int k = 0; k < SYN_PAIRS; ++k) {
-                    if (k >= kcount) continue;
-                    if (__ballot(ps[k].e != 0) == 0) {
-                        if (li > 0) syn_advance<false>(ps[k], c);
-                        if (j)
-                            syn_terms<1, POL, false>(ps[k], c, A);
-                        else
-                            syn_terms<0, POL, false>(ps[k], c, A);
-                    } else {
-                        if (li > 0) syn_advance<true>(ps[k], c);
-                        if (__ballot(ps[k].e >= -1) == 0) continue;
-                        if (j)
-                            syn_terms<1, POL, true>(ps[k], c, A);
-                        else
-                            syn_terms<0, POL, true>(ps[k], c, A);
-                    }
+            for (int c = 0; c < (POL ? 3 : 1); ++c) ga[c].fetch(a.alm_in[c], (base + from) * 2, nalm * 2, tid);
+        };
+        auto put = [&](int to) {
+            gs.put(st[to], tid);
+#pragma unroll
+            for (int c = 0; c < (POL ? 3 : 1); ++c) ga[c].put(al[c][to], tid);
+        };
+        fetch(li);
+        put(0);
+        __syncthreads();
+        for (int ch = 0; li < nl; ++ch) {
+            const int end = min(li + LCHUNK, nl), c0 = li;
+            fetch(c0 + LCHUNK);
+            auto at = [&](int i, Step &s, SynAlm<POL> &x) {
+                s = reinterpret_cast<const Step *>(st[ch & 1])[i];
+                x.t[0] = al[0][ch & 1][2 * i];
+                x.t[1] = al[0][ch & 1][2 * i + 1];
+                if constexpr (POL) {
+                    x.e[0] = al[1][ch & 1][2 * i];
+                    x.e[1] = al[1][ch & 1][2 * i + 1];
+                    x.b[0] = al[2][ch & 1][2 * i];
+                    x.b[1] = al[2][ch & 1][2 * i + 1];
                 }
+            };
+            for (; li + LB <= end; li += LB) {
+                Step s[LB];
+                SynAlm<POL> x[LB];
+#pragma unroll
+                for (int j = 0; j < LB; ++j) at(li - c0 + j, s[j], x[j]);
+                syn_block<POL, true, LB>(ps[0], f[0], s, x);
+            }
+            for (; li < end; ++li) {                                  // only at lmax: a chunk holds whole blocks
+                Step s;
+                SynAlm<POL> x;
+                at(li - c0, s, x);
+                syn_one<POL>(ps[0], f[0], s, x, li & 1);
+            }
+            put((ch + 1) & 1);
+            __syncthreads();
+        }
+    } else     if (li + LB <= nl) {
+        Step s[LB];
+        SynAlm<POL> al[LB];
+#pragma unroll
+        for (int j = 0; j < LB; ++j) {
+            s[j] = load_step(steps_of(a, base + li + j));
+            al[j].load(a, base + li + j);
+        }
+        for (; li + LB <= nl; li += LB) {
+            // the next block's steps and a_lm, in flight during this one (the last block's: again its own)
+            const int64_t next = base + (li + 2 * LB <= nl ? li + LB : li);
+            Step sn[LB];
+            SynAlm<POL> an[LB];
+#pragma unroll
+            for (int j = 0; j < LB; ++j) {
+                sn[j] = load_step(steps_of(a, next + j));
+                an[j].load(a, next + j);
+            }
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                if (k == 0) syn_block<POL, true, LB>(ps[k], f[k], s, al);
+                else syn_block<POL, false, LB>(ps[k], f[k], s, al);
+            }
+#pragma unroll
+            for (int j = 0; j < LB; ++j) {
+                s[j] = sn[j];
+                al[j] = an[j];
             }
         }
-        wave_sync();
+    }
+    for (; li < nl; ++li) {
+        const Step s = load_step(steps_of(a, base + li));
+        SynAlm<POL> al;
+        al.load(a, base + li);
+#pragma unroll
+        for (int k = 0; k < K; ++k) syn_one<POL>(ps[k], f[k], s, al, li & 1);
     }
 #pragma unroll
-    for (int k = 0; k < SYN_PAIRS; ++k) {
-        const int pi = tid + k * SYN_THREADS;
-        if (k >= kcount || pi >= npairs) continue;
+    for (int k = 0; k < K; ++k) {
+        const int pi = tid + k * NT;
+        if (pi >= npairs) continue;
         const int rn = pi, rs = a.nrings - 1 - pi;
-#pragma unroll
-        for (int f = 0; f < 3; ++f) {
-            if (f >= a.nfields) break;
-            const double2 s0 = ps[k].acc[f][0], s1 = ps[k].acc[f][1];
-            double2 *G = a.F + ((size_t)f * (a.mmax + 1) + m) * a.nrings;
-            G[rn] = make_double2(s0.x + s1.x, s0.y + s1.y);
-            if (rs != rn) G[rs] = make_double2(s0.x - s1.x, s0.y - s1.y);
+        const SynSums &x = f[k];
+        double2 *G = a.F + (size_t)m * a.nrings;
+        G[rn] = make_double2(x.Te.x + x.To.x, x.Te.y + x.To.y);
+        if (rs != rn) G[rs] = make_double2(x.Te.x - x.To.x, x.Te.y - x.To.y);
+        if (POL) {
+            // Q = (P + M) / 2, U = (P - M) / 2i, with P, M = minus the sums
+            const size_t fs = (size_t)(a.mmax + 1) * a.nrings;
+            G += fs;
+            G[rn] = make_double2(-0.5 * (x.Pn.x + x.Mn.x), -0.5 * (x.Pn.y + x.Mn.y));
+            if (rs != rn) G[rs] = make_double2(-0.5 * (x.Ps.x + x.Ms.x), -0.5 * (x.Ps.y + x.Ms.y));
+            G += fs;
+            G[rn] = make_double2(-0.5 * (x.Pn.y - x.Mn.y), 0.5 * (x.Pn.x - x.Mn.x));
+            if (rs != rn) G[rs] = make_double2(-0.5 * (x.Ps.y - x.Ms.y), 0.5 * (x.Ps.x - x.Ms.x));
         }
     }
 }
@@ -1064,16 +1185,21 @@ hipError_t launch_rings(const ShtArgs &a, hipStream_t s) {
 
 hipError_t launch_ring_fourier(const ShtArgs &a, hipStream_t s) { return launch_rings<false>(a, s); }
 
+template <bool POL>
+static void launch_alm2ring(const ShtArgs &a, hipStream_t s) {
+    const dim3 g(a.mmax + 1);
+    if (a.nside > 512) hipLaunchKernelGGL((alm2ring_kernel<POL, 4, 8, 2>), g, dim3(512), 0, s, a);
+    else if (a.nside > 256) hipLaunchKernelGGL((alm2ring_kernel<POL, 4, 4, 2>), g, dim3(256), 0, s, a);
+    else if (a.nside > 128) hipLaunchKernelGGL((alm2ring_kernel<POL, 2, 4, 2>), g, dim3(256), 0, s, a);
+    else if (a.nside > 64) hipLaunchKernelGGL((alm2ring_kernel<POL, 1, 4, 4>), g, dim3(256), 0, s, a);
+    else if (a.nside > 32) hipLaunchKernelGGL((alm2ring_kernel<POL, 1, 2, 4>), g, dim3(128), 0, s, a);
+    else hipLaunchKernelGGL((alm2ring_kernel<POL, 1, 1, 4>), g, dim3(64), 0, s, a);
+}
+
 hipError_t launch_alm2map(const ShtArgs &a, hipStream_t s) {
-    const size_t lds = (size_t)(SYN_THREADS / 64) * LCHUNK * (sizeof(Coef) + NCOMP * sizeof(double));
-    const void *k = a.nfields == 3 ? (const void *)alm2ring_kernel<true> : (const void *)alm2ring_kernel<false>;
-    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    if (a.nfields == 3)
-        hipLaunchKernelGGL(alm2ring_kernel<true>, dim3(a.mmax + 1), dim3(SYN_THREADS), lds, s, a);
-    else
-        hipLaunchKernelGGL(alm2ring_kernel<false>, dim3(a.mmax + 1), dim3(SYN_THREADS), lds, s, a);
-    e = hipGetLastError();
+    if (a.nfields == 3) launch_alm2ring<true>(a, s);
+    else launch_alm2ring<false>(a, s);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_rings<true>(a, s);
 }
@@ -1091,12 +1217,15 @@ hipError_t launch_steps(const ShtArgs &a, hipStream_t s) {
 
 // K and NW cover 2 nside pairs with one workgroup: four pairs a lane on large maps
 // (the cross-lane sums are shared by four pairs), one on small ones, where the
-// workgroups are few and the chain of l is the time.
-template <bool POL, int K, int NW>
+// workgroups are few and the chain of l is the time (nside 128, lmax 383: 70 us,
+// 178 with eight waves and four pairs a lane for any map; eight l a block there,
+// 70 against 76 with four).
+template <bool POL, int K, int NW, int LB>
 static hipError_t launch_alm_t(ShtArgs a, hipStream_t s) {
-    const size_t lds = alm_lds<POL, NW>() + (POL ? 2 * LCHUNK * sizeof(WxStep) : 0);
+    static_assert(sizeof(WxStep) == sizeof(Step), "either kind of staged steps");
+    const size_t lds = alm_lds<POL, NW, LB>() + 2 * LCHUNK * sizeof(Step);
     if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute((const void *)alm_kernel<POL, K, NW>,
+        const hipError_t e = hipFuncSetAttribute((const void *)alm_kernel<POL, K, NW, LB>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
@@ -1105,7 +1234,7 @@ static hipError_t launch_alm_t(ShtArgs a, hipStream_t s) {
         a.wx_parts = (2 * a.nside + 64 * NW - 1) / (64 * NW);
     }
     const int blocks = a.wx_m * a.wx_parts + a.mmax + 1 - a.wx_m;
-    hipLaunchKernelGGL((alm_kernel<POL, K, NW>), dim3(blocks), dim3(64 * NW), lds, s, a);
+    hipLaunchKernelGGL((alm_kernel<POL, K, NW, LB>), dim3(blocks), dim3(64 * NW), lds, s, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.wx_parts < 2) return e;
     const int64_t count = (int64_t)a.wx_m * (2 * a.lmax + 3 - a.wx_m) / 2;      // a_lm of m < wx_m
@@ -1115,12 +1244,12 @@ static hipError_t launch_alm_t(ShtArgs a, hipStream_t s) {
 
 template <bool POL>
 static hipError_t launch_alm_p(const ShtArgs &a, hipStream_t s) {
-    if (a.nside > 512) return launch_alm_t<POL, 4, 8>(a, s);
-    if (a.nside > 256) return launch_alm_t<POL, 4, 4>(a, s);
-    if (a.nside > 128) return launch_alm_t<POL, 2, 4>(a, s);
-    if (a.nside > 64) return launch_alm_t<POL, 1, 4>(a, s);
-    if (a.nside > 32) return launch_alm_t<POL, 1, 2>(a, s);
-    return launch_alm_t<POL, 1, 1>(a, s);
+    if (a.nside > 512) return launch_alm_t<POL, 4, 8, 4>(a, s);
+    if (a.nside > 256) return launch_alm_t<POL, 4, 4, 4>(a, s);
+    if (a.nside > 128) return launch_alm_t<POL, 2, 4, 4>(a, s);
+    if (a.nside > 64) return launch_alm_t<POL, 1, 4, 8>(a, s);
+    if (a.nside > 32) return launch_alm_t<POL, 1, 2, 8>(a, s);
+    return launch_alm_t<POL, 1, 1, 8>(a, s);
 }
 
 hipError_t launch_alm(const ShtArgs &a, hipStream_t s) {

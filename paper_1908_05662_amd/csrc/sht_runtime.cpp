@@ -163,7 +163,10 @@ pisco_status pisco_alm2map(pisco_ctx *ctx, int64_t nside, int32_t lmax, const do
     const Layout L = layout(workspace, nside, lmax, pol);
     const double *alm[3] = {alm_T, alm_E, alm_B};
     double *maps[3] = {T, Q, U};
-    return launched(ctx, synthesise(base_args(nside, lmax, pol, L), alm, maps, static_cast<hipStream_t>(stream)));
+    const pisco::ShtArgs a = base_args(nside, lmax, pol, L);
+    const hipStream_t st = static_cast<hipStream_t>(stream);
+    const hipError_t e = pisco::launch_steps(a, st);
+    return launched(ctx, e == hipSuccess ? synthesise(a, alm, maps, st) : e);
 }
 
 pisco_status pisco_alm2cl(pisco_ctx *ctx, int32_t lmax, const double *alm_x, const double *alm_y, double *cl,
