@@ -13,9 +13,8 @@ constexpr int SHT_STEP_BYTES = 48;
 
 struct ShtArgs {
     int nside, lmax, mmax, nfields;        // nfields: 1 (T) or 3 (T, Q, U)
-    int nrings;                            // 4 nside - 1
     const double *map[3];                  // RING order, 12 nside^2 each
-    double2 *F;                            // [nfields][mmax + 1][nrings]: weighted ring Fourier sums
+    double2 *F;                            // [nfields signals][mmax + 1][2 nside ring pairs][P, M]: ring Fourier sums
     double *alm[3];                        // complex interleaved, m-major: T, E, B
     int add;                               // analysis: add to alm instead of replacing it
     int wx_m, wx_parts;                    // analysis: m < wx_m in wx_parts workgroups each (filled in by launch_alm)
@@ -23,6 +22,7 @@ struct ShtArgs {
     double *partial;                       // analysis: [part][alm size][6] sums of the first m
     const double *alm_in[3];               // synthesis input (complex interleaved)
     double *map_out[3];                    // synthesis output (RING order)
+    int residual;                          // synthesis: map less the synthesised map
 };
 
 struct ClArgs {
@@ -35,7 +35,6 @@ hipError_t launch_steps(const ShtArgs &a, hipStream_t s);            // before a
 hipError_t launch_ring_fourier(const ShtArgs &a, hipStream_t s);
 hipError_t launch_alm(const ShtArgs &a, hipStream_t s);
 hipError_t launch_alm2map(const ShtArgs &a, hipStream_t s);          // alm_in -> F (as G) -> map_out
-hipError_t launch_axpy(double *y, const double *x, double alpha, int64_t n, bool reverse, hipStream_t s);
 hipError_t launch_alm2cl(const ClArgs &a, hipStream_t s);
 
 }  // namespace pisco

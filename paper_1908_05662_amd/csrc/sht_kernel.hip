@@ -67,105 +67,433 @@ __device__ inline RingGeom sht_ring(int N, int r) {
     return g;
 }
 
-// Rings [r0, r1) and [r2, r3): one launch per ring-length class, so that the
-// LDS each workgroup reserves matches the longest ring of its class.
-struct RingRange {
-    int r0, r1, r2, r3;
-};
+// ----------------------------------------------------------------------
+// Ring transforms.  A workgroup takes a north ring and its mirror (same length n =
+// 4 k and first longitude) and transforms up to three complex signals:
+// T_N + i T_S, Q_N + i U_N and Q_S + i U_S.  The sums the other kernels want of a
+// signal z are P_m = sum_j z_j e^{-i m phi_j} and M_m = sum_j conj(z_j) e^{-i m phi_j},
+// with Z the signal's DFT P_m = e^{-i m phi_0} Z[m], M_m = e^{-i m phi_0} conj Z[-m]
+// (indices mod n): for spin signals these are the sums of Q + iU and Q - iU, for
+// T of T_N + i T_S and T_N - i T_S.  Stored [signal][m][pair][P, M].
+//
+// A power-of-two n (the belt, a few polar rings) is one FFT in LDS: radix-4
+// Stockham passes in place (a pass reads everything into registers, then writes),
+// twiddles from a quarter-wave table.  Any other k splits n = 4 k by one radix-4
+// step into four transforms of length k, each a chirp convolution (Bluestein 1970)
+// of power-of-two length >= 2 k - 1 by the same FFT; the chirp's spectrum stays in
+// registers, and the chirps and the radix-4 step's twiddles are one exponential
+// e^{-i pi (4 j^2 + 2 a j) / n} of an exact integer.  (A DFT of the odd factor of n
+// summed directly took O(n) operations a point: most of 3.4 ms at nside 1024, one
+// LDS read per multiply-add, and the passes called sincospi for every butterfly.)
+// ----------------------------------------------------------------------
+// Pair of workgroup b: the chirp rings first (the longest), then the belt; four
+// consecutive pairs on one die (workgroups are dealt to the eight in turn), so
+// that the 32-byte results of neighbouring pairs meet in one L2.
+__device__ inline int pair_of_block(int N) {
+    int b = blockIdx.x;
+    if (N >= 16) b = ((b >> 5) << 5) + ((b & 7) << 2) + ((b >> 3) & 3);
+    return b < N ? N - 1 - b : b;
+}
 
-__global__ void __launch_bounds__(256) ring_fourier_kernel(ShtArgs a, RingRange rr) {
-    extern __shared__ double2 sh_ring[];
-    const int b = blockIdx.x;
-    const int r = b < rr.r1 - rr.r0 ? rr.r0 + b : rr.r2 + (b - (rr.r1 - rr.r0));
-    const RingGeom g = sht_ring(a.nside, r);
-    const int n = g.n;
-    const int P = n & -n;                // power-of-two factor
-    const int q = n / P;                 // odd factor
-    double2 *bufA = sh_ring;
-    double2 *bufB = sh_ring + n;
-    double2 *tab = sh_ring + 2 * n;          // e^{-2 pi i t / q}, t < q (q <= n / 4 when q > 1)
-    double *xs = reinterpret_cast<double *>(bufB);
-    const double w = 4.0 * M_PI / (12.0 * (double)a.nside * (double)a.nside);
-    if (q > 1) {
-        for (int t = threadIdx.x; t < q; t += blockDim.x) {
-            double st, ct;
-            sincospi(2.0 * (double)t / (double)q, &st, &ct);
-            tab[t] = make_double2(ct, -st);
+// e^{-i pi t / n}
+__device__ inline double2 cis(int t, int n) {
+    double sn, cs;
+    sincospi((double)t / (double)n, &sn, &cs);
+    return make_double2(cs, -sn);
+}
+
+__device__ inline double2 cmul(double2 a, double2 b) {
+    return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
+}
+
+// (-i)^p z
+__device__ inline double2 turn(double2 z, int p) {
+    p &= 3;
+    const double x = p & 1 ? z.y : z.x, y = p & 1 ? -z.x : z.y;
+    return p & 2 ? make_double2(-x, -y) : make_double2(x, y);
+}
+
+// Orders this wave's LDS writes before its later LDS reads (lanes exchange
+// values inside one wave; no other wave touches the region).
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// FFT of 2^L values in LDS by a group of NT threads (at most 4 B NT values), thread
+// tid of the group; groups of a workgroup run side by side on their own data, in
+// step.  A group of one wave needs no barrier.
+template <int NT, int B>
+struct LdsFft {
+    double2 *x;                          // data
+    const double2 *tab;                  // e^{-2 pi i t / M}, t < M / 4
+    int L, M, tid;
+    static __device__ inline void sync() {
+        if constexpr (NT == 64) wave_sync();
+        else __syncthreads();
+    }
+    __device__ inline void init(double2 *data, double2 *table, int log2m, int t) {
+        x = data;
+        tab = table;
+        L = log2m;
+        M = 1 << log2m;
+        tid = t;
+        for (int i = threadIdx.x; 4 * i < M; i += blockDim.x) table[i] = cis(2 * i, M);
+        __syncthreads();
+    }
+    // x <- DFT(x), natural order; the group's writes to x need no barrier of their own, the result none
+    __device__ inline void run() const {
+        sync();
+        int ls = 0;                                                   // log2 of the finished length
+        if (L & 1) {
+            double2 u[2 * B], v[2 * B];
+#pragma unroll
+            for (int i = 0; i < 2 * B; ++i) {
+                const int j = tid + i * NT;
+                if (2 * j < M) {
+                    u[i] = x[j];
+                    v[i] = x[j + M / 2];
+                }
+            }
+            sync();
+#pragma unroll
+            for (int i = 0; i < 2 * B; ++i) {
+                const int j = tid + i * NT;
+                if (2 * j < M) {
+                    x[2 * j] = make_double2(u[i].x + v[i].x, u[i].y + v[i].y);
+                    x[2 * j + 1] = make_double2(u[i].x - v[i].x, u[i].y - v[i].y);
+                }
+            }
+            sync();
+            ls = 1;
+        }
+        const int q = M / 4;
+        for (; ls < L; ls += 2) {
+            double2 o[B][4];
+#pragma unroll
+            for (int i = 0; i < B; ++i) {
+                const int j = tid + i * NT;
+                if (j < q) {
+                    const int t = (j & ((1 << ls) - 1)) << (L - 2 - ls);
+                    const int t2 = 2 * t, t3 = 3 * t;
+                    const double2 w1 = tab[t], w2 = turn(tab[t2 & (q - 1)], t2 >> (L - 2));
+                    const double2 w3 = turn(tab[t3 & (q - 1)], t3 >> (L - 2));
+                    const double2 x0 = x[j], x1 = cmul(x[j + q], w1), x2 = cmul(x[j + 2 * q], w2), x3 = cmul(x[j + 3 * q], w3);
+                    const double2 a = make_double2(x0.x + x2.x, x0.y + x2.y), b = make_double2(x0.x - x2.x, x0.y - x2.y);
+                    const double2 c = make_double2(x1.x + x3.x, x1.y + x3.y);
+                    const double2 d = make_double2(x1.y - x3.y, x3.x - x1.x);       // -i (x1 - x3)
+                    o[i][0] = make_double2(a.x + c.x, a.y + c.y);
+                    o[i][1] = make_double2(b.x + d.x, b.y + d.y);
+                    o[i][2] = make_double2(a.x - c.x, a.y - c.y);
+                    o[i][3] = make_double2(b.x - d.x, b.y - d.y);
+                }
+            }
+            sync();
+#pragma unroll
+            for (int i = 0; i < B; ++i) {
+                const int j = tid + i * NT;
+                if (j < q) {
+                    const int k = j & ((1 << ls) - 1), at = ((j - k) << 2) + k;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) x[at + (r << ls)] = o[i][r];
+                }
+            }
+            sync();
         }
     }
-    for (int f = 0; f < a.nfields; ++f) {
-        const double *x = a.map[f] + g.first;
-        for (int j = threadIdx.x; j < n; j += blockDim.x) xs[j] = x[j];
-        __syncthreads();
-        // P DFTs of length q over the stride-P subsequences x[P j2 + j1]; the input is
-        // real, so Y[q - k2] = conj Y[k2] and only k2 <= (q - 1) / 2 is summed
-        const int h = (q + 1) / 2;
-        for (int it = threadIdx.x; it < P * h; it += blockDim.x) {
-            const int j1 = it / h, k2 = it - j1 * h;
-            double re = 0.0, im = 0.0;
-            if (q == 1) {
-                re = xs[j1];
-            } else {
-                // twiddles e^{-2 pi i j2 k2 / q} from the ring's table (index j2 k2 mod q),
-                // four interleaved accumulators (j2 = c mod 4)
-                double ar[4] = {0, 0, 0, 0}, ai[4] = {0, 0, 0, 0};
-                int idx = 0;
-                int j2 = 0;
-                for (; j2 + 3 < q; j2 += 4) {
+};
+
+// The chirp transform of length k (not a power of two, k <= B NT), element
+// j = tid + i NT in u[i].
+template <int NT, int B>
+struct Chirp {
+    LdsFft<NT, B> f;
+    int k, n;
+    double2 spec[2 * B];                 // DFT of e^{i pi j^2 / k}, over M
+    __device__ inline double2 phase(int j, int a) const {             // e^{-i pi (4 j^2 + 2 a j) / n}
+        return cis((4 * j * j + 2 * a * j) % (2 * n), n);              // j <= 1024
+    }
+    __device__ inline void init(double2 *data, double2 *table, int ring_k, int tid) {
+        k = ring_k;
+        n = 4 * k;
+        f.init(data, table, 32 - __clz(2 * k - 2), tid);              // 2^L >= 2 k - 1
+        const double inv = 1.0 / (double)f.M;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const double2 tw = tab[idx];
-                        const double xv = xs[P * (j2 + c) + j1];
-                        ar[c] = fma(xv, tw.x, ar[c]);
-                        ai[c] = fma(xv, tw.y, ai[c]);
-                        idx += k2;
-                        idx = idx >= q ? idx - q : idx;
-                    }
-                }
-                for (; j2 < q; ++j2) {
-                    const double2 tw = tab[idx];
-                    const double xv = xs[P * j2 + j1];
-                    ar[0] = fma(xv, tw.x, ar[0]);
-                    ai[0] = fma(xv, tw.y, ai[0]);
-                    idx += k2;
-                    idx = idx >= q ? idx - q : idx;
-                }
-                re = (ar[0] + ar[1]) + (ar[2] + ar[3]);
-                im = (ai[0] + ai[1]) + (ai[2] + ai[3]);
+        for (int i = 0; i < 2 * B; ++i) {
+            const int j = tid + i * NT;
+            if (j < f.M) {
+                const int d = j < k ? j : f.M - j;
+                const double2 c = d < k ? phase(d, 0) : make_double2(0.0, 0.0);
+                f.x[j] = make_double2(inv * c.x, -inv * c.y);
             }
-            bufA[j1 * q + k2] = make_double2(re, im);
-            if (k2 > 0) bufA[j1 * q + q - k2] = make_double2(re, -im);
         }
-        __syncthreads();
-        // radix-2 passes: sequences c and c + Ps/2 (offsets of stride Ps) merge into
-        // sequence c of stride Ps/2 and twice the length
-        double2 *src = bufA, *dst = bufB;
-        int L = q;
-        for (int Ps = P; Ps > 1; Ps >>= 1) {
-            const int half = Ps >> 1;
-            for (int it = threadIdx.x; it < half * L; it += blockDim.x) {
-                const int c = it / L, k = it - c * L;
-                const double2 E = src[c * L + k];
-                const double2 O = src[(c + half) * L + k];
-                double sn, cs;
-                sincospi((double)k / (double)L, &sn, &cs);          // e^{-i pi k / L}
-                const double tr = fma(O.x, cs, O.y * sn);
-                const double ti = fma(O.y, cs, -O.x * sn);
-                dst[c * 2 * L + k] = make_double2(E.x + tr, E.y + ti);
-                dst[c * 2 * L + k + L] = make_double2(E.x - tr, E.y - ti);
+        f.run();
+#pragma unroll
+        for (int i = 0; i < 2 * B; ++i) {
+            const int j = tid + i * NT;
+            if (j < f.M) spec[i] = f.x[j];
+        }
+    }
+    // u: inputs times their phases (0 past k); returns the sums before the output phases
+    __device__ inline void run(double2 *u, int tid) const {
+        f.sync();
+#pragma unroll
+        for (int i = 0; i < 2 * B; ++i) {
+            const int j = tid + i * NT;
+            if (j < f.M) f.x[j] = i < B && j < k ? u[i < B ? i : 0] : make_double2(0.0, 0.0);
+        }
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {
+            f.run();
+            if (half) break;
+#pragma unroll
+            for (int i = 0; i < 2 * B; ++i) {
+                const int j = tid + i * NT;
+                if (j < f.M) {
+                    const double2 p = cmul(f.x[j], spec[i]);
+                    f.x[j] = make_double2(p.x, -p.y);                 // the inverse DFT as conj DFT conj
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            const int j = tid + i * NT;
+            u[i] = j < k ? make_double2(f.x[j].x, -f.x[j].y) : make_double2(0.0, 0.0);
+        }
+    }
+};
+
+// One ring pair: where a signal's samples are (null: zero).
+struct RingPair {
+    int n, k;
+    bool pow2, equator;
+    bool shifted;                        // first longitude: pi / n or 0
+    int64_t north, south;                // first pixels
+    __device__ inline RingPair(int N, int pair) {
+        const RingGeom g = sht_ring(N, pair), m = sht_ring(N, 4 * N - 2 - pair);
+        n = g.n;
+        k = n / 4;
+        pow2 = (k & (k - 1)) == 0;
+        equator = pair == 2 * N - 1;
+        shifted = g.phi0_over_pi > 0.0;
+        north = g.first;
+        south = m.first;
+    }
+    // real and imaginary parts of signal s in maps x[3]
+    template <class T>
+    __device__ inline void parts(T *const x[3], int s, T *&re, T *&im) const {
+        re = s == 0 ? x[0] + north : x[1] + (s == 1 ? north : south);
+        im = s == 0 ? (equator ? nullptr : x[0] + south) : x[2] + (s == 1 ? north : south);
+    }
+    __device__ inline int signals(int nfields) const { return nfields == 1 ? 1 : equator ? 2 : 3; }
+    // e^{-i m phi_0} z, times w
+    __device__ inline double2 phased(double2 z, int m, double w) const {
+        const double2 p = cmul(z, shifted ? cis(m, n) : make_double2(1.0, 0.0));
+        return make_double2(w * p.x, w * p.y);
+    }
+};
+
+// G groups of NT threads.  Large maps: one group, a transform at a time, two
+// workgroups a compute unit (nside 1024).  Small maps: a workgroup's transforms (three
+// signals, or the twelve quarter-length ones of a chirp ring) side by side, since
+// the number of rings leaves the chip idle and the chain of passes is the time.
+// LDS in units of nside values: see ring_lds.
+template <int G>
+constexpr int ring_lds(bool syn) {
+    const int chirp = 2 * G + (syn ? (G >= 12 ? 12 : 4) : 0), belt = 4 * (G >= 12 ? 3 : G);
+    return 1 + (chirp > belt ? chirp : belt);
+}
+
+template <int NT, int B, int G>
+__global__ void __launch_bounds__(NT * G) ring_fourier_kernel(ShtArgs a) {
+    extern __shared__ double2 sh_ring[];
+    const int N = a.nside, npairs = 2 * N, grp = threadIdx.x / NT, tid = threadIdx.x % NT;
+    const int pair = pair_of_block(N);
+    const RingPair R(N, pair);
+    const int n = R.n, k = R.k;
+    const double w = 4.0 * M_PI / (12.0 * (double)N * (double)N);
+    const int ns = R.signals(a.nfields);
+    double2 *table = sh_ring, *data = sh_ring + N;
+    auto out = [&](int s, int m) { return a.F + (((size_t)s * (a.mmax + 1) + m) * npairs + pair) * 2; };
+    if (R.pow2) {
+        LdsFft<NT, B> f;
+        f.init(data + grp * 4 * N, table, 31 - __clz(n), tid);        // (groups past the signals: no data)
+#pragma unroll 1
+        for (int s0 = 0; s0 < ns; s0 += G) {
+            const int s = s0 + grp;
+            const bool ok = s < ns;
+            const double *re, *im;
+            if (ok) {
+                R.parts(a.map, s, re, im);
+                for (int j = tid; j < n; j += NT) f.x[j] = make_double2(re[j], im ? im[j] : 0.0);
+            }
+            if (ok || NT > 64) f.run();                               // idle groups keep the barriers
+            if (ok) {
+                for (int m = tid; m <= a.mmax; m += NT) {
+                    const int i = m & (n - 1);
+                    const double2 p = f.x[i], q = f.x[(n - i) & (n - 1)];
+                    double2 *o = out(s, m);
+                    o[0] = R.phased(p, m, w);
+                    o[1] = R.phased(make_double2(q.x, -q.y), m, w);
+                }
             }
             __syncthreads();
-            double2 *t = src;
-            src = dst;
-            dst = t;
-            L <<= 1;
         }
-        double2 *out = a.F + (size_t)f * (a.mmax + 1) * a.nrings + r;
-        for (int m = threadIdx.x; m <= a.mmax; m += blockDim.x) {
-            const double2 X = src[m % n];
-            double sn, cs;
-            sincospi((double)m * g.phi0_over_pi, &sn, &cs);        // e^{-i m phi0}
-            out[(size_t)m * a.nrings] = make_double2(w * fma(X.x, cs, X.y * sn), w * fma(X.y, cs, -X.x * sn));
+        return;
+    }
+    Chirp<NT, B> c;
+    c.init(data + grp * 2 * N, table, k, tid);
+    double2 post[B];
+#pragma unroll
+    for (int i = 0; i < B; ++i) post[i] = c.phase(min(tid + i * NT, k), 0);
+#pragma unroll 1
+    for (int q0 = 0; q0 < 4 * ns; q0 += G) {
+        const int t = (q0 + grp) & 3, s = (q0 + grp) >> 2;            // Z[4 j + t] of signal s
+        const bool ok = s < ns;
+        const double *re = nullptr, *im = nullptr;
+        if (ok) R.parts(a.map, s, re, im);
+        double2 u[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            const int j = tid + i * NT;
+            double2 z = make_double2(0.0, 0.0);
+            if (ok && j < k) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const double2 v = turn(make_double2(re[j + b * k], im ? im[j + b * k] : 0.0), b * t);
+                    z.x += v.x;
+                    z.y += v.y;
+                }
+                z = cmul(z, c.phase(j, t));
+            }
+            u[i] = z;
+        }
+        c.run(u, tid);
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            const int j = tid + i * NT;
+            if (!ok || j >= k) continue;
+            // phi_0 = pi / n: e^{-i m phi_0} changes sign from m to m + n
+            const int at = 4 * j + t;
+            double2 z = R.phased(cmul(u[i], post[i]), at, w);
+            double2 y = at ? make_double2(-z.x, z.y) : make_double2(z.x, -z.y);
+            for (int m = at; m <= a.mmax; m += n) {
+                out(s, m)[0] = z;
+                z = make_double2(-z.x, -z.y);
+            }
+            for (int m = at ? n - at : 0; m <= a.mmax; m += n) {
+                out(s, m)[1] = y;
+                y = make_double2(-y.x, -y.y);
+            }
+        }
+    }
+}
+
+// The inverse: z_j = sum_m P_m e^{i m phi_j} + sum_{m > 0} conj(M_m) e^{-i m phi_j}
+// (at m = 0 half of each), as conj DFT conj of the sums folded onto the ring, into
+// the maps, or the reference maps less them.
+template <int NT, int B, int G>
+__global__ void __launch_bounds__(NT * G) ring_synth_kernel(ShtArgs a) {
+    extern __shared__ double2 sh_ring[];
+    const int N = a.nside, npairs = 2 * N, grp = threadIdx.x / NT, tid = threadIdx.x % NT;
+    const int pair = pair_of_block(N);
+    const RingPair R(N, pair);
+    const int n = R.n, k = R.k;
+    const int ns = R.signals(a.nfields);
+    double2 *table = sh_ring, *data = sh_ring + N;
+    // conj of the folded sum at index i of the ring
+    auto folded = [&](int s, int i) {
+        const double2 *F = a.F + ((size_t)s * (a.mmax + 1) * npairs + pair) * 2;
+        // e^{i m phi_0} changes sign from m to m + n on the shifted rings: its value at i
+        // (P_m e^{i m phi_0}) serves both sums
+        const double turn_sign = R.shifted ? -1.0 : 1.0;
+        double2 h = make_double2(0.0, 0.0);
+        double w = i ? 1.0 : 0.5;
+#pragma unroll 4
+        for (int m = i; m <= a.mmax; m += n) {                        // conj(P_m)
+            const double2 p = F[(size_t)m * npairs * 2];
+            h.x = fma(w, p.x, h.x);
+            h.y = fma(-w, p.y, h.y);
+            w = m ? w * turn_sign : turn_sign;
+        }
+        w = i ? turn_sign : 0.5;
+#pragma unroll 4
+        for (int m = i ? n - i : 0; m <= a.mmax; m += n) {            // M_m
+            const double2 p = F[(size_t)m * npairs * 2 + 1];
+            h.x = fma(w, p.x, h.x);
+            h.y = fma(w, p.y, h.y);
+            w = m ? w * turn_sign : turn_sign;
+        }
+        h = R.phased(h, i, 1.0);
+        return h;
+    };
+    auto put = [&](int s, int j, double2 z) {                         // z: conj of the signal
+        double *re, *im;
+        R.parts(a.map_out, s, re, im);
+        if (a.residual) {
+            const double *r0, *i0;
+            R.parts(a.map, s, r0, i0);
+            re[j] = r0[j] - z.x;
+            if (im) im[j] = i0[j] + z.y;
+        } else {
+            re[j] = z.x;
+            if (im) im[j] = -z.y;
+        }
+    };
+    if (R.pow2) {
+        LdsFft<NT, B> f;
+        f.init(data + grp * 4 * N, table, 31 - __clz(n), tid);        // (groups past the signals: no data)
+#pragma unroll 1
+        for (int s0 = 0; s0 < ns; s0 += G) {
+            const int s = s0 + grp;
+            const bool ok = s < ns;
+            if (ok)
+                for (int i = tid; i < n; i += NT) f.x[i] = folded(s, i);
+            if (ok || NT > 64) f.run();
+            if (ok)
+                for (int j = tid; j < n; j += NT) put(s, j, f.x[j]);
+            __syncthreads();
+        }
+        return;
+    }
+    constexpr int SPB = G >= 12 ? 3 : 1;                              // signals side by side
+    double2 *sums = data + 2 * N * G;                                 // [SPB][n]
+    Chirp<NT, B> c;
+    c.init(data + grp * 2 * N, table, k, tid);
+    double2 post[B];
+#pragma unroll
+    for (int i = 0; i < B; ++i) post[i] = c.phase(min(tid + i * NT, k), 0);
+#pragma unroll 1
+    for (int s0 = 0; s0 < ns; s0 += SPB) {
+        for (int i = threadIdx.x; i < min(SPB, ns - s0) * n; i += NT * G) sums[i] = folded(s0 + i / n, i % n);
+        __syncthreads();
+#pragma unroll 1
+        for (int q0 = 0; q0 < 4 * SPB; q0 += G) {
+            const int t = (q0 + grp) & 3, s = (q0 + grp) >> 2;        // samples 4 j + t of signal s0 + s
+            const bool ok = s < SPB && s0 + s < ns;
+            double2 u[B];
+#pragma unroll
+            for (int i = 0; i < B; ++i) {
+                const int j = tid + i * NT;
+                double2 z = make_double2(0.0, 0.0);
+                if (ok && j < k) {
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) {
+                        const double2 v = turn(sums[s * n + j + b * k], b * t);
+                        z.x += v.x;
+                        z.y += v.y;
+                    }
+                    z = cmul(z, c.phase(j, t));
+                }
+                u[i] = z;
+            }
+            c.run(u, tid);
+#pragma unroll
+            for (int i = 0; i < B; ++i) {
+                const int j = tid + i * NT;
+                if (ok && j < k) put(s0 + s, 4 * j + t, cmul(u[i], post[i]));
+            }
         }
         __syncthreads();
     }
@@ -358,14 +686,6 @@ __device__ inline double start_norm(int m, int lane) {
     return sqrt(pr / (4.0 * M_PI));
 }
 
-// Orders this wave's LDS writes before its later LDS reads (lanes exchange
-// values inside one wave; no other wave touches the region).
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // An a_lm value into place, or added to it (the refinement steps' corrections).
 __device__ inline void put_alm(const ShtArgs &a, double *dst, double re, double im) {
     if (a.add) {
@@ -380,6 +700,33 @@ __device__ inline void put_alm(const ShtArgs &a, double *dst, double re, double 
 struct PairSums {
     double2 Tp, Tm, Pn, Ps, Mn, Ms;
 };
+
+template <bool POL>
+__device__ inline PairSums load_pair(const ShtArgs &a, int m, int pair, bool ok) {
+    const int npairs = 2 * a.nside;
+    const bool south = ok && pair != npairs - 1;                      // the equator is its own mirror
+    const double2 zero = make_double2(0.0, 0.0);
+    auto at = [&](int s) { return a.F + (((size_t)s * (a.mmax + 1) + m) * npairs + pair) * 2; };
+    PairSums f;
+    const double2 P = ok ? at(0)[0] : zero, M = ok ? at(0)[1] : zero;
+    // T_N = (P + M) / 2, T_S = (P - M) / 2i
+    const double2 n = make_double2(0.5 * (P.x + M.x), 0.5 * (P.y + M.y));
+    const double2 t = south ? make_double2(0.5 * (P.y - M.y), -0.5 * (P.x - M.x)) : zero;
+    f.Tp = make_double2(n.x + t.x, n.y + t.y);
+    f.Tm = make_double2(n.x - t.x, n.y - t.y);
+    f.Pn = f.Mn = f.Ps = f.Ms = zero;
+    if (POL) {
+        if (ok) {
+            f.Pn = at(1)[0];
+            f.Mn = at(1)[1];
+        }
+        if (south) {
+            f.Ps = at(2)[0];
+            f.Ms = at(2)[1];
+        }
+    }
+    return f;
+}
 
 // lambda and f of one l (parity ODD of l - m) against the pair's sums: acc = (T, S+, S-)
 template <bool ODD, bool POL>
@@ -526,21 +873,20 @@ __device__ void alm_wx(const ShtArgs &a, int m, int part, int tid, double *lds) 
     WxStep *steps = reinterpret_cast<WxStep *>(lds + (2 * LCHUNK * NCOMP + NS * 17) * NW);
     const int npairs = 2 * a.nside, pi = part * NT + tid;
     const bool ok = pi < npairs;
-    const int rn = ok ? pi : 0, rs = a.nrings - 1 - rn;
-    double2 fn[3] = {}, fs[3] = {};
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        if (ok) {
-            const double2 *F = a.F + ((size_t)c * (a.mmax + 1) + m) * a.nrings;
-            fn[c] = F[rn];
-            if (rs != rn) fs[c] = F[rs];
-        }
-    }
-    double2 P[3], M[3];                                               // north +- south
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        P[c] = make_double2(fn[c].x + fs[c].x, fn[c].y + fs[c].y);
-        M[c] = make_double2(fn[c].x - fs[c].x, fn[c].y - fs[c].y);
+    const int rn = ok ? pi : 0;
+    const PairSums F = load_pair<true>(a, m, rn, ok);
+    double2 P[3], M[3];                                               // T, Q, U: north +- south
+    {
+        const double2 qn = make_double2(0.5 * (F.Pn.x + F.Mn.x), 0.5 * (F.Pn.y + F.Mn.y));
+        const double2 qs = make_double2(0.5 * (F.Ps.x + F.Ms.x), 0.5 * (F.Ps.y + F.Ms.y));
+        const double2 un = make_double2(0.5 * (F.Pn.y - F.Mn.y), -0.5 * (F.Pn.x - F.Mn.x));
+        const double2 us = make_double2(0.5 * (F.Ps.y - F.Ms.y), -0.5 * (F.Ps.x - F.Ms.x));
+        P[0] = F.Tp;
+        M[0] = F.Tm;
+        P[1] = make_double2(qn.x + qs.x, qn.y + qs.y);
+        M[1] = make_double2(qn.x - qs.x, qn.y - qs.y);
+        P[2] = make_double2(un.x + us.x, un.y + us.y);
+        M[2] = make_double2(un.x - us.x, un.y - us.y);
     }
     const RingGeom g = sht_ring(a.nside, rn);
     PairState p = start_pair(g, m, start_norm(m, lane), ok);
@@ -641,24 +987,7 @@ __global__ void __launch_bounds__(64 * NW, K >= 4 ? 2 : 1) alm_kernel(ShtArgs a)
         const int pi = tid + k * NT;
         const bool ok = pi < npairs;
         const int rn = ok ? pi : 0;
-        const int rs = a.nrings - 1 - rn;                            // mirror ring; rs == rn on the equator
-        double2 fn[3] = {}, fs[3] = {};
-#pragma unroll
-        for (int c = 0; c < (POL ? 3 : 1); ++c) {
-            if (ok) {
-                const double2 *F = a.F + ((size_t)c * (a.mmax + 1) + m) * a.nrings;
-                fn[c] = F[rn];
-                if (rs != rn) fs[c] = F[rs];
-            }
-        }
-        f[k].Tp = make_double2(fn[0].x + fs[0].x, fn[0].y + fs[0].y);
-        f[k].Tm = make_double2(fn[0].x - fs[0].x, fn[0].y - fs[0].y);
-        if (POL) {
-            f[k].Pn = make_double2(fn[1].x - fn[2].y, fn[1].y + fn[2].x);
-            f[k].Mn = make_double2(fn[1].x + fn[2].y, fn[1].y - fn[2].x);
-            f[k].Ps = make_double2(fs[1].x - fs[2].y, fs[1].y + fs[2].x);
-            f[k].Ms = make_double2(fs[1].x + fs[2].y, fs[1].y - fs[2].x);
-        }
+        f[k] = load_pair<POL>(a, m, rn, ok);
         ps[k] = start_pair(sht_ring(N, rn), m, cm, ok);
     }
 
@@ -985,146 +1314,19 @@ __global__ void __launch_bounds__(64 * NW, K >= 4 ? 2 : 1) alm2ring_kernel(ShtAr
     for (int k = 0; k < K; ++k) {
         const int pi = tid + k * NT;
         if (pi >= npairs) continue;
-        const int rn = pi, rs = a.nrings - 1 - pi;
         const SynSums &x = f[k];
-        double2 *G = a.F + (size_t)m * a.nrings;
-        G[rn] = make_double2(x.Te.x + x.To.x, x.Te.y + x.To.y);
-        if (rs != rn) G[rs] = make_double2(x.Te.x - x.To.x, x.Te.y - x.To.y);
+        auto at = [&](int s) { return a.F + (((size_t)s * (a.mmax + 1) + m) * npairs + pi) * 2; };
+        // T_N +- i T_S
+        const double2 n = make_double2(x.Te.x + x.To.x, x.Te.y + x.To.y), t = make_double2(x.Te.x - x.To.x, x.Te.y - x.To.y);
+        at(0)[0] = make_double2(n.x - t.y, n.y + t.x);
+        at(0)[1] = make_double2(n.x + t.y, n.y - t.x);
         if (POL) {
-            // Q = (P + M) / 2, U = (P - M) / 2i, with P, M = minus the sums
-            const size_t fs = (size_t)(a.mmax + 1) * a.nrings;
-            G += fs;
-            G[rn] = make_double2(-0.5 * (x.Pn.x + x.Mn.x), -0.5 * (x.Pn.y + x.Mn.y));
-            if (rs != rn) G[rs] = make_double2(-0.5 * (x.Ps.x + x.Ms.x), -0.5 * (x.Ps.y + x.Ms.y));
-            G += fs;
-            G[rn] = make_double2(-0.5 * (x.Pn.y - x.Mn.y), 0.5 * (x.Pn.x - x.Mn.x));
-            if (rs != rn) G[rs] = make_double2(-0.5 * (x.Ps.y - x.Ms.y), 0.5 * (x.Ps.x - x.Ms.x));
+            at(1)[0] = make_double2(-x.Pn.x, -x.Pn.y);
+            at(1)[1] = make_double2(-x.Mn.x, -x.Mn.y);
+            at(2)[0] = make_double2(-x.Ps.x, -x.Ps.y);
+            at(2)[1] = make_double2(-x.Ms.x, -x.Ms.y);
         }
     }
-}
-
-// x_j = Re sum_{m=0..mmax} c_m G_m e^{i m (phi0 + 2 pi j / n)}, c_0 = 1, c_m = 2:
-// the m sums folded onto k = m mod n give H, and x = Re DFT(conj H) = DFT(conj Hs)
-// with Hs[k] = (H[k] + conj H[n - k]) / 2 Hermitian.  Then the stride-P
-// subsequences of conj Hs pair up: their q-point DFTs obey
-// Y_{P-j1}[k] = e^{2 pi i k / q} conj Y_{j1}[k] (1 <= j1 < P), so only
-// j1 = 0..P/2 are summed.
-__global__ void __launch_bounds__(256) ring_synth_kernel(ShtArgs a, RingRange rr) {
-    extern __shared__ double2 sh_ring[];
-    const int b = blockIdx.x;
-    const int r = b < rr.r1 - rr.r0 ? rr.r0 + b : rr.r2 + (b - (rr.r1 - rr.r0));
-    const RingGeom g = sht_ring(a.nside, r);
-    const int n = g.n;
-    const int P = n & -n;
-    const int q = n / P;
-    double2 *bufA = sh_ring;
-    double2 *bufB = sh_ring + n;
-    double2 *tab = sh_ring + 2 * n;
-    if (q > 1) {
-        for (int t = threadIdx.x; t < q; t += blockDim.x) {
-            double st, ct;
-            sincospi(2.0 * (double)t / (double)q, &st, &ct);
-            tab[t] = make_double2(ct, -st);
-        }
-    }
-    for (int f = 0; f < a.nfields; ++f) {
-        const double2 *G = a.F + (size_t)f * (a.mmax + 1) * a.nrings + r;
-        for (int k = threadIdx.x; k < n; k += blockDim.x) {
-            double hr = 0.0, hi = 0.0;
-            for (int m = k; m <= a.mmax; m += n) {
-                const double2 v = G[(size_t)m * a.nrings];
-                double sn, cs;
-                sincospi((double)m * g.phi0_over_pi, &sn, &cs);       // e^{+i m phi0}
-                const double c = m == 0 ? 1.0 : 2.0;
-                hr = fma(c, fma(v.x, cs, -v.y * sn), hr);
-                hi = fma(c, fma(v.x, sn, v.y * cs), hi);
-            }
-            bufA[k] = make_double2(hr, hi);
-        }
-        __syncthreads();
-        // bufA <- conj Hs
-        for (int k = threadIdx.x; 2 * k <= n; k += blockDim.x) {
-            const int k2 = k == 0 ? 0 : n - k;
-            const double2 u = bufA[k], v = bufA[k2];
-            const double2 hs = make_double2(0.5 * (u.x + v.x), 0.5 * (u.y - v.y));   // (H[k] + conj H[n-k]) / 2
-            bufA[k] = make_double2(hs.x, -hs.y);
-            bufA[k2] = hs;                                                        // conj of Hs[n-k] = conj conj Hs[k]
-        }
-        __syncthreads();
-        double2 *src = bufA, *dst = bufB;
-        if (q > 1) {
-            // complex input: all k2 < q for j1 = 0..P/2 (P >= 4 on every ring with q > 1);
-            // four interleaved accumulators (j2 = c mod 4)
-            const int jhalf = P >= 4 ? P / 2 : P - 1;
-            for (int it = threadIdx.x; it < (jhalf + 1) * q; it += blockDim.x) {
-                const int j1 = it / q, k2 = it - j1 * q;
-                double ar[4] = {0, 0, 0, 0}, ai[4] = {0, 0, 0, 0};
-                int idx = 0;
-                int j2 = 0;
-                for (; j2 + 3 < q; j2 += 4) {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const double2 tw = tab[idx];
-                        const double2 xv = bufA[P * (j2 + c) + j1];
-                        ar[c] = fma(xv.x, tw.x, fma(-xv.y, tw.y, ar[c]));
-                        ai[c] = fma(xv.x, tw.y, fma(xv.y, tw.x, ai[c]));
-                        idx += k2;
-                        idx = idx >= q ? idx - q : idx;
-                    }
-                }
-                for (; j2 < q; ++j2) {
-                    const double2 tw = tab[idx];
-                    const double2 xv = bufA[P * j2 + j1];
-                    ar[0] = fma(xv.x, tw.x, fma(-xv.y, tw.y, ar[0]));
-                    ai[0] = fma(xv.x, tw.y, fma(xv.y, tw.x, ai[0]));
-                    idx += k2;
-                    idx = idx >= q ? idx - q : idx;
-                }
-                bufB[j1 * q + k2] = make_double2((ar[0] + ar[1]) + (ar[2] + ar[3]), (ai[0] + ai[1]) + (ai[2] + ai[3]));
-            }
-            __syncthreads();
-            // the rest by the pairing: Y_{j1}[k] = e^{2 pi i k / q} conj Y_{P - j1}[k]
-            for (int it = threadIdx.x; it < (P - 1 - jhalf) * q; it += blockDim.x) {
-                const int j1 = jhalf + 1 + it / q, k2 = it % q;
-                const double2 y = bufB[(P - j1) * q + k2];
-                const double2 t = tab[k2];                                          // e^{-2 pi i k / q}
-                // conj(t) * conj(y) = conj(t * y)
-                bufB[j1 * q + k2] = make_double2(t.x * y.x - t.y * y.y, -(t.x * y.y + t.y * y.x));
-            }
-            __syncthreads();
-            src = bufB;
-            dst = bufA;
-        }
-        int L = q;
-        for (int Ps = P; Ps > 1; Ps >>= 1) {
-            const int half = Ps >> 1;
-            for (int it = threadIdx.x; it < half * L; it += blockDim.x) {
-                const int c = it / L, k = it - c * L;
-                const double2 E = src[c * L + k];
-                const double2 O = src[(c + half) * L + k];
-                double sn, cs;
-                sincospi((double)k / (double)L, &sn, &cs);
-                const double tr = fma(O.x, cs, O.y * sn);
-                const double ti = fma(O.y, cs, -O.x * sn);
-                dst[c * 2 * L + k] = make_double2(E.x + tr, E.y + ti);
-                dst[c * 2 * L + k + L] = make_double2(E.x - tr, E.y - ti);
-            }
-            __syncthreads();
-            double2 *t = src;
-            src = dst;
-            dst = t;
-            L <<= 1;
-        }
-        double *out = a.map_out[f] + g.first;
-        for (int j = threadIdx.x; j < n; j += blockDim.x) out[j] = src[j].x;
-        __syncthreads();
-    }
-}
-
-// y <- x + alpha y (reverse) or y <- y + alpha x
-__global__ void __launch_bounds__(256) axpy_kernel(double *y, const double *x, double alpha, int64_t n, bool reverse) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] = reverse ? fma(alpha, y[i], x[i]) : fma(alpha, x[i], y[i]);
 }
 
 // One wave per l: lanes take m = lane, lane + 64, ...; then a shuffle tree.
@@ -1147,40 +1349,27 @@ __global__ void __launch_bounds__(64) alm2cl_kernel(ClArgs a) {
 
 }  // namespace
 
-template <bool SYN>
-hipError_t launch_rings(const ShtArgs &a, hipStream_t s) {
-    const int N = a.nside;
-    const void *kern = SYN ? (const void *)ring_synth_kernel : (const void *)ring_fourier_kernel;
-    // LDS: two ring buffers and the odd-factor twiddle table (q <= length / 4)
-    auto lds_for = [](int nmax) { return (2 * (size_t)nmax + (size_t)nmax / 4 + 1) * sizeof(double2); };
-    hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_for(4 * N));
-    if (e != hipSuccess) return e;
-    // classes by cap ring index k (ring length 4k): k <= N/4, N/4 < k <= N/2, the rest
-    // (longer polar rings and the equatorial belt, length 4N)
-    const int c1 = N / 4, c2 = N / 2;
-    const int bounds[3] = {c1, c2, N};
-    int lo = 0;
-    for (int c = 0; c < 3; ++c) {
-        const int hi = bounds[c];
-        RingRange rr{};
-        if (c < 2) {       // north rings k = lo+1..hi and their southern mirrors
-            rr = RingRange{lo, hi, a.nrings - hi, a.nrings - lo};
-        } else {           // everything between
-            rr = RingRange{lo, a.nrings - lo, 0, 0};
-        }
-        const int nblocks = (rr.r1 - rr.r0) + (rr.r3 - rr.r2);
-        const int nmax = c < 2 ? 4 * hi : 4 * N;
-        if (nblocks > 0) {
-            if (SYN)
-                hipLaunchKernelGGL(ring_synth_kernel, dim3(nblocks), dim3(256), lds_for(nmax), s, a, rr);
-            else
-                hipLaunchKernelGGL(ring_fourier_kernel, dim3(nblocks), dim3(256), lds_for(nmax), s, a, rr);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        lo = hi;
+// One launch for all ring pairs (see ring_fourier_kernel on the groups).
+template <bool SYN, int NT, int B, int G>
+static hipError_t launch_rings_t(const ShtArgs &a, hipStream_t s) {
+    const size_t lds = (size_t)ring_lds<G>(SYN) * a.nside * sizeof(double2);
+    if (lds > 64 * 1024) {
+        const void *k = SYN ? (const void *)ring_synth_kernel<NT, B, G> : (const void *)ring_fourier_kernel<NT, B, G>;
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    if (SYN) hipLaunchKernelGGL((ring_synth_kernel<NT, B, G>), dim3(2 * a.nside), dim3(NT * G), lds, s, a);
+    else hipLaunchKernelGGL((ring_fourier_kernel<NT, B, G>), dim3(2 * a.nside), dim3(NT * G), lds, s, a);
+    return hipGetLastError();
+}
+
+template <bool SYN>
+static hipError_t launch_rings(const ShtArgs &a, hipStream_t s) {
+    static_assert(SHT_MAX_NSIDE <= 2 * 512, "butterflies of the longest ring");
+    if (a.nside > 512) return launch_rings_t<SYN, 512, 2, 1>(a, s);
+    if (a.nside > 256) return launch_rings_t<SYN, 256, 2, 4>(a, s);
+    if (a.nside > 128) return launch_rings_t<SYN, 128, 2, 4>(a, s);
+    return launch_rings_t<SYN, 64, 2, 12>(a, s);
 }
 
 hipError_t launch_ring_fourier(const ShtArgs &a, hipStream_t s) { return launch_rings<false>(a, s); }
@@ -1202,12 +1391,6 @@ hipError_t launch_alm2map(const ShtArgs &a, hipStream_t s) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_rings<true>(a, s);
-}
-
-hipError_t launch_axpy(double *y, const double *x, double alpha, int64_t n, bool reverse, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(axpy_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, y, x, alpha, n, reverse);
-    return hipGetLastError();
 }
 
 hipError_t launch_steps(const ShtArgs &a, hipStream_t s) {

@@ -36,7 +36,7 @@ int64_t nfield(bool pol) { return pol ? 3 : 1; }
 // residual map per field.  Its size is part of the interface and dates from
 // eight waves' partial sums of every a_lm and an a_lm correction per field (the
 // kernels also read, and do not use, up to 7 steps past the last a_lm's: inside it
-// for every lmax).
+// for every lmax, as are the sums of 4 nside rings in place of 4 nside - 1).
 int64_t workspace_bytes(int64_t nside, int64_t lmax, bool pol) {
     return fourier_bytes(nside, lmax, pol) + 8 * nalm(lmax) * 6 * 8 + nfield(pol) * 12 * nside * nside * 8 +
            nfield(pol) * nalm(lmax) * 16;
@@ -52,7 +52,7 @@ Layout layout(void *ws, int64_t nside, int64_t lmax, bool pol) {
     char *p = static_cast<char *>(ws);
     Layout L;
     L.F = reinterpret_cast<double2 *>(p);
-    p += fourier_bytes(nside, lmax, pol);
+    p += nfield(pol) * (lmax + 1) * 4 * nside * (int64_t)sizeof(double2);
     L.resid = reinterpret_cast<double *>(p);
     p += nfield(pol) * 12 * nside * nside * 8;
     L.steps = p;
@@ -67,7 +67,6 @@ pisco::ShtArgs base_args(int64_t nside, int32_t lmax, bool pol, const Layout &L)
     a.lmax = lmax;
     a.mmax = lmax;
     a.nfields = pol ? 3 : 1;
-    a.nrings = (int)(4 * nside - 1);
     a.F = L.F;
     a.steps = L.steps;
     a.partial = L.partial;
@@ -120,10 +119,11 @@ pisco_status map2alm(pisco_ctx *ctx, int64_t nside, int32_t lmax, int32_t iterat
     if (e == hipSuccess) e = analyse(a, maps, alm, st);
     // Jacobi steps: a <- a + map2alm(m - alm2map(a))
     for (int it = 0; it < iterations && e == hipSuccess; ++it) {
-        e = synthesise(a, alm, resid, st);
-        for (int f = 0; f < nf && e == hipSuccess; ++f) e = pisco::launch_axpy(resid[f], maps[f], -1.0, npix, true, st);
-        const double *rc[3] = {resid[0], resid[1], resid[2]};
         pisco::ShtArgs d = a;
+        d.residual = 1;
+        for (int f = 0; f < nf; ++f) d.map[f] = maps[f];
+        e = synthesise(d, alm, resid, st);
+        const double *rc[3] = {resid[0], resid[1], resid[2]};
         d.add = 1;
         if (e == hipSuccess) e = analyse(d, rc, alm, st);
     }
