@@ -26,9 +26,10 @@ struct ShtArgs {
 };
 
 struct ClArgs {
-    int lmax, nspec;                       // up to 6 spectra
-    const double *x[6], *y[6];             // complex interleaved a_lm of each pair
-    double *cl;                            // [nspec][lmax + 1]
+    int lmax;
+    bool teb;                              // x = a^T, a^E, a^B: spectra TT, EE, BB, TE, EB, TB; else of x[0] and y[0]
+    const double *x[3], *y[1];             // complex interleaved
+    double *cl;                            // [6 or 1][lmax + 1]
 };
 
 hipError_t launch_steps(const ShtArgs &a, hipStream_t s);            // before any launch_alm or launch_alm2map of its lmax

@@ -16,7 +16,7 @@
 //                        exponent, so sin^m theta cannot underflow) and
 //                        accumulate against the pair's ring sums; every four l a
 //                        wave adds its lanes, every 64 l the workgroup its waves;
-//   alm2cl_kernel        one wave per l: C_l of up to six a_lm pairs;
+//   alm2cl_kernel        C_l of a pair of a_lm, or of the six pairs of T, E, B;
 //   alm2ring_kernel      the synthesis: the same recurrences, lanes own ring pairs
 //                        and sum over l in registers (no cross-lane sums);
 //   ring_synth_kernel    one workgroup per ring: the m sums folded onto the ring
@@ -83,8 +83,10 @@ __device__ inline RingGeom sht_ring(int N, int r) {
 // of power-of-two length >= 2 k - 1 by the same FFT; the chirp's spectrum stays in
 // registers, and the chirps and the radix-4 step's twiddles are one exponential
 // e^{-i pi (4 j^2 + 2 a j) / n} of an exact integer.  (A DFT of the odd factor of n
-// summed directly took O(n) operations a point: most of 3.4 ms at nside 1024, one
-// LDS read per multiply-add, and the passes called sincospi for every butterfly.)
+// summed directly took O(n) operations a point, an LDS read per multiply-add, and
+// the passes called sincospi for every butterfly: 3.4 ms at nside 1024, lmax 3071,
+// now 0.86 ms, in passes of LDS reads, barriers and writes; 54 us at nside 128 in three
+// launches, now 20.)
 // ----------------------------------------------------------------------
 // Pair of workgroup b: the chirp rings first (the longest), then the belt; four
 // consecutive pairs on one die (workgroups are dealt to the eight in turn), so
@@ -1329,21 +1331,51 @@ __global__ void __launch_bounds__(64 * NW, K >= 4 ? 2 : 1) alm2ring_kernel(ShtAr
     }
 }
 
-// One wave per l: lanes take m = lane, lane + 64, ...; then a shuffle tree.
-__global__ void __launch_bounds__(64) alm2cl_kernel(ClArgs a) {
-    const int l = blockIdx.x;
-    const int lane = threadIdx.x;
-    for (int sp = 0; sp < a.nspec; ++sp) {
-        double acc = 0.0;
-        for (int m = lane; m <= l; m += 64) {
-            const int64_t idx = (int64_t)m * (2 * a.lmax + 1 - m) / 2 + l;
-            const double2 x = reinterpret_cast<const double2 *>(a.x[sp])[idx];
-            const double2 y = reinterpret_cast<const double2 *>(a.y[sp])[idx];
-            const double p = fma(x.x, y.x, x.y * y.y);
-            acc += m == 0 ? p : 2.0 * p;
+// C_l: a workgroup takes CL_L consecutive l, half a wave of lanes over them (an
+// a_lm column is contiguous in l) and the 2 CL_WAVES half waves over m, then adds the
+// halves in a fixed order.  Reads each a_lm once for all the spectra (TEB: T, E, B
+// and their six pairs; else one pair).  Bound by the reads: lmax 3071, 0.10 ms for 226
+// MB; 0.73 with a wave per l, whose lanes over m read a line each, six times over.
+constexpr int CL_L = 32, CL_WAVES = 16;
+template <bool TEB>
+__global__ void __launch_bounds__(64 * CL_WAVES) alm2cl_kernel(ClArgs a) {
+    constexpr int NX = TEB ? 6 : 1, HALVES = 2 * CL_WAVES;
+    __shared__ double part[NX][HALVES][CL_L];
+    const int li = threadIdx.x % CL_L, half = threadIdx.x / CL_L;
+    const int l = blockIdx.x * CL_L + li;
+    double acc[NX];
+#pragma unroll
+    for (int t = 0; t < NX; ++t) acc[t] = 0.0;
+    if (l <= a.lmax) {
+        for (int m = half; m <= l; m += HALVES) {
+            const int64_t i = (int64_t)m * (2 * a.lmax + 1 - m) / 2 + l;
+            const double w = m == 0 ? 1.0 : 2.0;
+            if constexpr (TEB) {
+                const double2 T = reinterpret_cast<const double2 *>(a.x[0])[i];
+                const double2 E = reinterpret_cast<const double2 *>(a.x[1])[i];
+                const double2 B = reinterpret_cast<const double2 *>(a.x[2])[i];
+                acc[0] = fma(w, fma(T.x, T.x, T.y * T.y), acc[0]);
+                acc[1] = fma(w, fma(E.x, E.x, E.y * E.y), acc[1]);
+                acc[2] = fma(w, fma(B.x, B.x, B.y * B.y), acc[2]);
+                acc[3] = fma(w, fma(T.x, E.x, T.y * E.y), acc[3]);
+                acc[4] = fma(w, fma(E.x, B.x, E.y * B.y), acc[4]);
+                acc[5] = fma(w, fma(T.x, B.x, T.y * B.y), acc[5]);
+            } else {
+                const double2 x = reinterpret_cast<const double2 *>(a.x[0])[i];
+                const double2 y = reinterpret_cast<const double2 *>(a.y[0])[i];
+                acc[0] = fma(w, fma(x.x, y.x, x.y * y.y), acc[0]);
+            }
         }
-        for (int o = 32; o; o >>= 1) acc += __shfl_xor(acc, o, 64);
-        if (lane == 0) a.cl[(size_t)sp * (a.lmax + 1) + l] = acc / (2.0 * l + 1.0);
+    }
+#pragma unroll
+    for (int t = 0; t < NX; ++t) part[t][half][li] = acc[t];
+    __syncthreads();
+    for (int i = threadIdx.x; i < NX * CL_L; i += blockDim.x) {
+        const int t = i / CL_L, j = i % CL_L, lo = blockIdx.x * CL_L + j;
+        if (lo > a.lmax) continue;
+        double s = 0.0;
+        for (int h = 0; h < HALVES; ++h) s += part[t][h][j];
+        a.cl[(size_t)t * (a.lmax + 1) + lo] = s / (2.0 * lo + 1.0);
     }
 }
 
@@ -1440,7 +1472,9 @@ hipError_t launch_alm(const ShtArgs &a, hipStream_t s) {
 }
 
 hipError_t launch_alm2cl(const ClArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(alm2cl_kernel, dim3(a.lmax + 1), dim3(64), 0, s, a);
+    const dim3 g(a.lmax / CL_L + 1), t(64 * CL_WAVES);
+    if (a.teb) hipLaunchKernelGGL(alm2cl_kernel<true>, g, t, 0, s, a);
+    else hipLaunchKernelGGL(alm2cl_kernel<false>, g, t, 0, s, a);
     return hipGetLastError();
 }
 

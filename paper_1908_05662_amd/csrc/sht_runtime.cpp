@@ -178,7 +178,6 @@ pisco_status pisco_alm2cl(pisco_ctx *ctx, int32_t lmax, const double *alm_x, con
     if (ed != hipSuccess) return launched(ctx, ed);
     pisco::ClArgs a{};
     a.lmax = lmax;
-    a.nspec = 1;
     a.x[0] = alm_x;
     a.y[0] = alm_y;
     a.cl = cl;
@@ -197,17 +196,11 @@ pisco_status pisco_anafast(pisco_ctx *ctx, int64_t nside, int32_t lmax, int32_t 
     pisco::ClArgs a{};
     a.lmax = lmax;
     a.cl = cl;
+    a.teb = Q != nullptr;
+    a.x[0] = a.y[0] = alm_T;
     if (Q) {
-        const double *x[6] = {alm_T, alm_E, alm_B, alm_T, alm_E, alm_T};
-        const double *y[6] = {alm_T, alm_E, alm_B, alm_E, alm_B, alm_B};
-        a.nspec = 6;
-        for (int k = 0; k < 6; ++k) {
-            a.x[k] = x[k];
-            a.y[k] = y[k];
-        }
-    } else {
-        a.nspec = 1;
-        a.x[0] = a.y[0] = alm_T;
+        a.x[1] = alm_E;
+        a.x[2] = alm_B;
     }
     return launched(ctx, pisco::launch_alm2cl(a, st));
 }
