@@ -1202,9 +1202,13 @@ __device__ __forceinline__ void consume_records(const typename Cond<QF, PixRecQ,
     }
 }
 
+// With `parts` > 1 the waves of a workgroup share the tile: wave `part` takes every
+// parts-th chunk of each ring batch (the groups of records whose terms are summed in
+// FP32 stay the same; only the FP64 sums are split), and the first wave adds the
+// waves' sums in order.  L is this wave's slice, the others' lie beside it.
 template <int MODE, int BEAM, int CH, bool PS, bool HWP>
 __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin, int32_t cnt, TileLds<CH> &L,
-                              float *vrec, int lane) {
+                              float *vrec, int lane, int32_t part, int32_t parts) {
     static_assert(CH % WAVE == 0, "chunks are whole waves of records");
     const float4 *__restrict__ sky = reinterpret_cast<const float4 *>(A.sky);
     const int32_t N = (int32_t)A.nside;
@@ -1289,7 +1293,7 @@ __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin
         // ring of the chunk's first record, or an earlier one: each lane's search
         // starts there instead of at the batch's first ring
         int32_t seg0 = 0;
-        for (int32_t pb = 0; pb < total; pb += CH) {
+        for (int32_t pb = part * CH; pb < total; pb += parts * CH) {
             const int32_t m_end = min(CH, total - pb);
             // fill: one pixel record per lane, FP32 differences from the centre
             int32_t seg = seg0;
@@ -1430,6 +1434,34 @@ __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin
         }
     }
 
+    if (parts > 1) {
+        // the waves' sums meet in their own slices (free now)
+        struct Sums {
+            double a0[WAVE], a1[WAVE], a2[WAVE], an[WAVE];
+            int32_t np[WAVE];
+        };
+        static_assert(sizeof(Sums) <= sizeof(TileLds<CH>), "the sums fit a slice");
+        Sums &mine = reinterpret_cast<Sums &>(L);
+        wave_sync();
+        mine.a0[lane] = acc0.s;
+        mine.a1[lane] = acc1.s;
+        mine.a2[lane] = acc2.s;
+        mine.an[lane] = accn.s;
+        mine.np[lane] = npairs;
+        __syncthreads();
+        if (part == 0) {
+            for (int32_t w = 1; w < parts; ++w) {
+                const Sums &o = reinterpret_cast<const Sums &>(*(&L + w));
+                acc0.s += o.a0[lane];
+                acc1.s += o.a1[lane];
+                acc2.s += o.a2[lane];
+                accn.s += o.an[lane];
+                npairs += o.np[lane];
+            }
+        }
+        __syncthreads();   // the next tile overwrites the slices
+        if (part != 0) return;
+    }
     if (!valid) return;
     float *out = reinterpret_cast<float *>(A.out);
     const int64_t o = D.out_offset + t;
@@ -1848,20 +1880,30 @@ __global__ void __launch_bounds__(512, (tile_min_waves<MODE, BEAM>())) tile_kern
     float *vrec = (BEAM == BEAM_FULL && MODE == MODE_TOD && A.vbeam)
                       ? reinterpret_cast<float *>(lds_raw + sizeof(TileLds<CH>) * (blockDim.x / WAVE)) + wid * CH
                       : nullptr;
-    int32_t q = (A.n_queues > 1) ? (int32_t)(blockIdx.x % (uint32_t)A.n_queues) : 0;
+    // a shared tile's workgroup takes every gridDim-th tile (uniform over the
+    // workgroup: the waves meet at barriers)
+    const bool shared = A.share_tiles != 0;
+    const int32_t part = shared ? __builtin_amdgcn_readfirstlane(wid) : 0;
+    const int32_t parts = shared ? (int32_t)(blockDim.x / WAVE) : 1;
+    int32_t q = (!shared && A.n_queues > 1) ? (int32_t)(blockIdx.x % (uint32_t)A.n_queues) : 0;
+    int32_t next = (int32_t)blockIdx.x;
     int32_t exhausted = 0;
     while (exhausted < A.n_queues) {
-        int32_t ti = 0;
-        if (lane == 0) ti = pop_tile(&A.counters[q], A.queue_len[q]);
-        ti = __builtin_amdgcn_readfirstlane(__shfl(ti, 0, WAVE));
+        int32_t ti = next;
+        if (!shared) {
+            if (lane == 0) ti = pop_tile(&A.counters[q], A.queue_len[q]);
+            ti = __builtin_amdgcn_readfirstlane(__shfl(ti, 0, WAVE));
+        }
+        next += (int32_t)gridDim.x;
         if (ti >= A.queue_len[q]) {
+            next = (int32_t)blockIdx.x;
             q = (q + 1 == A.n_queues) ? 0 : q + 1;
             ++exhausted;
             continue;
         }
         const Tile tl = A.tiles[(int64_t)q * A.tiles_per_queue + ti];
         const DetDesc &D = A.dets[tl.det];
-        convolve_tile<MODE, BEAM, CH, PS, HWP>(A, D, tl.begin, tl.count, L, vrec, lane);
+        convolve_tile<MODE, BEAM, CH, PS, HWP>(A, D, tl.begin, tl.count, L, vrec, lane, part, parts);
     }
 }
 
@@ -2047,6 +2089,20 @@ hipError_t launch_zero_counters(int32_t *counters, int n, hipStream_t s) {
     return hipGetLastError();
 }
 
+// A wave takes a tile, and four waves fit a SIMD: with fewer tiles than that the chip
+// is partly idle and the time is one wave's walk through one tile.  Then 8, 4 or 2
+// waves share each tile (each does the tile's set-up again).  Measured at nside
+// 1024, 2 deg, one-grid beams, us for T tiles with 1 / 2 / 4 / 8 waves a tile: T = 64:
+// 602 / 306 / 171 / 118; 256: 632 / 318 / 183 / 133; 512: 644 / 336 / 213 / 209; 1024:
+// 715 / 371 / 347 / 397; 2048: 1088 / 633 / 675 / 797; 4096: 1269 / 1177 / 1288 / 1485;
+// 6144: 1790 / 1775 / 1924 / 2190 (256 compute units; four-channel beams, Stokes pickups
+// and 6 deg discs cross at the same places).
+void share_tiles(ConvArgs &a, int64_t n, int num_cu) {
+    const int w = n <= num_cu ? 8 : n <= 4 * num_cu ? 4 : n <= 20 * num_cu ? 2 : 0;
+    a.share_tiles = w;
+    a.share_groups = w ? (int32_t)std::min<int64_t>(n, (int64_t)num_cu * (16 / w)) : 0;
+}
+
 template <typename T, int MODE>
 static hipError_t launch_pixel(const ConvArgs &a, int waves, int groups, hipStream_t s) {
     const size_t lds = sizeof(WaveLds<T>) * (size_t)waves;
@@ -2060,6 +2116,10 @@ static hipError_t launch_pixel(const ConvArgs &a, int waves, int groups, hipStre
 template <int MODE, int BEAM, int CH, bool PS, bool HWP>
 static hipError_t launch_tile_h(const ConvArgs &a, int waves, int groups, hipStream_t s) {
     const bool v = BEAM == BEAM_FULL && MODE == MODE_TOD && a.vbeam;
+    if (a.share_tiles) {
+        waves = a.share_tiles;
+        groups = a.share_groups;
+    }
     const size_t lds = (sizeof(TileLds<CH>) + (v ? sizeof(float) * CH : 0)) * (size_t)waves;
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     if (lds > 64 * 1024) {  // allow the larger LDS allocations of gfx950 (160 KiB per CU)
@@ -2272,7 +2332,7 @@ void *static_scratch(int device) {
 }
 
 hipError_t launch_static(ConvArgs tile, ConvArgs pix, const DetDesc &D, bool tile_path, bool f64, int waves,
-                         int groups, void *base, hipStream_t s) {
+                         int groups, int num_cu, void *base, hipStream_t s) {
     unsigned char *b = static_cast<unsigned char *>(base);
     int32_t *ctrl = reinterpret_cast<int32_t *>(b);
     const int64_t ng = (D.n_samples + WAVE - 1) / WAVE;
@@ -2299,10 +2359,11 @@ hipError_t launch_static(ConvArgs tile, ConvArgs pix, const DetDesc &D, bool til
     pix.counters = ctrl + 16;
     pix.queue_len = ctrl + 24;
     if (tile_path) {
-        e = launch_conv(tile, f64, waves, groups, s);
+        share_tiles(tile, ng, num_cu);
+        e = launch_conv(tile, f64, waves, (int)std::min<int64_t>(groups, ng), s);
         if (e != hipSuccess) return e;
     }
-    return launch_conv(pix, f64, waves, groups, s);
+    return launch_conv(pix, f64, waves, (int)std::min<int64_t>(groups, ng * WAVE), s);
 }
 
 }  // namespace pisco

@@ -65,7 +65,11 @@ struct ConvArgs {
     int32_t per_sample;      // some detector of the launch uses per-sample normalisation
     int32_t hwp;             // some detector of the launch has a half-wave plate
     int32_t vbeam;           // some detector of the launch has a full beam with a V column
+    int32_t share_tiles;     // tile path: waves that share a tile (0: a wave takes a tile)
+    int32_t share_groups;    // workgroups of a launch that shares tiles
 };
+// Fill share_tiles and share_groups of a tile launch over n tiles (at most).
+void share_tiles(ConvArgs &a, int64_t n, int num_cu);
 
 // Launch helpers (conv_kernel.hip).  Return the launch error.
 hipError_t launch_zero_counters(int32_t *counters, int n, hipStream_t s);
@@ -109,7 +113,7 @@ void *static_scratch(int device);
 // device, then run the tile and pixel kernels with args tile / pix (their plan
 // pointers are filled in here).
 hipError_t launch_static(ConvArgs tile, ConvArgs pix, const DetDesc &D, bool tile_path, bool f64, int waves,
-                         int groups, void *base, hipStream_t s);
+                         int groups, int num_cu, void *base, hipStream_t s);
 
 }  // namespace pisco
 

@@ -651,7 +651,9 @@ hipError_t enqueue(pisco_ctx *c, const Plan &p, void *out, int out_mode, hipStre
     if (e != hipSuccess) return e;
     const bool f64 = c->sky_dtype == PISCO_F64;
     if (p.tq.ntiles > 0) {
-        e = pisco::launch_conv(make_args(c, p, out, out_mode, true), f64, c->wpg, c->gpc * c->num_cu, s);
+        pisco::ConvArgs a = make_args(c, p, out, out_mode, true);
+        pisco::share_tiles(a, p.tq.ntiles, c->num_cu);
+        e = pisco::launch_conv(a, f64, c->wpg, c->gpc * c->num_cu, s);
         if (e != hipSuccess) return e;
     }
     if (p.pq.ntiles > 0) {
@@ -1658,7 +1660,7 @@ pisco_status pisco_convolve_static(pisco_ctx *c, int32_t det, int out_mode, void
     const bool tile_path = (c->algo == PISCO_ALGO_TILE || c->algo == PISCO_ALGO_TILE_MX) && c->sky_dtype == PISCO_F32;
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = pisco::launch_static(tile, pix, x, tile_path, c->sky_dtype == PISCO_F64, c->wpg,
-                                        c->gpc * c->num_cu, base, s);
+                                        c->gpc * c->num_cu, c->num_cu, base, s);
     if (e == hipSuccess && sub) {
         const SlApply ap = sl_apply_of(d, d.th, d.ph, d.ps, d.nsamp, 0);
         e = pisco::mlp_apply_pointing(ap.net, ap.th, ap.ph, ap.ps, ap.n, ap.mean, ap.stdv, ap.coef,
