@@ -96,6 +96,12 @@ __device__ inline double ring_of_theta(int32_t N, double th) {
     return (double)N * (2.0 - 1.5 * z);
 }
 
+// The same from z = cos(theta).
+__device__ inline double ring_of_z(int32_t N, double z) {
+    const double w = (double)N * sqrt(3.0 * fmax(0.0, 1.0 - fabs(z)));
+    return fabs(z) <= 2.0 / 3.0 ? (double)N * (2.0 - 1.5 * z) : (z > 0.0 ? w : 4.0 * N - w);
+}
+
 // Pixels of ring g with cos(angular distance) >= cosr, as k in [lo, lo + cnt)
 // counted from the pixel nearest the boresight longitude (cnt = n: whole ring).
 __device__ inline void ring_interval(double cosr, double z0, double s0, const RingGeom &g, double dphic,
@@ -150,7 +156,24 @@ __device__ inline void half_sincos(float x, float &s, float &c) {
     pc = fmaf(x2, pc, C2);
     c = fmaf(x2, pc, 1.0f);
 }
-__device__ inline void half_sincos(double x, double &s, double &c) { sincos(x, &s, &c); }
+// FP64: the device math library, and for |x| <= 1/4 the Taylor series to x^11 and x^12
+// (truncation 1e-17 and 3e-20 relative).  Lane by lane: a value may not depend on what
+// the wave's other lanes hold.
+__device__ inline void half_sincos(double x, double &s, double &c) {
+    const double x2 = x * x;
+    double ps = fma(x2, -1.0 / 39916800.0, 1.0 / 362880.0);
+    ps = fma(x2, ps, -1.0 / 5040.0);
+    ps = fma(x2, ps, 1.0 / 120.0);
+    ps = fma(x2, ps, -1.0 / 6.0);
+    s = fma(x * x2, ps, x);
+    double pc = fma(x2, 1.0 / 479001600.0, -1.0 / 3628800.0);
+    pc = fma(x2, pc, 1.0 / 40320.0);
+    pc = fma(x2, pc, -1.0 / 720.0);
+    pc = fma(x2, pc, 1.0 / 24.0);
+    pc = fma(x2, pc, -0.5);
+    c = fma(x2, pc, 1.0);
+    if (fabs(x) > 0.25) sincos(x, &s, &c);
+}
 
 // Per-lane accumulator: compensated (Kahan) in FP32, plain in FP64.  The
 // compensated sum is s - c.
@@ -163,9 +186,10 @@ template <> struct Acc<float> {
         c = (t - s) - y;
         s = t;
     }
-    __device__ inline void wave_reduce() {
+    template <int G>
+    __device__ inline void reduce() {   // over groups of G lanes
 #pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) {
+        for (int m = G / 2; m >= 1; m >>= 1) {
             const float os = __shfl_xor(s, m, WAVE);
             const float oc = __shfl_xor(c, m, WAVE);
             add(os);
@@ -177,9 +201,10 @@ template <> struct Acc<float> {
 template <> struct Acc<double> {
     double s = 0.0;
     __device__ inline void add(double x) { s += x; }
-    __device__ inline void wave_reduce() {
+    template <int G>
+    __device__ inline void reduce() {
 #pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m, WAVE);
+        for (int m = G / 2; m >= 1; m >>= 1) s += __shfl_xor(s, m, WAVE);
     }
     __device__ inline double value() const { return s; }
 };
@@ -238,6 +263,15 @@ __device__ inline int wave_inclusive_scan(int v, int) {
     return v;
 }
 
+// The same within each row of 16 lanes.
+__device__ inline int row_inclusive_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    return v;
+}
+
 template <typename T> __device__ inline T lerp(T a, T b, T t) { return fma(t, b - a, a); }
 
 // Reciprocal: the hardware approximation (1 ulp) in FP32, exact division in FP64.
@@ -289,14 +323,32 @@ __device__ inline BeamVals<T> beam_lookup(const void *beam, int32_t n, int32_t i
 }
 
 // ----------------------------------------------------------------------
-// Pixel-parallel path: one sample at a time, lanes over its disc pixels
+// Pixel-parallel path: lanes over the pixels of a sample's disc.  G = 64: a sample
+// at a time.  G = 16 (discs of at most 16 rings): four samples at a time, a row of 16
+// lanes each, so that the FP64 set-up of a sample and of its rings, which costs more
+// than the at most 100 pixels of such a disc, serves four at once.  What bounds it is
+// that set-up in both forms.  FP64 samples swept over an nside-64 sky, 4.5 deg, us for
+// 8192 / 32768 / 131072 samples with G = 64 and 16: 119 / 223 / 596 and 18 / 50 / 172.
+// Past 16 rings the few-sample latency decides: at 23 rings (nside 128) 131072 samples
+// take 694 and 382, but 16 of them 13 and 22, as a disc's pixels then take a row many
+// rounds, one sky and beam latency each.
 // ----------------------------------------------------------------------
-template <typename T, int MODE, int BEAM>
-__device__ void convolve_sample(const ConvArgs &A, const DetDesc &D, int64_t pos, WaveLds<T> &L, int lane) {
+// What a tile's samples share.
+struct PixTile {
+    double sz, cz;        // sin, cos of zeta
+    double sr;            // sin of rho_max
+};
+
+template <typename T, int MODE, int BEAM, int G>
+__device__ void convolve_sample(const ConvArgs &A, const DetDesc &D, const PixTile &P, int64_t pos, bool valid,
+                                WaveLds<T> &L, int lane) {
     const int64_t t = sample_at(D, pos);
     using R4 = typename Rec4<T>::type;
     const R4 *__restrict__ sky = reinterpret_cast<const R4 *>(A.sky);
     const int32_t N = (int32_t)A.nside;
+    const int sl = lane & (G - 1);                       // lane of the sample's group
+    RingRec<T> *recs = L.rec + (lane & ~(G - 1));        // the group's rings and segment ends
+    int32_t *seg_end = L.seg_end + 2 * (lane & ~(G - 1));
 
     // FP64 set-up of the sample's frame
     const double th0 = D.theta[t];
@@ -306,7 +358,12 @@ __device__ void convolve_sample(const ConvArgs &A, const DetDesc &D, int64_t pos
     sincos(th0, &s0, &z0);
     ph0 -= TWO_PI * floor(ph0 * (1.0 / TWO_PI));
     sincos(ps0, &sp, &cp);
-    sincos(ps0 + D.zeta, &sg, &cg);
+    if constexpr (G == WAVE) {
+        sincos(ps0 + D.zeta, &sg, &cg);
+    } else {
+        sg = sp * P.cz + cp * P.sz;
+        cg = cp * P.cz - sp * P.sz;
+    }
     const T cpsi = (T)cp, spsi = (T)sp, g1 = (T)cg, g2 = (T)sg, z0t = (T)z0, s0t = (T)s0;
     const int32_t n = D.n;
     const T inv_h = (T)D.inv_h;
@@ -328,14 +385,25 @@ __device__ void convolve_sample(const ConvArgs &A, const DetDesc &D, int64_t pos
 
     const int32_t nring = 4 * N - 1;
     const double rho = D.rho_max;
-    const int32_t r_lo = (th0 - rho <= 0.0) ? 1 : max(1, (int32_t)floor(ring_of_theta(N, th0 - rho)) - 1);
-    const int32_t r_hi = (th0 + rho >= PI) ? nring : min(nring, (int32_t)ceil(ring_of_theta(N, th0 + rho)) + 1);
+    int32_t r_lo, r_hi;
+    if constexpr (G == WAVE) {
+        r_lo = (th0 - rho <= 0.0) ? 1 : max(1, (int32_t)floor(ring_of_theta(N, th0 - rho)) - 1);
+        r_hi = (th0 + rho >= PI) ? nring : min(nring, (int32_t)ceil(ring_of_theta(N, th0 + rho)) + 1);
+    } else {
+        // no more rings than the disc can meet (16 a pass), from the edges' cosines:
+        // the ring coordinate is off by less than 1e-6 wherever it exceeds one
+        const double zl = z0 * D.cos_rho_max + s0 * P.sr, zh = z0 * D.cos_rho_max - s0 * P.sr;
+        r_lo = (th0 - rho <= 0.0) ? 1 : max(1, (int32_t)ceil(ring_of_z(N, zl) - 1e-6));
+        r_hi = (th0 + rho >= PI) ? nring : min(nring, (int32_t)floor(ring_of_z(N, zh) + 1e-6));
+        if (!valid) r_hi = r_lo - 1;
+    }
 
     Acc<T> acc0, acc1, acc2, accn;
     int64_t npairs = 0;
 
-    for (int32_t rb = r_lo; rb <= r_hi; rb += WAVE) {
-        const int32_t r = rb + lane;
+    // (G < 64: until the wave's last sample has no ring left)
+    for (int32_t rb = r_lo; G == WAVE ? rb <= r_hi : __any(rb <= r_hi); rb += G) {
+        const int32_t r = rb + sl;
         int32_t n0 = 0, n1 = 0;
         if (r <= r_hi) {
             const RingGeom g = ring_geom(N, r);
@@ -386,14 +454,14 @@ __device__ void convolve_sample(const ConvArgs &A, const DetDesc &D, int64_t pos
             R.jc = jc;
             R.k0 = k0;
             R.k1 = k1;
-            L.rec[lane] = R;
+            recs[sl] = R;
         }
         const int32_t tot = n0 + n1;
-        const int32_t incl = wave_inclusive_scan(tot, lane);
+        const int32_t incl = G == WAVE ? wave_inclusive_scan(tot, lane) : row_inclusive_scan(tot);
         const int32_t excl = incl - tot;
-        L.seg_end[2 * lane] = excl + n0;
-        L.seg_end[2 * lane + 1] = incl;
-        const int32_t total = __shfl(incl, WAVE - 1, WAVE);
+        seg_end[2 * sl] = excl + n0;
+        seg_end[2 * sl + 1] = incl;
+        const int32_t total = __shfl(incl, lane | (G - 1), WAVE);
         if (MODE == MODE_COUNT) {
             npairs += total;
             continue;
@@ -401,10 +469,10 @@ __device__ void convolve_sample(const ConvArgs &A, const DetDesc &D, int64_t pos
         wave_sync();
 
         int32_t seg = 0;
-        for (int32_t f = lane; f < total; f += WAVE) {
-            while (f >= L.seg_end[seg]) ++seg;
-            const int32_t start = (seg == 0) ? 0 : L.seg_end[seg - 1];
-            const RingRec<T> &R = L.rec[seg >> 1];
+        for (int32_t f = sl; f < total; f += G) {
+            while (f >= seg_end[seg]) ++seg;
+            const int32_t start = (seg == 0) ? 0 : seg_end[seg - 1];
+            const RingRec<T> &R = recs[seg >> 1];
             const int32_t rn = R.n;
             const int32_t k = ((seg & 1) ? R.k1 : R.k0) + (f - start);
             const int32_t half = rn >> 1;
@@ -480,16 +548,16 @@ __device__ void convolve_sample(const ConvArgs &A, const DetDesc &D, int64_t pos
     }
 
     if (MODE == MODE_COUNT) {
-        if (lane == 0) reinterpret_cast<T *>(A.out)[D.out_offset + t] = (T)npairs;
+        if (sl == 0 && valid) reinterpret_cast<T *>(A.out)[D.out_offset + t] = (T)npairs;
         return;
     }
-    accn.wave_reduce();
-    acc0.wave_reduce();
+    accn.template reduce<G>();
+    acc0.template reduce<G>();
     if (MODE == MODE_STOKES) {
-        acc1.wave_reduce();
-        acc2.wave_reduce();
+        acc1.template reduce<G>();
+        acc2.template reduce<G>();
     }
-    if (lane == 0) {
+    if (sl == 0 && valid) {
         double Nrm = D.norm_scale;
         if (D.norm_mode == 1) {
             const double sn = accn.value() * (BEAM == BEAM_SCALAR ? D.w[3] : 1.0);
@@ -1839,35 +1907,86 @@ __device__ inline bool tile_is_coherent(const DetDesc &D, int64_t begin, int32_t
 // ----------------------------------------------------------------------
 // Kernels
 // ----------------------------------------------------------------------
-// Next tile of queue q for the calling wave (lane 0): a plain load first, so
-// waves that find a queue drained add nothing to the atomics its counter
-// serialises (thousands of waves checking every queue at the end of a launch).
-// The counter only grows, so a stale load at worst leads to the atomic.
-__device__ inline int32_t pop_tile(int32_t *counter, int32_t len) {
-    if (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= len) return len;
-    return atomicAdd(counter, 1);
-}
+// A wave's walk over the queues, its own first.  A wave owns the first OWN rounds of
+// tiles of its place in the launch; the later ones it pops from a counter (which starts
+// at the first tile that no wave owns).  The pops of one counter are served one after
+// the other, about 67 ns each, so a launch of 4096 waves that popped their first tiles
+// too had its last wave start 270 us late, and 8192 small tiles took 550 us.  A launch
+// that shares tiles pops nothing: a workgroup takes every gridDim-th tile.
+template <int OWN> struct TileWalk {
+    int32_t q, exhausted, own, rounds;
+    __device__ inline TileWalk(const ConvArgs &A, int wid) {
+        const uint32_t nq = (uint32_t)A.n_queues;
+        exhausted = 0;
+        rounds = OWN;
+        if (A.share_tiles) {
+            q = 0;
+            own = (int32_t)blockIdx.x;
+        } else {
+            q = nq > 1 ? (int32_t)(blockIdx.x % nq) : 0;
+            own = (int32_t)(nq > 1 ? blockIdx.x / nq : blockIdx.x) * (int32_t)(blockDim.x / WAVE) +
+                  __builtin_amdgcn_readfirstlane(wid);
+        }
+    }
+    // The next tile of the wave, or false when every queue is drained.  A plain load
+    // goes before the pop, so waves that find a queue drained add nothing to the
+    // atomics; the counter only grows, so a stale load at worst leads to the atomic.
+    __device__ inline bool next(const ConvArgs &A, int lane, Tile &tl) {
+        while (exhausted < A.n_queues) {
+            const int32_t len = A.queue_len[q];
+            int32_t ti = own;
+            if (A.share_tiles) {
+                own += (int32_t)gridDim.x;
+            } else {
+                // a round of queue q: the waves of its workgroups
+                const int32_t nq = A.n_queues;
+                const int32_t round = ((int32_t)gridDim.x + nq - 1 - q) / nq * (int32_t)(blockDim.x / WAVE);
+                if (rounds > 0) {
+                    --rounds;
+                    own += round;
+                } else {
+                    ti = len;
+                    if (lane == 0 && __hip_atomic_load(&A.counters[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
+                                             OWN * round < len)
+                        ti = OWN * round + atomicAdd(&A.counters[q], 1);
+                    ti = __builtin_amdgcn_readfirstlane(ti);
+                }
+            }
+            if (ti < len) {
+                tl = A.tiles[(int64_t)q * A.tiles_per_queue + ti];
+                return true;
+            }
+            own = (int32_t)blockIdx.x;
+            rounds = 0;
+            q = (q + 1 == A.n_queues) ? 0 : q + 1;
+            ++exhausted;
+        }
+        return false;
+    }
+};
 
 template <typename T, int MODE, int BEAM>
-__global__ void __launch_bounds__(512) conv_kernel(ConvArgs A) {
+__global__ void __launch_bounds__(512, (pixel_waves_per_simd(sizeof(T) == 8))) conv_kernel(ConvArgs A) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = threadIdx.x / WAVE;
     WaveLds<T> &L = reinterpret_cast<WaveLds<T> *>(lds_raw)[wid];
-    int32_t q = (A.n_queues > 1) ? (int32_t)(blockIdx.x % (uint32_t)A.n_queues) : 0;
-    int32_t exhausted = 0;
-    while (exhausted < A.n_queues) {
-        int32_t ti = 0;
-        if (lane == 0) ti = pop_tile(&A.counters[q], A.queue_len[q]);
-        ti = __shfl(ti, 0, WAVE);
-        if (ti >= A.queue_len[q]) {
-            q = (q + 1 == A.n_queues) ? 0 : q + 1;
-            ++exhausted;
+    TileWalk<2> walk(A, wid);
+    Tile tl;
+    while (walk.next(A, lane, tl)) {
+        const DetDesc &D = A.dets[tl.det];
+        const int64_t end = tl.begin + tl.count;
+        PixTile P{};
+        if (!D.pixel_rows) {
+            for (int64_t t = tl.begin; t < end; ++t) convolve_sample<T, MODE, BEAM, WAVE>(A, D, P, t, true, L, lane);
             continue;
         }
-        const Tile tl = A.tiles[(int64_t)q * A.tiles_per_queue + ti];
-        const DetDesc &D = A.dets[tl.det];
-        for (int64_t t = tl.begin; t < tl.begin + tl.count; ++t) convolve_sample<T, MODE, BEAM>(A, D, t, L, lane);
+        sincos(D.zeta, &P.sz, &P.cz);
+        P.sr = sqrt(D.omega_max * (2.0 - D.omega_max));
+        for (int64_t t = tl.begin; t < end; t += 4) {
+            const int64_t mine = t + lane / 16;
+            convolve_sample<T, MODE, BEAM, 16>(A, D, P, min(mine, end - 1), mine < end, L, lane);
+        }
     }
 }
 
@@ -1880,31 +1999,12 @@ __global__ void __launch_bounds__(512, (tile_min_waves<MODE, BEAM>())) tile_kern
     float *vrec = (BEAM == BEAM_FULL && MODE == MODE_TOD && A.vbeam)
                       ? reinterpret_cast<float *>(lds_raw + sizeof(TileLds<CH>) * (blockDim.x / WAVE)) + wid * CH
                       : nullptr;
-    // a shared tile's workgroup takes every gridDim-th tile (uniform over the
-    // workgroup: the waves meet at barriers)
-    const bool shared = A.share_tiles != 0;
-    const int32_t part = shared ? __builtin_amdgcn_readfirstlane(wid) : 0;
-    const int32_t parts = shared ? (int32_t)(blockDim.x / WAVE) : 1;
-    int32_t q = (!shared && A.n_queues > 1) ? (int32_t)(blockIdx.x % (uint32_t)A.n_queues) : 0;
-    int32_t next = (int32_t)blockIdx.x;
-    int32_t exhausted = 0;
-    while (exhausted < A.n_queues) {
-        int32_t ti = next;
-        if (!shared) {
-            if (lane == 0) ti = pop_tile(&A.counters[q], A.queue_len[q]);
-            ti = __builtin_amdgcn_readfirstlane(__shfl(ti, 0, WAVE));
-        }
-        next += (int32_t)gridDim.x;
-        if (ti >= A.queue_len[q]) {
-            next = (int32_t)blockIdx.x;
-            q = (q + 1 == A.n_queues) ? 0 : q + 1;
-            ++exhausted;
-            continue;
-        }
-        const Tile tl = A.tiles[(int64_t)q * A.tiles_per_queue + ti];
-        const DetDesc &D = A.dets[tl.det];
-        convolve_tile<MODE, BEAM, CH, PS, HWP>(A, D, tl.begin, tl.count, L, vrec, lane, part, parts);
-    }
+    const int32_t part = A.share_tiles ? __builtin_amdgcn_readfirstlane(wid) : 0;
+    const int32_t parts = A.share_tiles ? (int32_t)(blockDim.x / WAVE) : 1;
+    TileWalk<1> walk(A, wid);
+    Tile tl;
+    while (walk.next(A, lane, tl))
+        convolve_tile<MODE, BEAM, CH, PS, HWP>(A, A.dets[tl.det], tl.begin, tl.count, L, vrec, lane, part, parts);
 }
 
 template <int MODE, int BEAM, int CH, bool PS>
@@ -1913,18 +2013,9 @@ __global__ void __launch_bounds__(512, 2) tile_mx_kernel(ConvArgs A) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = threadIdx.x / WAVE;
     TileLdsMx<CH, mx_nacc<MODE>()> &L = reinterpret_cast<TileLdsMx<CH, mx_nacc<MODE>()> *>(lds_raw)[wid];
-    int32_t q = (A.n_queues > 1) ? (int32_t)(blockIdx.x % (uint32_t)A.n_queues) : 0;
-    int32_t exhausted = 0;
-    while (exhausted < A.n_queues) {
-        int32_t ti = 0;
-        if (lane == 0) ti = pop_tile(&A.counters[q], A.queue_len[q]);
-        ti = __builtin_amdgcn_readfirstlane(__shfl(ti, 0, WAVE));
-        if (ti >= A.queue_len[q]) {
-            q = (q + 1 == A.n_queues) ? 0 : q + 1;
-            ++exhausted;
-            continue;
-        }
-        const Tile tl = A.tiles[(int64_t)q * A.tiles_per_queue + ti];
+    TileWalk<1> walk(A, wid);
+    Tile tl;
+    while (walk.next(A, lane, tl)) {
         const DetDesc &D = A.dets[tl.det];
         convolve_tile_mx<MODE, BEAM, CH, PS>(A, D, tl.begin, tl.count, L, lane);
         wave_sync();  // the next tile's set-up overwrites the frames this one read

@@ -38,7 +38,18 @@ struct DetDesc {
     int32_t norm_mode;     // 0 fixed, 1 per sample
     int32_t has_inner;     // rho_min > 0
     int32_t needs_clip;    // the disc can reach beyond the grid
+    int32_t pixel_rows;    // pixel path: four samples at a time, see pixel_rows()
 };
+// Whether the pixel path takes four samples of a detector at a time: its disc has at
+// most 3 nside rho_max rings (at the equator), and 16 of them are one pass of a sample's
+// 16 lanes.  A property of the detector alone, so that a sample's value does not depend
+// on the launch that it is part of.
+constexpr int32_t pixel_rows(int64_t nside, double rho_max) {
+    return 3.0 * (double)nside * rho_max <= 16.0 ? 1 : 0;
+}
+// Waves of the pixel path that a compute unit holds at once (set by its registers).
+constexpr int pixel_waves_per_simd(bool f64) { return f64 ? 2 : 3; }
+constexpr int pixel_waves_per_cu(bool f64) { return 4 * pixel_waves_per_simd(f64); }
 
 // A tile: `count` consecutive samples of detector `det` starting at `begin`.
 struct Tile {

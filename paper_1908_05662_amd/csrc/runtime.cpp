@@ -367,7 +367,7 @@ void sidelobe_coef(const DetState &d, double coef[3]) {
 // The kernels' description of a detector (pointing and output offset left to
 // the caller).  sub: the detector's trained surrogate stands in for the
 // annulus, so the exact disc ends at its main radius.
-DetDesc make_desc(const DetState &d, bool sub) {
+DetDesc make_desc(const DetState &d, int64_t nside, bool sub) {
     DetDesc x{};
     const double rho_max = sub ? std::min(d.rho_max, d.sl->r_main) : d.rho_max;
     x.beam = d.beam;
@@ -383,6 +383,7 @@ DetDesc make_desc(const DetState &d, bool sub) {
     x.rot2z[1] = std::sin(2.0 * d.zeta) / (x.inv_h * x.inv_h);
     x.omega_max = 2.0 * std::sin(0.5 * rho_max) * std::sin(0.5 * rho_max);
     x.omega_min = 2.0 * std::sin(0.5 * d.rho_min) * std::sin(0.5 * d.rho_min);
+    x.pixel_rows = pisco::pixel_rows(nside, rho_max);
     for (int i = 0; i < 4; ++i) x.w[i] = d.w[i];
     x.beam_v = d.beam_v;
     x.wv = d.wv;
@@ -394,6 +395,12 @@ DetDesc make_desc(const DetState &d, bool sub) {
     x.has_inner = d.rho_min > 0.0 ? 1 : 0;
     x.order = nullptr;
     return x;
+}
+
+// Workgroups of a pixel-path launch: those its registers let run at the same time.
+int32_t pixel_groups(const pisco_ctx *c) {
+    const int32_t fit = pisco::pixel_waves_per_cu(c->sky_dtype == PISCO_F64) / c->wpg;
+    return std::min(c->gpc, std::max<int32_t>(1, fit)) * c->num_cu;
 }
 
 // Upload descriptors, classify their 64-sample groups (tile paths) and fill the
@@ -503,10 +510,14 @@ pisco_status build_plan(pisco_ctx *c, Plan &p, std::vector<DetDesc> &descs, cons
         if (!flag[g]) pix_samples += groups[g].count;
     // (under a memory budget at least 16 samples a tile: the block sizing allows
     // about 2 bytes of queues per sample)
-    const int64_t waves = std::max<int64_t>(1, (int64_t)c->gpc * c->num_cu * c->wpg);
+    const int64_t waves = std::max<int64_t>(1, (int64_t)pixel_groups(c) * c->wpg);
     const int64_t min_pspt = c->budget > 0 ? 16 : 1;
-    const int32_t pspt = (int32_t)std::min<int64_t>(
-        c->spt, std::max<int64_t>(min_pspt, (pix_samples + 2 * waves - 1) / (2 * waves)));
+    // (samples of small discs go four at a time: whole steps of four, and a tile a wave)
+    bool rows = true;
+    for (const DetDesc &x : descs) rows = rows && x.pixel_rows;
+    int64_t pspt64 = rows ? ((pix_samples + waves - 1) / waves + 3) / 4 * 4 : (pix_samples + 2 * waves - 1) / (2 * waves);
+    pspt64 = std::max<int64_t>(min_pspt, pspt64);
+    const int32_t pspt = (int32_t)std::min<int64_t>(c->spt, pspt64);
     std::vector<Tile> ttiles, ptiles;
     for (size_t g = 0; g < groups.size(); ++g) {
         if (flag[g]) {
@@ -599,7 +610,7 @@ pisco_status prepare_plan(pisco_ctx *c, Plan &p, int32_t det, int out_mode) {
         const DetState &d = c->dets[k];
         if (!det_ready(d)) continue;
         const bool sl = sub && d.sl_on && d.sl;
-        DetDesc x = make_desc(d, sl);
+        DetDesc x = make_desc(d, c->nside, sl);
         x.theta = d.th;
         x.phi = d.ph;
         x.psi = d.ps;
@@ -658,7 +669,7 @@ hipError_t enqueue(pisco_ctx *c, const Plan &p, void *out, int out_mode, hipStre
     }
     if (p.pq.ntiles > 0) {
         // no more workgroups than the pixel path has tiles for (a wave takes a tile)
-        const int64_t g = std::min<int64_t>((int64_t)c->gpc * c->num_cu, (p.pq.ntiles + c->wpg - 1) / c->wpg);
+        const int64_t g = std::min<int64_t>(pixel_groups(c), (p.pq.ntiles + c->wpg - 1) / c->wpg);
         e = pisco::launch_conv(make_args(c, p, out, out_mode, false), f64, c->wpg, (int)std::max<int64_t>(1, g), s);
         if (e != hipSuccess) return e;
     }
@@ -1196,7 +1207,7 @@ pisco_status convolve_blocks(pisco_ctx *c, int32_t det, int out_mode, void *out,
                 release();
                 return fail(c, PISCO_EDEVICE, "block upload failed: %s", hipGetErrorString(e));
             }
-            DetDesc x = make_desc(d, sl);
+            DetDesc x = make_desc(d, c->nside, sl);
             x.theta = th;
             x.phi = ph;
             x.psi = ps;
@@ -1637,7 +1648,7 @@ pisco_status pisco_convolve_static(pisco_ctx *c, int32_t det, int out_mode, void
     void *base = pisco::static_scratch(c->device);
     if (!base) return fail(c, PISCO_EDEVICE, "the plan array's device address is unknown");
     HIP_TRY(c, hipSetDevice(c->device));
-    DetDesc x = make_desc(d, sub);
+    DetDesc x = make_desc(d, c->nside, sub);
     x.theta = d.th;
     x.phi = d.ph;
     x.psi = d.ps;
