@@ -2185,11 +2185,11 @@ hipError_t launch_zero_counters(int32_t *counters, int n, hipStream_t s) {
 // waves share each tile (each does the tile's set-up again).  Measured at nside
 // 1024, 2 deg, one-grid beams, us for T tiles with 1 / 2 / 4 / 8 waves a tile: T = 64:
 // 602 / 306 / 171 / 118; 256: 632 / 318 / 183 / 133; 512: 644 / 336 / 213 / 209; 1024:
-// 715 / 371 / 347 / 397; 2048: 1088 / 633 / 675 / 797; 4096: 1269 / 1177 / 1288 / 1485;
-// 6144: 1790 / 1775 / 1924 / 2190 (256 compute units; four-channel beams, Stokes pickups
-// and 6 deg discs cross at the same places).
+// 715 / 371 / 347 / 397; 2048: 1088 / 633 / 675 / 797; and with 1 / 2 waves, 3072: 910 /
+// 889; 3584: 1074 / 1174; 4096: 1133 / 1215; 5120: 1465 / 1469 (256 compute units;
+// four-channel beams, Stokes pickups and 6 deg discs cross at the same places).
 void share_tiles(ConvArgs &a, int64_t n, int num_cu) {
-    const int w = n <= num_cu ? 8 : n <= 4 * num_cu ? 4 : n <= 20 * num_cu ? 2 : 0;
+    const int w = n <= num_cu ? 8 : n <= 4 * num_cu ? 4 : n <= 12 * num_cu ? 2 : 0;
     a.share_tiles = w;
     a.share_groups = w ? (int32_t)std::min<int64_t>(n, (int64_t)num_cu * (16 / w)) : 0;
 }

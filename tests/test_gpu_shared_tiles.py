@@ -2,7 +2,7 @@
 value may not depend on how many tiles the launch holds.  The terms are summed in
 FP32 in the same groups and only the FP64 sums of the groups are split, so TODs and
 pickups agree to one FP32 rounding (2^-23 of the value: two neighbouring floats),
-counts exactly; the two entry points agree throughout.  Streams of 1, 256, 257, 1024, 1025, 5120 and 5121 tiles (the ends of
+counts exactly; the two entry points agree throughout.  Streams of 1, 256, 257, 1024, 1025, 3072, 3073 and 5121 tiles (the ends of
 the 8-, 4- and 2-wave launches with 256 compute units), the last tile ragged."""
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ import pytest
 from gpu_helpers import say
 
 pytestmark = pytest.mark.gpu
-TILES = (1, 256, 257, 1024, 1025, 5120, 5121)
+TILES = (1, 256, 257, 1024, 1025, 3072, 3073, 5121)
 D2R = np.pi / 180
 
 
