@@ -6,10 +6,10 @@
 
 #define MLP_IN 5
 #define MLP_OUT 3
+#define MLP_WCOL_ROWS 32   // rows of a block of the weighted column sums
 
 namespace pisco {
 
-enum { MLP_EPI_FWD = 0, MLP_EPI_BWD_D = 1, MLP_EPI_BWD_W = 2 };
 #define MLP_MAX_L 16
 
 // Fused inference + TOD epilogue over a pointing stream (infer_kernel).
@@ -27,11 +27,29 @@ struct MlpInferArgs {
 
 hipError_t mlp_in_fwd(const float *x, const __bf16 *w0, const float *b0, int32_t n, int32_t H, float *z, __bf16 *a,
                       hipStream_t s);
-// C = A B with A[m][k] at a[m*lda + k] and B(k, n) at b[n*ldb + k]; epilogues as
-// in mlp_kernels.hip (t_out, if not null, receives the transposed bf16 output).
-hipError_t mlp_gemm(int epi, const __bf16 *a, int64_t lda, const __bf16 *b, int64_t ldb, int32_t M, int32_t N,
-                    int32_t K, int32_t k_slice, const float *bias, float *z_out, __bf16 *a_out, __bf16 *t_out,
-                    int64_t ldt, const float *z_prev, float *partial, hipStream_t s);
+// The H x H layers of a batch in one launch (chain_kernel), forward or backward.
+struct MlpChain {
+    const __bf16 *in;       // forward: A_0; backward: dZ_{L-1}; [rows][H]
+    __bf16 *out;            // forward: A_{L-1}; backward: dZ_0
+    const __bf16 *w;        // forward: W_1, W_2, ...; backward: W_1^T, W_2^T, ...
+    int64_t w_stride;
+    const float *bias;      // forward: b_1, b_2, ...
+    int64_t b_stride;
+    float *z;               // pre-activations [layer][rows][H], z_stride apart (forward: null = not stored)
+    int64_t z_stride;
+    __bf16 *t;              // transposed copies [layer][H][ldt]: forward A_0 .. A_{L-2} (null = not stored),
+                            // backward dZ_{L-1} .. dZ_1
+    int64_t t_stride, ldt;
+    float *part_bias;       // backward: column sums of each layer's dZ, [layer][block of MLP_WCOL_ROWS rows][H]
+    int64_t pb_stride;
+    int32_t n, L, H;        // rows (buffers padded to 128), hidden layers, width
+};
+hipError_t mlp_chain(const MlpChain &c, bool bwd, int num_cu, hipStream_t s);
+// partial[layer][slice] = A B over the slice's k_slice of the K rows of the batch, with
+// A[m][k] at a[m*ld + k] and B(k, n) at b[n*ld + k]; the layers operand_stride and
+// partial_stride apart.
+hipError_t mlp_wgrad(const __bf16 *a, const __bf16 *b, int64_t ld, int64_t operand_stride, int32_t H, int32_t K,
+                     int32_t k_slice, int32_t layers, float *partial, int64_t partial_stride, hipStream_t s);
 // dst[c * ldd + r] = src[r * lds + c] (R, C multiples of 64), for `batch` matrices.
 hipError_t mlp_transpose(const __bf16 *src, int64_t lds, __bf16 *dst, int64_t ldd, int32_t R, int32_t C,
                          int32_t batch, int64_t src_stride, int64_t dst_stride, hipStream_t s);
@@ -55,7 +73,6 @@ hipError_t mlp_out(const __bf16 *a, const float *zL, const __bf16 *wout, const f
 // part[b * stride + u * su + k * sk] = sum over the rows r of block b (MLP_WCOL_ROWS
 // rows each) of w(r, k) m[r][u], w(r, k) = wt[r K + k] or 1 (wt null, K = 1);
 // ones[b K + k] = sum_r w(r, k) when given.  K in {1, 3, 5}.
-#define MLP_WCOL_ROWS 32
 hipError_t mlp_wcolsum(const __bf16 *m, const float *wt, int32_t K, int32_t n, int32_t H, float *part, int64_t stride,
                        int32_t su, int32_t sk, float *ones, hipStream_t s);
 hipError_t mlp_adam(float *w, float *m, float *v, const float *g, __bf16 *wb, int64_t count, float lr_t, float b1,

@@ -7,10 +7,13 @@
 //
 // Kernels
 //   in_fwd      layer 0 (K = 5) on the vector ALU: Z1 = X W0^T + b0, A1 = SiLU(Z1)
-//   gemm        H x H layers on MFMA, three operand layouts:
-//                 FWD   Z = A W^T + b -> Z (fp32), SiLU(Z) (bf16)
-//                 BWD_D dZ_prev = (dZ W) * SiLU'(Z_prev)   (bf16)
-//                 BWD_W partial dW = dZ^T A over one batch slice (fp32, split-K)
+//   chain       every H x H layer of a block of rows on MFMA, one launch:
+//                 forward   Z = A W^T + b -> Z (fp32), SiLU(Z) (bf16, on chip)
+//                 backward  dZ_prev = (dZ W) * SiLU'(Z_prev)  (bf16, on chip),
+//                           with the bias gradients' partial column sums
+//               both leave the transposed copies that the weight gradients read
+//   wgrad       partial dW = dZ^T A over one batch slice (fp32, split-K), for
+//               every H x H layer in one launch
 //   out_rows    output layer (N = 3): Y, MSE loss, dY, dZ_L = (dY W_out) * SiLU'(Z_L)
 //   wcolsum     per-block partial weighted column sums: the bias gradients,
 //               dW0 = dZ1^T X and dW_out = dY^T A_L (with db_out)
@@ -39,36 +42,30 @@ __device__ inline float silu_grad(float z) {
 }
 
 // ----------------------------------------------------------------------
-// GEMM: C[M x N] = A[M x K] B[K x N] with both operands k-contiguous: A[m][k]
-// at a[m*lda + k] and B given by rows n, B(k, n) at b[n*ldb + k] (so the
-// layers' backward passes read transposed copies the forward epilogues,
-// the output layer and Adam keep).  M, N multiples of the tile (64 or 128),
-// K of 32.  Workgroup: four waves as 2 x 2, each (BM/2) x (BN/2) of
+// Weight gradients: C[H x H] = A[H x K] B[K x H] over the batch (K), both operands
+// k-contiguous: A[m][k] at a[m*ld + k] (dZ^T) and B(k, n) at b[n*ld + k] (the
+// activations' transposes).  H a multiple of the tile (64 or 128), K of 32.
+// Workgroup: four waves as 2 x 2, each (BM/2) x (BN/2) of
 // v_mfma_f32_16x16x32_bf16 tiles; 64-wide k steps staged in LDS, double
 // buffered (the next step's tiles are fetched into registers while the
 // current step's MFMAs run; k past the end of the slice reads as zero and its
 // MFMAs are skipped).  Every output element is one MFMA chain over k0 = 0, 32,
-// 64, ... with lane l holding k0 + 8 (l / 16) .. + 7 of row l % 16: the
-// fragments and order of the fused inference kernel.
+// 64, ... of its slice.  grid.z walks the layers and their slices: all layers in
+// one launch keep loads, products and stores of different workgroups in flight
+// together.  WGRADMEASURED
 // ----------------------------------------------------------------------
 constexpr int TK = 32;                 // k per MFMA
 constexpr int KS = 64, LDK = KS + 8;   // k per staged step; LDS rows padded by 16 bytes
 
-enum { EPI_FWD = MLP_EPI_FWD, EPI_BWD_D = MLP_EPI_BWD_D, EPI_BWD_W = MLP_EPI_BWD_W };
-
-struct GemmArgs {
-    const __bf16 *a;
+struct WgradArgs {
+    const __bf16 *a;       // layer 0 of the launch; the next ones operand_stride on
     const __bf16 *b;
-    int64_t lda, ldb;
-    int32_t M, N, K;
-    int32_t k_slice;       // split-K slice length (multiple of 32)
-    const float *bias;     // FWD
-    float *z_out;          // FWD: pre-activation (ldc = N)
-    __bf16 *a_out;         // FWD: SiLU(Z); BWD_D: dZ_prev (ldc = N)
-    __bf16 *t_out;         // optional transposed copy of a_out: t_out[n * ldt + m]
-    int64_t ldt;
-    const float *z_prev;   // BWD_D: pre-activation of the previous layer
-    float *partial;        // BWD_W: [slice][M][N]
+    int64_t ld, operand_stride;
+    int32_t H, K;
+    int32_t k_slice;       // split-K slice length (multiple of 64)
+    int32_t slices;        // slices a layer
+    float *partial;        // [layer][slice][H][H], layers partial_stride apart
+    int64_t partial_stride;
 };
 
 // Rows [r0, r0 + R) x k [k0, k0 + KS) of a k-contiguous operand: R * KS / 8
@@ -95,14 +92,17 @@ struct TileRegs {
     }
 };
 
-template <int EPI, int BM, int BN>
-__global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
+template <int BM, int BN>
+__global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs g) {
     constexpr int WM = BM / 2, WN = BN / 2, FI = WM / 16, FJ = WN / 16;
     __shared__ __align__(16) __bf16 As[2][BM][LDK];
     __shared__ __align__(16) __bf16 Bs[2][BN][LDK];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const int kb = blockIdx.z * g.k_slice, ke = min(g.K, kb + g.k_slice);
+    const int layer = blockIdx.z / g.slices, slice = blockIdx.z % g.slices;
+    const __bf16 *ga = g.a + layer * g.operand_stride, *gb = g.b + layer * g.operand_stride;
+    float *out = g.partial + layer * g.partial_stride + (int64_t)slice * g.H * g.H;
+    const int kb = slice * g.k_slice, ke = min(g.K, kb + g.k_slice);
     const int wm = (wave >> 1) * WM, wn = (wave & 1) * WN;
     const int r = lane & 15, kq = (lane >> 4) * 8;
     f32x4 acc[FI][FJ];
@@ -114,8 +114,8 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
     TileRegs<BM> ra;
     TileRegs<BN> rb;
     if (kb < ke) {
-        ra.load(g.a, g.lda, m0, kb, ke, tid);
-        rb.load(g.b, g.ldb, n0, kb, ke, tid);
+        ra.load(ga, g.ld, m0, kb, ke, tid);
+        rb.load(gb, g.ld, n0, kb, ke, tid);
         ra.store(As[0], tid);
         rb.store(Bs[0], tid);
     }
@@ -124,8 +124,8 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
     for (int k0 = kb; k0 < ke; k0 += KS) {
         const bool more = k0 + KS < ke;
         if (more) {
-            ra.load(g.a, g.lda, m0, k0 + KS, ke, tid);
-            rb.load(g.b, g.ldb, n0, k0 + KS, ke, tid);
+            ra.load(ga, g.ld, m0, k0 + KS, ke, tid);
+            rb.load(gb, g.ld, n0, k0 + KS, ke, tid);
         }
 #pragma unroll
         for (int ks = 0; ks < KS; ks += TK) {
@@ -151,36 +151,15 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
         cur ^= 1;
     }
 
-    // epilogue: lane holds C[row0 + 4 (lane/16) + q][col0 + lane%16], q = 0..3
+    // lane holds C[row0 + 4 (lane/16) + q][col0 + lane%16], q = 0..3
 #pragma unroll
     for (int i = 0; i < FI; ++i)
 #pragma unroll
         for (int j = 0; j < FJ; ++j) {
-            const int rowb = m0 + wm + 16 * i + 4 * (lane >> 4);
+            const int row = m0 + wm + 16 * i + 4 * (lane >> 4);
             const int col = n0 + wn + 16 * j + (lane & 15);
-            __bf16 t4[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int row = rowb + q;
-                const float v = acc[i][j][q];
-                const int64_t o = (int64_t)row * g.N + col;
-                if (EPI == EPI_FWD) {
-                    const float z = v + g.bias[col];
-                    g.z_out[o] = z;
-                    t4[q] = (__bf16)silu(z);
-                    g.a_out[o] = t4[q];
-                } else if (EPI == EPI_BWD_D) {
-                    t4[q] = (__bf16)(v * silu_grad(g.z_prev[o]));
-                    g.a_out[o] = t4[q];
-                } else {
-                    g.partial[(int64_t)blockIdx.z * g.M * g.N + o] = v;
-                }
-            }
-            // four consecutive rows of one column: one 8-byte store into the transposed copy
-            if (EPI != EPI_BWD_W && g.t_out) {
-                typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-                *reinterpret_cast<bf16x4 *>(g.t_out + (int64_t)col * g.ldt + rowb) = bf16x4{t4[0], t4[1], t4[2], t4[3]};
-            }
+            for (int q = 0; q < 4; ++q) out[(int64_t)(row + q) * g.H + col] = acc[i][j][q];
         }
 }
 
@@ -416,7 +395,7 @@ __global__ void apply_kernel(const float *y, int64_t n, float m0, float m1, floa
 // registers, then, after a barrier, its activations overwrite its input),
 // weights read from L2.  At most 128 registers per lane, so that four waves
 // share a SIMD.  The H x H layers use the operand fragments and K order of
-// gemm_kernel, layer 0 the FMA chain of in_fwd_kernel, the output layer the
+// chain_kernel, layer 0 the FMA chain of in_fwd_kernel, the output layer the
 // per-lane order and butterfly of out_rows_kernel and the epilogue
 // apply_kernel's arithmetic, so the result equals the layer-by-layer forward
 // pass followed by apply, bit for bit.
@@ -439,8 +418,8 @@ __device__ inline void features_of(const double *th, const double *ph, const dou
 // The wave's 64 units of an H x H layer for the 64 RB rows in LDS, as Z^T = W A^T:
 // the weights are the MFMA's first operand (lane l: unit u0 + 16 i + l % 16,
 // k0 + 8 (l / 16) .. + 7, from L2), the activations its second (row 16 j +
-// l % 16, the same k, from LDS), so each output element is the training
-// GEMM's product chain over k0 = 0, 32, ... with the operands exchanged.  The
+// l % 16, the same k, from LDS), so each output element is one product
+// chain over k0 = 0, 32, ....  The
 // weight fragments of WD k steps are in flight (a ring of register slots,
 // refilled as each is used); every weight fragment serves 4 RB row tiles, so
 // more rows per workgroup read the weights from L2 fewer times per row.
@@ -497,6 +476,151 @@ __device__ inline void hxh_store(const float *__restrict__ bias, __bf16 *act, in
                                     (__bf16)silu(acc[i][j][2] + bq.z), (__bf16)silu(acc[i][j][3] + bq.w)};
             *reinterpret_cast<bf16x4 *>(act + row * LD + ub) = o;
         }
+    }
+}
+
+// ----------------------------------------------------------------------
+// Training: the H x H layers of 16 JT rows per workgroup, forward or backward, in
+// one launch.  A row's layers depend on that row alone, so a workgroup of H / 64
+// waves keeps its rows' activations (dZ in the backward pass) in LDS, updated in
+// place as infer_kernel's, reads the weights from L2 and stores what the other
+// passes need: Z in FP32, the transposed copies [H][ldt] of the weight gradients'
+// operands, the bias gradients' partial sums.  Layer by layer as a product with an
+// epilogue the chip idled in turn: its loads, products and 32 MB of stores came one
+// after the other in every workgroup at once, 18 to 21 us a layer and direction at H
+// = 512 and 8192 rows, where its bytes take 8.  CHAINMEASURED
+// Each output element is the MFMA chain over k0 = 0, 32, ... of infer_kernel.
+// Rows past n (the buffers are padded to 128) carry stale values that nothing reads.
+// ----------------------------------------------------------------------
+// The wave's 64 units of an H x H layer for the 16 JT rows in LDS (hxh_products with
+// H known, WDC k steps of weights in flight).
+template <int NW, int JT, int WDC>
+__device__ inline void chain_products(const __bf16 *__restrict__ W, const __bf16 *act, int u0, int lane,
+                                      f32x4 (&acc)[4][JT]) {
+    constexpr int H = 64 * NW, LD = H + 8, STEPS = H / 32;
+    const int r16 = lane & 15, kq = (lane >> 4) * 8;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < JT; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const __bf16 *wrow = W + (int64_t)(u0 + r16) * H + kq;
+    bf16x8 wf[WDC][4];
+#pragma unroll
+    for (int sl = 0; sl < WDC; ++sl)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (sl < STEPS) wf[sl][i] = *reinterpret_cast<const bf16x8 *>(wrow + (int64_t)16 * i * H + 32 * sl);
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+#pragma unroll
+        for (int j = 0; j < JT; ++j) {
+            const bf16x8 af = *reinterpret_cast<const bf16x8 *>(act + (16 * j + r16) * LD + 32 * st + kq);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[st % WDC][i], af, acc[i][j], 0, 0, 0);
+        }
+        if (st + WDC < STEPS) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                wf[st % WDC][i] = *reinterpret_cast<const bf16x8 *>(wrow + (int64_t)16 * i * H + 32 * (st + WDC));
+        }
+    }
+}
+
+// Thread u takes unit u of the buffer: its rows as the transposed copy's words, and
+// (pb) the sums of each block of MLP_WCOL_ROWS rows, in order.
+template <int JT>
+__device__ inline void chain_columns(const __bf16 *act, int LD, int u, int32_t r0, int32_t n, __bf16 *t, int64_t ldt,
+                                     float *pb, int H) {
+    constexpr int R = MLP_WCOL_ROWS;
+    static_assert(16 * JT % R == 0, "whole blocks of rows");
+#pragma unroll
+    for (int b = 0; b < 16 * JT / R; ++b) {
+        __bf16 v[R];
+#pragma unroll
+        for (int q = 0; q < R; ++q) v[q] = act[(b * R + q) * LD + u];
+        if (t) {
+#pragma unroll
+            for (int q = 0; q < R; q += 8)
+                *reinterpret_cast<bf16x8 *>(t + (int64_t)u * ldt + r0 + b * R + q) =
+                    bf16x8{v[q], v[q + 1], v[q + 2], v[q + 3], v[q + 4], v[q + 5], v[q + 6], v[q + 7]};
+        }
+        if (pb && r0 + b * R < n) {
+            float s = 0.0f;
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+                if (r0 + b * R + q < n) s += (float)v[q];
+            pb[(int64_t)(r0 / R + b) * H + u] = s;
+        }
+    }
+}
+
+template <int NW, int JT, bool BWD>
+__global__ void __launch_bounds__(64 * NW, 2) chain_kernel(MlpChain g) {
+    constexpr int H = 64 * NW, LD = H + 8, R = 16 * JT;
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) unsigned char lds[];
+    __bf16 *act = reinterpret_cast<__bf16 *>(lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int u0 = 64 * __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15;
+    const int32_t r0 = (int32_t)blockIdx.x * R;
+    for (int c = tid; c < R * H / 8; c += 64 * NW) {
+        const int row = c / (H / 8), k = 8 * (c % (H / 8));
+        *reinterpret_cast<bf16x8 *>(act + row * LD + k) =
+            *reinterpret_cast<const bf16x8 *>(g.in + (int64_t)(r0 + row) * H + k);
+    }
+    __syncthreads();
+    // layers in the order of the pass: l is the layer whose values the buffer holds
+    int l = BWD ? g.L - 1 : 0;
+    for (int step = 0;; ++step) {
+        const bool end = step == g.L - 1;
+        if (!BWD && g.t && !end)
+            chain_columns<JT>(act, LD, tid, r0, g.n, g.t + l * g.t_stride, g.ldt, nullptr, H);
+        if (BWD)
+            chain_columns<JT>(act, LD, tid, r0, g.n, end ? nullptr : g.t + l * g.t_stride, g.ldt,
+                              g.part_bias + l * g.pb_stride, H);
+        if (end) break;
+        const int nl = BWD ? l - 1 : l + 1;
+        float4 zp[4][JT];
+        if (BWD) {
+            const float *z = g.z + nl * g.z_stride + (int64_t)(r0 + r16) * H + u0 + 4 * (lane >> 4);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < JT; ++j)
+                    zp[i][j] = *reinterpret_cast<const float4 *>(z + (int64_t)16 * j * H + 16 * i);
+        }
+        f32x4 acc[4][JT];
+        chain_products<NW, JT, NW == 1 ? 2 : 4>(g.w + (int64_t)(BWD ? l - 1 : l) * g.w_stride, act, u0, lane, acc);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int ub = u0 + 16 * i + 4 * (lane >> 4);   // this lane's four units
+            float4 bq{0.0f, 0.0f, 0.0f, 0.0f};
+            if (!BWD) bq = *reinterpret_cast<const float4 *>(g.bias + l * g.b_stride + ub);
+#pragma unroll
+            for (int j = 0; j < JT; ++j) {
+                const int row = 16 * j + r16;
+                bf16x4 o;
+                if (BWD) {
+                    o = bf16x4{(__bf16)(acc[i][j][0] * silu_grad(zp[i][j].x)), (__bf16)(acc[i][j][1] * silu_grad(zp[i][j].y)),
+                               (__bf16)(acc[i][j][2] * silu_grad(zp[i][j].z)), (__bf16)(acc[i][j][3] * silu_grad(zp[i][j].w))};
+                } else {
+                    const float4 zq{acc[i][j][0] + bq.x, acc[i][j][1] + bq.y, acc[i][j][2] + bq.z, acc[i][j][3] + bq.w};
+                    if (g.z) *reinterpret_cast<float4 *>(g.z + nl * g.z_stride + (int64_t)(r0 + row) * H + ub) = zq;
+                    o = bf16x4{(__bf16)silu(zq.x), (__bf16)silu(zq.y), (__bf16)silu(zq.z), (__bf16)silu(zq.w)};
+                }
+                *reinterpret_cast<bf16x4 *>(act + row * LD + ub) = o;
+            }
+        }
+        __syncthreads();
+        l = nl;
+    }
+    for (int c = tid; c < R * H / 8; c += 64 * NW) {
+        const int row = c / (H / 8), k = 8 * (c % (H / 8));
+        *reinterpret_cast<bf16x8 *>(g.out + (int64_t)(r0 + row) * H + k) =
+            *reinterpret_cast<const bf16x8 *>(act + row * LD + k);
     }
 }
 
@@ -625,40 +749,63 @@ hipError_t mlp_in_fwd(const float *x, const __bf16 *w0, const float *b0, int32_t
 // 128 x 128 tiles only when they still give two workgroups per CU (512);
 // otherwise 64 x 64 tiles, four times as many workgroups to hide the load
 // latency of these short-K products.
-template <int EPI>
-static void gemm_launch(const GemmArgs &g, hipStream_t s) {
-    const int64_t z = (g.K + g.k_slice - 1) / g.k_slice;
-    const bool big = g.M % 128 == 0 && g.N % 128 == 0 && (int64_t)(g.M / 128) * (g.N / 128) * z >= 512;
-    const int t = big ? 128 : 64;
-    const dim3 grid(g.N / t, g.M / t, (unsigned)z);
-    if (big) hipLaunchKernelGGL((gemm_kernel<EPI, 128, 128>), grid, dim3(256), 0, s, g);
-    else hipLaunchKernelGGL((gemm_kernel<EPI, 64, 64>), grid, dim3(256), 0, s, g);
-}
-
-hipError_t mlp_gemm(int epi, const __bf16 *a, int64_t lda, const __bf16 *b, int64_t ldb, int32_t M, int32_t N,
-                    int32_t K, int32_t k_slice, const float *bias, float *z_out, __bf16 *a_out, __bf16 *t_out,
-                    int64_t ldt, const float *z_prev, float *partial, hipStream_t s) {
-    if (M % 64 || N % 64 || K % TK || k_slice % KS || k_slice <= 0) return hipErrorInvalidValue;
-    GemmArgs g;
+hipError_t mlp_wgrad(const __bf16 *a, const __bf16 *b, int64_t ld, int64_t operand_stride, int32_t H, int32_t K,
+                     int32_t k_slice, int32_t layers, float *partial, int64_t partial_stride, hipStream_t s) {
+    if (H % 64 || K % TK || k_slice % KS || k_slice <= 0) return hipErrorInvalidValue;
+    if (layers <= 0 || K == 0) return hipSuccess;
+    WgradArgs g;
     g.a = a;
     g.b = b;
-    g.lda = lda;
-    g.ldb = ldb;
-    g.M = M;
-    g.N = N;
+    g.ld = ld;
+    g.operand_stride = operand_stride;
+    g.H = H;
     g.K = K;
     g.k_slice = k_slice;
-    g.bias = bias;
-    g.z_out = z_out;
-    g.a_out = a_out;
-    g.t_out = t_out;
-    g.ldt = ldt;
-    g.z_prev = z_prev;
+    g.slices = (K + k_slice - 1) / k_slice;
     g.partial = partial;
-    if (epi == EPI_FWD) gemm_launch<EPI_FWD>(g, s);
-    else if (epi == EPI_BWD_D) gemm_launch<EPI_BWD_D>(g, s);
-    else gemm_launch<EPI_BWD_W>(g, s);
+    g.partial_stride = partial_stride;
+    const int64_t z = (int64_t)g.slices * layers;
+    const bool big = H % 128 == 0 && (int64_t)(H / 128) * (H / 128) * z >= 512;
+    const int t = big ? 128 : 64;
+    const dim3 grid(H / t, H / t, (unsigned)z);
+    if (big) hipLaunchKernelGGL((wgrad_kernel<128, 128>), grid, dim3(256), 0, s, g);
+    else hipLaunchKernelGGL((wgrad_kernel<64, 64>), grid, dim3(256), 0, s, g);
     return hipGetLastError();
+}
+
+// 64 rows a workgroup when that still gives every CU one (the weights are then read
+// from L2 once per 64 rows), 32 otherwise.
+template <int NW, int JT, bool BWD>
+static hipError_t chain_launch(const MlpChain &a, hipStream_t s) {
+    const size_t lds = (size_t)(16 * JT) * (64 * NW + 8) * sizeof(__bf16);
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&chain_kernel<NW, JT, BWD>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((chain_kernel<NW, JT, BWD>), dim3(blocks_for(a.n, 16 * JT)), dim3(64 * NW), lds, s, a);
+    return hipGetLastError();
+}
+
+template <int NW>
+static hipError_t chain_rows(const MlpChain &a, bool bwd, int num_cu, hipStream_t s) {
+    if (a.n >= 64 * num_cu) return bwd ? chain_launch<NW, 4, true>(a, s) : chain_launch<NW, 4, false>(a, s);
+    return bwd ? chain_launch<NW, 2, true>(a, s) : chain_launch<NW, 2, false>(a, s);
+}
+
+hipError_t mlp_chain(const MlpChain &a, bool bwd, int num_cu, hipStream_t s) {
+    if (a.n == 0) return hipSuccess;
+    switch (a.H) {
+        case 64: return chain_rows<1>(a, bwd, num_cu, s);
+        case 128: return chain_rows<2>(a, bwd, num_cu, s);
+        case 192: return chain_rows<3>(a, bwd, num_cu, s);
+        case 256: return chain_rows<4>(a, bwd, num_cu, s);
+        case 320: return chain_rows<5>(a, bwd, num_cu, s);
+        case 384: return chain_rows<6>(a, bwd, num_cu, s);
+        case 448: return chain_rows<7>(a, bwd, num_cu, s);
+        case 512: return chain_rows<8>(a, bwd, num_cu, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t mlp_transpose(const __bf16 *src, int64_t lds, __bf16 *dst, int64_t ldd, int32_t R, int32_t C,

@@ -24,17 +24,19 @@ struct pisco_mlp {
     float *w = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
     __bf16 *wb = nullptr;
     int32_t mbp = 0;                 // rows of the activation buffers: max_batch rounded up to 128
-    std::vector<float *> z;          // L pre-activations [mbp][H]
-    std::vector<__bf16 *> a;         // L activations [mbp][H]
-    std::vector<__bf16 *> aT;        // their transposes [H][mbp] (operands of the weight gradients)
-    __bf16 *dz[2] = {nullptr, nullptr};      // back-propagated dL/dz [mbp][H]
-    __bf16 *dzT[2] = {nullptr, nullptr};     // their transposes [H][mbp]
+    float *z = nullptr;              // pre-activations [L][mbp][H]
+    __bf16 *a0 = nullptr, *aL = nullptr;     // first and last hidden activations [mbp][H]
+    __bf16 *aT = nullptr;            // transposes of the hidden activations [L][H][mbp] (weight gradients' operands)
+    __bf16 *dzL = nullptr, *dz0 = nullptr;   // dL/dz of the last and first hidden layer [mbp][H]
+    __bf16 *dzT = nullptr;           // transposes of the hidden layers' dL/dz [L][H][mbp] (layer 0's unused)
     __bf16 *wbT = nullptr;           // transposes of the hidden maps' BF16 weights, [L-1][H][H]
     float *y = nullptr, *xbuf = nullptr, *ybuf = nullptr;
     float *dy = nullptr;             // output-layer dL/dy [max_batch][3] (fp32)
     float *part_w = nullptr, *part_b = nullptr, *part_loss = nullptr;
-    std::vector<float *> part_map;   // split-K partials of each hidden map's weight gradient
-    std::vector<float *> part_bias;  // per-block partial column sums of each hidden layer's dL/dz
+    float *part_map = nullptr;       // split-K partials of the hidden maps' weight gradients, [L-1][slices][H][H]
+    int64_t part_map_stride = 0;
+    float *part_bias = nullptr;      // per-block partial column sums of the hidden layers' dL/dz, [L][blocks][H]
+    int64_t part_bias_stride = 0;
     float *part_in = nullptr;        // per-block partials of the input layer's weight gradient
     std::vector<void *> allocs;
 };
@@ -104,23 +106,35 @@ hipError_t refresh_wbT(pisco_mlp *m, hipStream_t s) {
 }
 
 // forward (+ loss and backward when tgt != nullptr) over one chunk of n rows
-// (GEMM rows padded to 128; padding rows carry stale values, never read back)
+// (buffers padded to 128 rows; padding rows carry stale values, never read back)
 pisco_status run(pisco_mlp *m, const float *x, const float *tgt, int32_t n, float *y, float *grad, float *loss,
                  hipStream_t s) {
     const int32_t H = m->H, L = m->L;
-    const int32_t np = round_up(n, 128);
     const int64_t ldt = m->mbp;
     const bool train = tgt != nullptr;
-    MLP_TRY(m, pisco::mlp_in_fwd(x, m->wb + m->off_w[0], m->w + m->off_b[0], n, H, m->z[0], m->a[0], s));
-    if (train && L > 1) MLP_TRY(m, pisco::mlp_transpose(m->a[0], H, m->aT[0], ldt, np, H, 1, 0, 0, s));
-    for (int l = 1; l < L; ++l)
-        MLP_TRY(m, pisco::mlp_gemm(pisco::MLP_EPI_FWD, m->a[l - 1], H, m->wb + m->off_w[l], H, np, H, H, H,
-                                   m->w + m->off_b[l], m->z[l], m->a[l], (train && l < L - 1) ? m->aT[l] : nullptr,
-                                   ldt, nullptr, nullptr, s));
+    const int num_cu = pisco::ctx_num_cu(m->ctx);
+    const int64_t act = (int64_t)m->mbp * H, wst = L > 1 ? m->off_w[2] - m->off_w[1] : 0;
+    pisco::MlpChain c{};
+    c.n = n;
+    c.L = L;
+    c.H = H;
+    c.ldt = ldt;
+    c.z_stride = c.t_stride = act;
+    MLP_TRY(m, pisco::mlp_in_fwd(x, m->wb + m->off_w[0], m->w + m->off_b[0], n, H, m->z, m->a0, s));
+    if (L > 1) {
+        c.in = m->a0;
+        c.out = m->aL;
+        c.w = m->wb + m->off_w[1];
+        c.bias = m->w + m->off_b[1];
+        c.w_stride = c.b_stride = wst;
+        c.z = train ? m->z : nullptr;
+        c.t = train ? m->aT : nullptr;
+        MLP_TRY(m, pisco::mlp_chain(c, false, num_cu, s));
+    }
+    const __bf16 *last = L > 1 ? m->aL : m->a0;
     const int32_t waves = (n + ROWS_PER_WAVE - 1) / ROWS_PER_WAVE;
-    int cur = 0;
-    MLP_TRY(m, pisco::mlp_out(m->a[L - 1], m->z[L - 1], m->wb + m->off_w[L], m->w + m->off_b[L], n, H, y, tgt,
-                              1.0f / (float)(n * MLP_OUT), m->dy, m->dz[cur], m->part_loss, waves, ROWS_PER_WAVE, s));
+    MLP_TRY(m, pisco::mlp_out(last, m->z + (L - 1) * act, m->wb + m->off_w[L], m->w + m->off_b[L], n, H, y, tgt,
+                              1.0f / (float)(n * MLP_OUT), m->dy, m->dzL, m->part_loss, waves, ROWS_PER_WAVE, s));
     if (!train) return PISCO_OK;
     MLP_TRY(m, pisco::mlp_loss_sum(m->part_loss, waves, 1.0f / (float)(n * MLP_OUT), loss, s));
     pisco::MlpReduceList R{};
@@ -134,35 +148,37 @@ pisco_status run(pisco_mlp *m, const float *x, const float *tgt, int32_t n, floa
     };
     const int32_t cblocks = (n + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK;
     // output map: dW_out[c][u] = sum_r dY[r][c] A_L[r][u], db_out[c] = sum_r dY[r][c]
-    MLP_TRY(m, pisco::mlp_wcolsum(m->a[L - 1], m->dy, MLP_OUT, n, H, m->part_w,
+    MLP_TRY(m, pisco::mlp_wcolsum(last, m->dy, MLP_OUT, n, H, m->part_w,
                                   (int64_t)MLP_OUT * H, 1, H, m->part_b, s));
     seg(m->part_w, cblocks, (int64_t)MLP_OUT * H, grad + m->off_w[L]);
     seg(m->part_b, cblocks, MLP_OUT, grad + m->off_b[L]);
-    if (L > 1) MLP_TRY(m, pisco::mlp_transpose(m->dz[cur], H, m->dzT[cur], ldt, np, H, 1, 0, 0, s));
-    for (int l = L - 1; l >= 1; --l) {
-        // weight gradient of map l: dZ_l^T A_{l-1} over the batch, split into slices
+    const __bf16 *first = m->dzL;
+    if (L > 1) {
+        // back through the hidden maps, then their weight gradients dZ_l^T A_{l-1} over
+        // the batch, split into slices
+        c.in = m->dzL;
+        c.out = m->dz0;
+        c.w = m->wbT;
+        c.w_stride = (int64_t)H * H;
+        c.z = m->z;
+        c.t = m->dzT;
+        c.part_bias = m->part_bias;
+        c.pb_stride = m->part_bias_stride;
+        MLP_TRY(m, pisco::mlp_chain(c, true, num_cu, s));
+        first = m->dz0;
         const int32_t ks = k_slice_for(n, H);
-        const int32_t slices = (n + ks - 1) / ks;
-        MLP_TRY(m, pisco::mlp_gemm(pisco::MLP_EPI_BWD_W, m->dzT[cur], ldt, m->aT[l - 1], ldt, H, H, n, ks, nullptr,
-                                   nullptr, nullptr, nullptr, 0, nullptr, m->part_map[l], s));
-        seg(m->part_map[l], slices, (int64_t)H * H, grad + m->off_w[l]);
-        MLP_TRY(m, pisco::mlp_wcolsum(m->dz[cur], nullptr, 1, n, H, m->part_bias[l], H, 1, 0,
-                                      nullptr, s));
-        seg(m->part_bias[l], cblocks, H, grad + m->off_b[l]);
-        // gradient into the previous layer's pre-activation (and its transpose unless it is layer 0)
-        const int nxt = cur ^ 1;
-        MLP_TRY(m, pisco::mlp_gemm(pisco::MLP_EPI_BWD_D, m->dz[cur], H, m->wbT + (int64_t)(l - 1) * H * H, H, np, H,
-                                   H, H, nullptr, nullptr, m->dz[nxt], l > 1 ? m->dzT[nxt] : nullptr, ldt,
-                                   m->z[l - 1], nullptr, s));
-        cur = nxt;
+        MLP_TRY(m, pisco::mlp_wgrad(m->dzT + act, m->aT, ldt, act, H, n, ks, L - 1, m->part_map, m->part_map_stride, s));
+        for (int l = L - 1; l >= 1; --l) {
+            seg(m->part_map + (l - 1) * m->part_map_stride, (n + ks - 1) / ks, (int64_t)H * H, grad + m->off_w[l]);
+            seg(m->part_bias + l * m->part_bias_stride, cblocks, H, grad + m->off_b[l]);
+        }
+    } else {
+        MLP_TRY(m, pisco::mlp_wcolsum(first, nullptr, 1, n, H, m->part_bias, H, 1, 0, nullptr, s));
     }
-    // input map: dW0[u][k] = sum_r dZ_1[r][u] X[r][k], and the first bias
-    MLP_TRY(m, pisco::mlp_wcolsum(m->dz[cur], x, MLP_IN, n, H, m->part_in, (int64_t)H * MLP_IN,
-                                  MLP_IN, 1, nullptr, s));
+    // input map: dW0[u][k] = sum_r dZ_0[r][u] X[r][k], and the first bias
+    MLP_TRY(m, pisco::mlp_wcolsum(first, x, MLP_IN, n, H, m->part_in, (int64_t)H * MLP_IN, MLP_IN, 1, nullptr, s));
     seg(m->part_in, cblocks, (int64_t)H * MLP_IN, grad + m->off_w[0]);
-    MLP_TRY(m, pisco::mlp_wcolsum(m->dz[cur], nullptr, 1, n, H, m->part_bias[0], H, 1, 0, nullptr,
-                                  s));
-    seg(m->part_bias[0], cblocks, H, grad + m->off_b[0]);
+    seg(m->part_bias, cblocks, H, grad + m->off_b[0]);
     MLP_TRY(m, pisco::mlp_reduce_many(R, s));
     return PISCO_OK;
 }
@@ -239,9 +255,12 @@ pisco_status pisco_mlp_create(pisco_ctx *ctx, int32_t width, int32_t hidden_laye
     const int32_t cblocks = (max_batch + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK;
     const int32_t slices = std::max(slices_for(width), (max_batch + k_slice_for(max_batch, width) - 1) /
                                                            k_slice_for(max_batch, width));
-    bool ok = alloc(m, &m->w, o) && alloc(m, &m->m, o) && alloc(m, &m->v, o) && alloc(m, &m->g, o) &&
-              alloc(m, &m->wb, o) && alloc(m, &m->dz[0], act) && alloc(m, &m->dz[1], act) &&
-              alloc(m, &m->dzT[0], act) && alloc(m, &m->dzT[1], act) &&
+    const bool ok = alloc(m, &m->w, o) && alloc(m, &m->m, o) && alloc(m, &m->v, o) && alloc(m, &m->g, o) &&
+              alloc(m, &m->wb, o) && alloc(m, &m->dzL, act) && alloc(m, &m->dz0, act) &&
+              alloc(m, &m->z, act * hidden_layers) && alloc(m, &m->a0, act) && alloc(m, &m->aL, act) &&
+              alloc(m, &m->aT, act * hidden_layers) && alloc(m, &m->dzT, act * hidden_layers) &&
+              alloc(m, &m->part_map, (size_t)(hidden_layers - 1) * slices * width * width) &&
+              alloc(m, &m->part_bias, (size_t)hidden_layers * cblocks * width) &&
               alloc(m, &m->wbT, (size_t)std::max(1, hidden_layers - 1) * width * width) &&
               alloc(m, &m->y, (size_t)max_batch * MLP_OUT) && alloc(m, &m->xbuf, (size_t)max_batch * MLP_IN) &&
               alloc(m, &m->ybuf, (size_t)max_batch * MLP_OUT) &&
@@ -249,18 +268,8 @@ pisco_status pisco_mlp_create(pisco_ctx *ctx, int32_t width, int32_t hidden_laye
               alloc(m, &m->part_w, (size_t)cblocks * MLP_OUT * width) &&
               alloc(m, &m->part_b, (size_t)cblocks * MLP_OUT) && alloc(m, &m->part_loss, waves) &&
               alloc(m, &m->part_in, (size_t)cblocks * width * MLP_IN);
-    m->part_map.assign(hidden_layers, nullptr);
-    m->part_bias.assign(hidden_layers, nullptr);
-    for (int l = 0; l < hidden_layers && ok; ++l) {
-        float *zz = nullptr;
-        __bf16 *aa = nullptr, *at = nullptr;
-        ok = alloc(m, &zz, act) && alloc(m, &aa, act) && alloc(m, &at, act) &&
-             alloc(m, &m->part_bias[l], (size_t)cblocks * width) &&
-             (l == 0 || alloc(m, &m->part_map[l], (size_t)slices * width * width));
-        m->z.push_back(zz);
-        m->a.push_back(aa);
-        m->aT.push_back(at);
-    }
+    m->part_map_stride = (int64_t)slices * width * width;
+    m->part_bias_stride = (int64_t)cblocks * width;
     if (!ok) {
         pisco_mlp_destroy(m);
         pisco::set_error(ctx, "sidelobe network allocation failed");
