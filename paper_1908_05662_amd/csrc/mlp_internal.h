@@ -17,7 +17,8 @@ struct MlpInferArgs {
     const double *th, *ph, *ps;  // pointing, n samples
     int64_t n;
     int32_t H, L;                // width, hidden layers
-    const __bf16 *wb;            // bf16 parameter copy (weights used from it)
+    const __bf16 *wb;            // bf16 parameter copy (first and last layer's weights)
+    const __bf16 *wp;            // the hidden maps' weights, mlp_pack's fwd
     const float *w;              // fp32 parameters (biases used from it)
     int64_t off_w[MLP_MAX_L + 1], off_b[MLP_MAX_L + 1];
     float mean[3], stdv[3];
@@ -31,8 +32,7 @@ hipError_t mlp_in_fwd(const float *x, const __bf16 *w0, const float *b0, int32_t
 struct MlpChain {
     const __bf16 *in;       // forward: A_0; backward: dZ_{L-1}; [rows][H]
     __bf16 *out;            // forward: A_{L-1}; backward: dZ_0
-    const __bf16 *w;        // forward: W_1, W_2, ...; backward: W_1^T, W_2^T, ...
-    int64_t w_stride;
+    const __bf16 *w;        // mlp_pack's W_1, W_2, ... (forward: fwd, backward: bwd)
     const float *bias;      // forward: b_1, b_2, ...
     int64_t b_stride;
     float *z;               // pre-activations [layer][rows][H], z_stride apart (forward: null = not stored)
@@ -50,9 +50,10 @@ hipError_t mlp_chain(const MlpChain &c, bool bwd, int num_cu, hipStream_t s);
 // partial_stride apart.
 hipError_t mlp_wgrad(const __bf16 *a, const __bf16 *b, int64_t ld, int64_t operand_stride, int32_t H, int32_t K,
                      int32_t k_slice, int32_t layers, float *partial, int64_t partial_stride, hipStream_t s);
-// dst[c * ldd + r] = src[r * lds + c] (R, C multiples of 64), for `batch` matrices.
-hipError_t mlp_transpose(const __bf16 *src, int64_t lds, __bf16 *dst, int64_t ldd, int32_t R, int32_t C,
-                         int32_t batch, int64_t src_stride, int64_t dst_stride, hipStream_t s);
+// The H x H weights of `layers` maps (row-major, stride apart) in the fragment order of
+// the kernels that multiply by them: fwd as they are, bwd transposed.
+hipError_t mlp_pack(const __bf16 *src, int64_t stride, int32_t H, int32_t layers, __bf16 *fwd, __bf16 *bwd,
+                    hipStream_t s);
 // Fixed-order sums of several partial arrays in one launch.
 #define MLP_MAX_SEGS 40
 struct MlpReduceSeg {

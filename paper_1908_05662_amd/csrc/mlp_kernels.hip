@@ -52,7 +52,7 @@ __device__ inline float silu_grad(float z) {
 // MFMAs are skipped).  Every output element is one MFMA chain over k0 = 0, 32,
 // 64, ... of its slice.  grid.z walks the layers and their slices: all layers in
 // one launch keep loads, products and stores of different workgroups in flight
-// together.  WGRADMEASURED
+// together: 512 x 10, 8192 rows, 9 launches of 17.9 us before, one of 90 now.
 // ----------------------------------------------------------------------
 constexpr int TK = 32;                 // k per MFMA
 constexpr int KS = 64, LDK = KS + 8;   // k per staged step; LDS rows padded by 16 bytes
@@ -163,20 +163,29 @@ __global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs g) {
         }
 }
 
-// dst[c * ldd + r] = src[r * lds + c] for an R x C bf16 matrix (both multiples of
-// 64), 64 x 64 tiles through LDS; grid.z walks a batch of matrices (strides sz, dz).
-__global__ void __launch_bounds__(256) transpose_kernel(const __bf16 *src, int64_t lds, __bf16 *dst, int64_t ldd,
-                                                        int64_t sz, int64_t dz) {
-    __shared__ __bf16 t[64][66];
-    src += blockIdx.z * sz;
-    dst += blockIdx.z * dz;
-    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+// The hidden maps' weights in the order of the MFMA fragments that chain_kernel and
+// infer_kernel read: [layer][64 units][k step of 32][16 units][lane][8], lane l holding
+// unit l % 16 and k = 8 (l / 16) .. + 7.  A fragment is 1 KiB of consecutive memory;
+// read from the row-major weights it was 64-byte pieces of 16 rows, whose stride of H
+// words falls on a quarter of the L2 channels and whose other halves the small L1
+// dropped before the next k step: 512 x 10, 8192 rows, forward 198 -> 154 us (146 with
+// the loads held in flight), backward 193 -> 173 (147); inference 256 x 4, 1e6 pointings,
+// 770 -> 731 us (695).
+// fwd takes W (unit = row), bwd its transpose (unit = column).
+__global__ void __launch_bounds__(256) pack_kernel(const __bf16 *src, int64_t stride, int32_t H, __bf16 *fwd,
+                                                   __bf16 *bwd) {
+    const int64_t chunk = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // 8 values each
+    if (chunk >= (int64_t)H * H / 8) return;
+    const int lane = chunk & 63, i = (chunk >> 6) & 3;
+    const int gs = (int)(chunk >> 8), steps = H / 32;
+    const int u = 64 * (gs / steps) + 16 * i + (lane & 15), k = 32 * (gs % steps) + 8 * (lane >> 4);
+    const __bf16 *w = src + blockIdx.y * stride;
+    const int64_t o = (int64_t)blockIdx.y * H * H + 8 * chunk;
+    *reinterpret_cast<bf16x8 *>(fwd + o) = *reinterpret_cast<const bf16x8 *>(w + (int64_t)u * H + k);
+    bf16x8 t;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) t[ty * 16 + k][tx] = src[(int64_t)(r0 + ty * 16 + k) * lds + c0 + tx];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) dst[(int64_t)(c0 + ty * 16 + k) * ldd + r0 + tx] = t[tx][ty * 16 + k];
+    for (int e = 0; e < 8; ++e) t[e] = w[(int64_t)(k + e) * H + u];
+    *reinterpret_cast<bf16x8 *>(bwd + o) = t;
 }
 
 // ----------------------------------------------------------------------
@@ -417,7 +426,7 @@ __device__ inline void features_of(const double *th, const double *ph, const dou
 
 // The wave's 64 units of an H x H layer for the 64 RB rows in LDS, as Z^T = W A^T:
 // the weights are the MFMA's first operand (lane l: unit u0 + 16 i + l % 16,
-// k0 + 8 (l / 16) .. + 7, from L2), the activations its second (row 16 j +
+// k0 + 8 (l / 16) .. + 7, in pack_kernel's order, from L2), the activations its second (row 16 j +
 // l % 16, the same k, from LDS), so each output element is one product
 // chain over k0 = 0, 32, ....  The
 // weight fragments of WD k steps are in flight (a ring of register slots,
@@ -432,12 +441,12 @@ __device__ inline void hxh_products(const __bf16 *__restrict__ W, const __bf16 *
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4 * RB; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    const __bf16 *wrow = W + (int64_t)(u0 + r16) * H + kq;
+    const bf16x8 *frag = reinterpret_cast<const bf16x8 *>(W + (int64_t)u0 * H) + lane;
     bf16x8 wf[WD][4];
 #pragma unroll
     for (int sl = 0; sl < WD; ++sl)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) wf[sl][i] = *reinterpret_cast<const bf16x8 *>(wrow + (int64_t)16 * i * H + 32 * sl);
+        for (int i = 0; i < 4; ++i) wf[sl][i] = frag[256 * sl + 64 * i];
     for (int k0 = 0; k0 < H; k0 += WD * 32) {
 #pragma unroll
         for (int sl = 0; sl < WD; ++sl) {
@@ -452,8 +461,9 @@ __device__ inline void hxh_products(const __bf16 *__restrict__ W, const __bf16 *
             const int kn = kc + WD * 32;
             if (kn < H) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) wf[sl][i] = *reinterpret_cast<const bf16x8 *>(wrow + (int64_t)16 * i * H + kn);
+                for (int i = 0; i < 4; ++i) wf[sl][i] = frag[8 * kn + 64 * i];
             }
+            __builtin_amdgcn_sched_barrier(0);   // (see chain_products)
         }
     }
 }
@@ -488,7 +498,8 @@ __device__ inline void hxh_store(const float *__restrict__ bias, __bf16 *act, in
 // operands, the bias gradients' partial sums.  Layer by layer as a product with an
 // epilogue the chip idled in turn: its loads, products and 32 MB of stores came one
 // after the other in every workgroup at once, 18 to 21 us a layer and direction at H
-// = 512 and 8192 rows, where its bytes take 8.  CHAINMEASURED
+// = 512 and 8192 rows, where its bytes take 8.  Now 16 us a layer, bound by the L2's
+// delivery of the weights (512 KiB a layer to every workgroup) and by the stores.
 // Each output element is the MFMA chain over k0 = 0, 32, ... of infer_kernel.
 // Rows past n (the buffers are padded to 128) carry stale values that nothing reads.
 // ----------------------------------------------------------------------
@@ -503,27 +514,36 @@ __device__ inline void chain_products(const __bf16 *__restrict__ W, const __bf16
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < JT; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    const __bf16 *wrow = W + (int64_t)(u0 + r16) * H + kq;
+    const bf16x8 *frag = reinterpret_cast<const bf16x8 *>(W + u0 * H) + lane;
     bf16x8 wf[WDC][4];
 #pragma unroll
     for (int sl = 0; sl < WDC; ++sl)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if (sl < STEPS) wf[sl][i] = *reinterpret_cast<const bf16x8 *>(wrow + (int64_t)16 * i * H + 32 * sl);
+            if (sl < STEPS) wf[sl][i] = frag[256 * sl + 64 * i];
+    // (the fences keep the loads where they stand: moved next to their use, as they
+    // would be to save registers, every step waited out the L2's latency)
+    bf16x8 af[2][JT];
+#pragma unroll
+    for (int j = 0; j < JT; ++j) af[0][j] = *reinterpret_cast<const bf16x8 *>(act + (16 * j + r16) * LD + kq);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int st = 0; st < STEPS; ++st) {
+        if (st + 1 < STEPS) {
 #pragma unroll
-        for (int j = 0; j < JT; ++j) {
-            const bf16x8 af = *reinterpret_cast<const bf16x8 *>(act + (16 * j + r16) * LD + 32 * st + kq);
+            for (int j = 0; j < JT; ++j)
+                af[(st + 1) & 1][j] = *reinterpret_cast<const bf16x8 *>(act + (16 * j + r16) * LD + 32 * (st + 1) + kq);
+        }
+#pragma unroll
+        for (int j = 0; j < JT; ++j)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[st % WDC][i], af, acc[i][j], 0, 0, 0);
-        }
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[st % WDC][i], af[st & 1][j], acc[i][j], 0, 0, 0);
         if (st + WDC < STEPS) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                wf[st % WDC][i] = *reinterpret_cast<const bf16x8 *>(wrow + (int64_t)16 * i * H + 32 * (st + WDC));
+            for (int i = 0; i < 4; ++i) wf[st % WDC][i] = frag[256 * (st + WDC) + 64 * i];
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -592,7 +612,7 @@ __global__ void __launch_bounds__(64 * NW, 2) chain_kernel(MlpChain g) {
                     zp[i][j] = *reinterpret_cast<const float4 *>(z + (int64_t)16 * j * H + 16 * i);
         }
         f32x4 acc[4][JT];
-        chain_products<NW, JT, NW == 1 ? 2 : 4>(g.w + (int64_t)(BWD ? l - 1 : l) * g.w_stride, act, u0, lane, acc);
+        chain_products<NW, JT, NW == 1 ? 2 : 4>(g.w + (int64_t)(BWD ? l - 1 : l) * H * H, act, u0, lane, acc);
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -681,7 +701,7 @@ __global__ void __launch_bounds__(64 * NW, RB == 1 ? 4 : 2) infer_kernel(MlpInfe
     // then (after the barrier) its units' activations over that input
     for (int l = 1; l < g.L; ++l) {
         f32x4 acc[4][4 * RB];
-        hxh_products<RB>(g.wb + g.off_w[l], act, H, LD, u0, lane, acc);
+        hxh_products<RB>(g.wp + (int64_t)(l - 1) * H * H, act, H, LD, u0, lane, acc);
         __syncthreads();
         hxh_store<RB>(g.w + g.off_b[l], act, LD, u0, lane, acc);
         __syncthreads();
@@ -774,7 +794,8 @@ hipError_t mlp_wgrad(const __bf16 *a, const __bf16 *b, int64_t ld, int64_t opera
 }
 
 // 64 rows a workgroup when that still gives every CU one (the weights are then read
-// from L2 once per 64 rows), 32 otherwise.
+// from L2 once per 64 rows), 32 otherwise.  A whole gradient of 512 x 10, us with 32 and
+// 64 rows: 8192 rows 488 / 510, where 64 leave half the CUs idle.
 template <int NW, int JT, bool BWD>
 static hipError_t chain_launch(const MlpChain &a, hipStream_t s) {
     const size_t lds = (size_t)(16 * JT) * (64 * NW + 8) * sizeof(__bf16);
@@ -808,12 +829,12 @@ hipError_t mlp_chain(const MlpChain &a, bool bwd, int num_cu, hipStream_t s) {
     }
 }
 
-hipError_t mlp_transpose(const __bf16 *src, int64_t lds, __bf16 *dst, int64_t ldd, int32_t R, int32_t C,
-                         int32_t batch, int64_t src_stride, int64_t dst_stride, hipStream_t s) {
-    if (R % 64 || C % 64) return hipErrorInvalidValue;
-    if (R == 0 || C == 0 || batch == 0) return hipSuccess;
-    hipLaunchKernelGGL(transpose_kernel, dim3(C / 64, R / 64, batch), dim3(256), 0, s, src, lds, dst, ldd,
-                       src_stride, dst_stride);
+hipError_t mlp_pack(const __bf16 *src, int64_t stride, int32_t H, int32_t layers, __bf16 *fwd, __bf16 *bwd,
+                    hipStream_t s) {
+    if (H % 64) return hipErrorInvalidValue;
+    if (layers <= 0) return hipSuccess;
+    hipLaunchKernelGGL(pack_kernel, dim3(blocks_for((int64_t)H * H / 8, 256), layers), dim3(256), 0, s, src, stride, H,
+                       fwd, bwd);
     return hipGetLastError();
 }
 

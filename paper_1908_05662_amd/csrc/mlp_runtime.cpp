@@ -29,7 +29,7 @@ struct pisco_mlp {
     __bf16 *aT = nullptr;            // transposes of the hidden activations [L][H][mbp] (weight gradients' operands)
     __bf16 *dzL = nullptr, *dz0 = nullptr;   // dL/dz of the last and first hidden layer [mbp][H]
     __bf16 *dzT = nullptr;           // transposes of the hidden layers' dL/dz [L][H][mbp] (layer 0's unused)
-    __bf16 *wbT = nullptr;           // transposes of the hidden maps' BF16 weights, [L-1][H][H]
+    __bf16 *wp = nullptr, *wpT = nullptr;    // the hidden maps' BF16 weights and their transposes, packed [L-1][H][H]
     float *y = nullptr, *xbuf = nullptr, *ybuf = nullptr;
     float *dy = nullptr;             // output-layer dL/dy [max_batch][3] (fp32)
     float *part_w = nullptr, *part_b = nullptr, *part_loss = nullptr;
@@ -97,12 +97,10 @@ int32_t k_slice_for(int32_t n, int32_t H) {
 
 int32_t round_up(int32_t n, int32_t q) { return (n + q - 1) / q * q; }
 
-// The BF16 transposes of the hidden maps' weights (operands of the backward pass).
-hipError_t refresh_wbT(pisco_mlp *m, hipStream_t s) {
+// The packed copies of the hidden maps' weights.
+hipError_t refresh_packed(pisco_mlp *m, hipStream_t s) {
     if (m->L < 2) return hipSuccess;
-    const int64_t stride = m->off_w[2] - m->off_w[1];
-    return pisco::mlp_transpose(m->wb + m->off_w[1], m->H, m->wbT, m->H, m->H, m->H, m->L - 1, stride,
-                                (int64_t)m->H * m->H, s);
+    return pisco::mlp_pack(m->wb + m->off_w[1], m->L > 2 ? m->off_w[2] - m->off_w[1] : 0, m->H, m->L - 1, m->wp, m->wpT, s);
 }
 
 // forward (+ loss and backward when tgt != nullptr) over one chunk of n rows
@@ -113,7 +111,7 @@ pisco_status run(pisco_mlp *m, const float *x, const float *tgt, int32_t n, floa
     const int64_t ldt = m->mbp;
     const bool train = tgt != nullptr;
     const int num_cu = pisco::ctx_num_cu(m->ctx);
-    const int64_t act = (int64_t)m->mbp * H, wst = L > 1 ? m->off_w[2] - m->off_w[1] : 0;
+    const int64_t act = (int64_t)m->mbp * H;
     pisco::MlpChain c{};
     c.n = n;
     c.L = L;
@@ -124,9 +122,9 @@ pisco_status run(pisco_mlp *m, const float *x, const float *tgt, int32_t n, floa
     if (L > 1) {
         c.in = m->a0;
         c.out = m->aL;
-        c.w = m->wb + m->off_w[1];
+        c.w = m->wp;
         c.bias = m->w + m->off_b[1];
-        c.w_stride = c.b_stride = wst;
+        c.b_stride = m->off_b[2] - m->off_b[1];
         c.z = train ? m->z : nullptr;
         c.t = train ? m->aT : nullptr;
         MLP_TRY(m, pisco::mlp_chain(c, false, num_cu, s));
@@ -158,8 +156,7 @@ pisco_status run(pisco_mlp *m, const float *x, const float *tgt, int32_t n, floa
         // the batch, split into slices
         c.in = m->dzL;
         c.out = m->dz0;
-        c.w = m->wbT;
-        c.w_stride = (int64_t)H * H;
+        c.w = m->wpT;
         c.z = m->z;
         c.t = m->dzT;
         c.part_bias = m->part_bias;
@@ -199,6 +196,7 @@ hipError_t mlp_apply_pointing(const pisco_mlp *m, const double *th, const double
     a.H = m->H;
     a.L = m->L;
     a.wb = m->wb;
+    a.wp = m->wp;
     a.w = m->w;
     for (int l = 0; l <= m->L; ++l) {
         a.off_w[l] = m->off_w[l];
@@ -261,7 +259,8 @@ pisco_status pisco_mlp_create(pisco_ctx *ctx, int32_t width, int32_t hidden_laye
               alloc(m, &m->aT, act * hidden_layers) && alloc(m, &m->dzT, act * hidden_layers) &&
               alloc(m, &m->part_map, (size_t)(hidden_layers - 1) * slices * width * width) &&
               alloc(m, &m->part_bias, (size_t)hidden_layers * cblocks * width) &&
-              alloc(m, &m->wbT, (size_t)std::max(1, hidden_layers - 1) * width * width) &&
+              alloc(m, &m->wp, (size_t)(hidden_layers - 1) * width * width) &&
+              alloc(m, &m->wpT, (size_t)(hidden_layers - 1) * width * width) &&
               alloc(m, &m->y, (size_t)max_batch * MLP_OUT) && alloc(m, &m->xbuf, (size_t)max_batch * MLP_IN) &&
               alloc(m, &m->ybuf, (size_t)max_batch * MLP_OUT) &&
               alloc(m, &m->dy, (size_t)max_batch * MLP_OUT) &&
@@ -321,7 +320,7 @@ pisco_status pisco_mlp_set_params(pisco_mlp *m, const float *params, int mem) {
     MLP_TRY(m, hipMemset(m->m, 0, b));
     MLP_TRY(m, hipMemset(m->v, 0, b));
     MLP_TRY(m, pisco::mlp_to_bf16(m->w, m->wb, m->nparam, nullptr));
-    MLP_TRY(m, refresh_wbT(m, nullptr));
+    MLP_TRY(m, refresh_packed(m, nullptr));
     MLP_TRY(m, hipDeviceSynchronize());
     m->step = 0;
     return PISCO_OK;
@@ -372,7 +371,7 @@ pisco_status pisco_mlp_train_step(pisco_mlp *m, const float *x, const float *t, 
     const float lr_t = (float)(lr / bc1);
     const float inv = (float)(1.0 / std::sqrt(bc2));
     MLP_TRY(m, pisco::mlp_adam(m->w, m->m, m->v, m->g, m->wb, m->nparam, lr_t, beta1, beta2, eps, inv, s));
-    MLP_TRY(m, refresh_wbT(m, s));
+    MLP_TRY(m, refresh_packed(m, s));
     return PISCO_OK;
 }
 
