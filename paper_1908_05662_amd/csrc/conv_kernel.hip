@@ -2189,7 +2189,8 @@ hipError_t launch_zero_counters(int32_t *counters, int n, hipStream_t s) {
 // 889; 3584: 1074 / 1174; 4096: 1133 / 1215; 5120: 1465 / 1469 (256 compute units;
 // four-channel beams, Stokes pickups and 6 deg discs cross at the same places).
 void share_tiles(ConvArgs &a, int64_t n, int num_cu) {
-    const int w = n <= num_cu ? 8 : n <= 4 * num_cu ? 4 : n <= 12 * num_cu ? 2 : 0;
+    // (the matrix-core path's waves take a tile each)
+    const int w = a.algo != ALGO_TILE ? 0 : n <= num_cu ? 8 : n <= 4 * num_cu ? 4 : n <= 12 * num_cu ? 2 : 0;
     a.share_tiles = w;
     a.share_groups = w ? (int32_t)std::min<int64_t>(n, (int64_t)num_cu * (16 / w)) : 0;
 }
