@@ -662,7 +662,8 @@ struct LaneFrame {
     float om, p1, p2, p3;   // 1 - p.c and p
     float a1, a2, a3;       // theta'_0
     float b1, b2, b3;       // phi'_0
-    float g1, g2, g3;       // co-polar direction at the boresight (matrix-core variant)
+    float g1, g2, g3;       // co-polar direction at the boresight (matrix-core variant); pair loop with a
+                            // plate: theta'_0 turned by 2 phi_t, first two components, grid units
     float c2p, s2p;         // cos, sin of 2 phi_t (half-wave plate; 1, 0 without one)
 };
 
@@ -1015,7 +1016,7 @@ constexpr double SCT1 = 8e-3;
 template <int MODE, int BEAM, bool PS, int NP, bool HWP, bool CLIP, bool INNER, int SC = 0, bool QF = false>
 __device__ __forceinline__ PairOut tile_pairs(const typename Cond<QF, PixRecQ, PixRec>::type *Rp, const float *Vp,
                                               const PairCtx &C, const BeamRsrc &beam, const BeamRsrc &vbeam) {
-    static_assert(!QF || (MODE == MODE_TOD && BEAM == BEAM_SCALAR && !HWP), "quadratic form: one-grid TOD, no plate");
+    static_assert(!QF || (MODE == MODE_TOD && BEAM == BEAM_SCALAR), "quadratic form: one-grid TOD");
     constexpr bool ZMASK = BEAM == BEAM_SCALAR && SC != 0 && MODE == MODE_TOD;
     const LaneFrame &F = C.F;
     typename Cond<QF, PixRecQ, PixRec>::type R[NP];
@@ -1146,7 +1147,10 @@ __device__ __forceinline__ PairOut tile_pairs(const typename Cond<QF, PixRecQ, P
         // projections take a - q p.  a.n is xp, in grid units like the lane's
         // a rows, so e, its projections and the angle terms below carry the
         // grid scale (1/h, 1/h^2); the records carry h^2.
-        const float q = xp[k] * rq[k];
+        // (a plate turns gamma by 2 phi_t.  In the quadratic form the vector that is
+        // carried is turned instead: g = cos(2 phi_t) theta'_0 + sin(2 phi_t) phi'_0,
+        // with g.n from the same two products that give the grid coordinates.)
+        const float q = (QF && HWP ? fmaf(F.s2p, yp[k], F.c2p * xp[k]) : xp[k]) * rq[k];
         if constexpr (QF) {
             // e is normal to n, so its first two tile-frame components fix it:
             // for vectors v, w normal to n, v.w = v_xy . (w_xy - (w_z / n_z) n_xy),
@@ -1154,8 +1158,8 @@ __device__ __forceinline__ PairOut tile_pairs(const typename Cond<QF, PixRecQ, P
             // product of the projections on theta_hat and on B theta_hat + C phi_hat,
             // as the quadratic form e_xy^T P e_xy (x h^2).  Here xp is
             // a.n / n_z, so q (p + n) = (xp rq) n_z (p + n).
-            const float ex = fmaf(-q, fmaf(R[k].Z, F.p1, R[k].ZX), F.a1);
-            const float ey = fmaf(-q, fmaf(R[k].Z, F.p2, R[k].ZY), F.a2);
+            const float ex = fmaf(-q, fmaf(R[k].Z, F.p1, R[k].ZX), HWP ? F.g1 : F.a1);
+            const float ey = fmaf(-q, fmaf(R[k].Z, F.p2, R[k].ZY), HWP ? F.g2 : F.a2);
             const float4 c = cl[k][0];
             const float bT = fmaf(fv[k], fmaf(fu[k], c.w, c.z), fmaf(fu[k], c.y, c.x));
             const float bTm = ZMASK ? bT : (in[k] ? bT : 0.0f);
@@ -1292,10 +1296,11 @@ __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin
 
     const int32_t n = D.n;
     const float inv_h = (float)D.inv_h;
-    // one-grid TOD without a plate: the angle terms as a quadratic form in the
-    // tangent-plane components of the carried theta'_0 (caps up to 60 deg, so
-    // that the third component n_z >= 1/2 of every staged pixel stays large)
-    const bool qf = MODE == MODE_TOD && BEAM == BEAM_SCALAR && !HWP && D.needs_clip == 0 && D.has_inner == 0 &&
+    // one-grid TOD: the angle terms as a quadratic form in the tangent-plane
+    // components of the carried theta'_0 (caps up to 60 deg, so that the third
+    // component n_z >= 1/2 of every staged pixel stays large).  With a plate, 880k
+    // samples of 2 deg discs took 3.75 ms on the plain records and take 3.31.
+    const bool qf = MODE == MODE_TOD && BEAM == BEAM_SCALAR && D.needs_clip == 0 && D.has_inner == 0 &&
                     cosRu >= 0.5;
     const float c0 = (float)(0.5 * (n - 1));
     const float tmax = (float)(n - 1);
@@ -1307,6 +1312,10 @@ __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin
     Fg.b1 *= inv_h;
     Fg.b2 *= inv_h;
     Fg.b3 *= inv_h;
+    if (HWP) {   // theta'_0 turned by 2 phi_t, for the quadratic form
+        Fg.g1 = fmaf(F.s2p, Fg.b1, F.c2p * Fg.a1);
+        Fg.g2 = fmaf(F.s2p, Fg.b2, F.c2p * Fg.a2);
+    }
     // omin = -1 without an inner disc, so `omg > omin` holds for every pixel (omg >= 0)
     const float omax = (float)D.omega_max, omin = D.has_inner ? (float)D.omega_min : -1.0f;
     const bool inner = D.has_inner != 0;
@@ -1459,7 +1468,7 @@ __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin
                     const PairCtx C{Fg, omax, omin, clip, inv_h, c0 + ringoff, tmax + ringoff, cmax, row, row_bytes,
                                     sg4, (float)(n - 1), ringoff, (uint32_t)row};
                     const float *vr = has_v ? vrec : nullptr;
-                    if constexpr (MODE == MODE_TOD && BEAM == BEAM_SCALAR && !HWP) {
+                    if constexpr (MODE == MODE_TOD && BEAM == BEAM_SCALAR) {
                         if (qf) {
                             const PixRecQ *rq = reinterpret_cast<const PixRecQ *>(L.rec);
                             if (tiny_q)
