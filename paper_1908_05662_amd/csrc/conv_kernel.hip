@@ -1298,7 +1298,7 @@ __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin
     const float inv_h = (float)D.inv_h;
     // one-grid TOD: the angle terms as a quadratic form in the tangent-plane
     // components of the carried theta'_0 (caps up to 60 deg, so that the third
-    // component n_z >= 1/2 of every staged pixel stays large).  With a plate, 880k
+    // component n_z >= 1/2 of every staged pixel stays large).  With a plate, 805k
     // samples of 2 deg discs took 3.75 ms on the plain records and take 3.31.
     const bool qf = MODE == MODE_TOD && BEAM == BEAM_SCALAR && D.needs_clip == 0 && D.has_inner == 0 &&
                     cosRu >= 0.5;
