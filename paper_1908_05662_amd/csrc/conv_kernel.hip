@@ -135,7 +135,7 @@ template <> struct Rec4<double> { using type = double4; };
 
 // sin and cos of x for |x| <= pi/2 + a little.  FP32: Taylor series to x^13
 // (sin) and x^14 (cos), truncation below 1e-9 on that range, keeping relative
-// precision of sin near 0.  FP64: the device math library.
+// precision of sin near 0.
 __device__ inline void half_sincos(float x, float &s, float &c) {
     constexpr float S3 = -1.0f / 6.0f, S5 = 1.0f / 120.0f, S7 = -1.0f / 5040.0f, S9 = 1.0f / 362880.0f,
                     S11 = -1.0f / 39916800.0f, S13 = 1.0f / 6227020800.0f;
