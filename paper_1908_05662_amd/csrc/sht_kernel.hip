@@ -1153,9 +1153,11 @@ __device__ inline void syn_one(PairState &p, SynSums &f, const Step &st, const S
         return;
     }
     const double s = odd ? -1.0 : 1.0;
-    double2 &T = odd ? f.To : f.Te;
-    T.x = fma(p.v, al.t[0], T.x);
-    T.y = fma(p.v, al.t[1], T.y);
+    // (values are selected, not a reference to one of the sums: that would keep the
+    // lane's sums in scratch memory, read and written at every l of the main loop too)
+    const double x = fma(p.v, al.t[0], odd ? f.To.x : f.Te.x), y = fma(p.v, al.t[1], odd ? f.To.y : f.Te.y);
+    f.Te = make_double2(odd ? f.Te.x : x, odd ? f.Te.y : y);
+    f.To = make_double2(odd ? x : f.To.x, odd ? y : f.To.y);
     if (POL) {
         const double px = al.e[0] - al.b[1], py = al.e[1] + al.b[0], mx = al.e[0] + al.b[1], my = al.e[1] - al.b[0];
         f.Pn.x = fma(p.fp, px, f.Pn.x);
@@ -1181,7 +1183,9 @@ __device__ inline void late_start(PairState &p, const RingGeom &g, int m) {
 
 // One workgroup of NW waves per m, K ring pairs a lane, LB l a step of the loop.
 // Bound by FP64 issue: 19 instructions per (l, pair); at nside 128, lmax 383 by the
-// chain of l (1.5 waves a SIMD): 42 us, 114 with W and X in 768-lane workgroups.
+// chain of l (1.5 waves a SIMD): 42 us, 114 with W and X in 768-lane workgroups.  A
+// whole polarised synthesis at nside 1024, lmax 3071: 11.2 ms, 18.3 with W and X and
+// the directly summed ring DFTs (193 registers; no scratch memory, see syn_one).
 template <bool POL, int K, int NW, int LB>
 __global__ void __launch_bounds__(64 * NW, K >= 4 ? 2 : 1) alm2ring_kernel(ShtArgs a) {
     constexpr int NT = 64 * NW;
@@ -1275,7 +1279,7 @@ __global__ void __launch_bounds__(64 * NW, K >= 4 ? 2 : 1) alm2ring_kernel(ShtAr
             put((ch + 1) & 1);
             __syncthreads();
         }
-    } else     if (li + LB <= nl) {
+    } else if (li + LB <= nl) {
         Step s[LB];
         SynAlm<POL> al[LB];
 #pragma unroll
