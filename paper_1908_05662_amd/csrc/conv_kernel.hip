@@ -1274,11 +1274,13 @@ __device__ __forceinline__ void consume_records(const typename Cond<QF, PixRecQ,
     }
 }
 
-// With `parts` > 1 the waves of a workgroup share the tile: wave `part` takes every
+// SHARE: the waves of a workgroup share the tile: wave `part` takes every
 // parts-th chunk of each ring batch (the groups of records whose terms are summed in
 // FP32 stay the same; only the FP64 sums are split), and the first wave adds the
-// waves' sums in order.  L is this wave's slice, the others' lie beside it.
-template <int MODE, int BEAM, int CH, bool PS, bool HWP>
+// waves' sums in order.  L is this wave's slice, the others' lie beside it.  (A form
+// of its own: carried as run-time values the sharing took the pair loop of unshared
+// launches from 11 to 24 spilled registers.)
+template <int MODE, int BEAM, int CH, bool PS, bool HWP, bool SHARE>
 __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin, int32_t cnt, TileLds<CH> &L,
                               float *vrec, int lane, int32_t part, int32_t parts) {
     static_assert(CH % WAVE == 0, "chunks are whole waves of records");
@@ -1370,7 +1372,7 @@ __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin
         // ring of the chunk's first record, or an earlier one: each lane's search
         // starts there instead of at the batch's first ring
         int32_t seg0 = 0;
-        for (int32_t pb = part * CH; pb < total; pb += parts * CH) {
+        for (int32_t pb = SHARE ? part * CH : 0; pb < total; pb += SHARE ? parts * CH : CH) {
             const int32_t m_end = min(CH, total - pb);
             // fill: one pixel record per lane, FP32 differences from the centre
             int32_t seg = seg0;
@@ -1511,7 +1513,7 @@ __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin
         }
     }
 
-    if (parts > 1) {
+    if constexpr (SHARE) {
         // the waves' sums meet in their own slices (free now)
         struct Sums {
             double a0[WAVE], a1[WAVE], a2[WAVE], an[WAVE];
@@ -1916,57 +1918,56 @@ __device__ inline bool tile_is_coherent(const DetDesc &D, int64_t begin, int32_t
 // ----------------------------------------------------------------------
 // Kernels
 // ----------------------------------------------------------------------
+// A wave's tile in scalar registers: the compiler does not see that the index is the
+// same for every lane, and the pair loop of one-grid TOD has no vector register to
+// spare (3 to 11 spilled with this, 14 to 36 without).
+__device__ inline Tile uniform_tile(Tile t) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)t.begin);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)t.begin >> 32));
+    t.begin = (int64_t)(((uint64_t)hi << 32) | lo);
+    t.count = __builtin_amdgcn_readfirstlane(t.count);
+    t.det = __builtin_amdgcn_readfirstlane(t.det);
+    return t;
+}
+
 // A wave's walk over the queues, its own first.  A wave owns the first OWN rounds of
 // tiles of its place in the launch; the later ones it pops from a counter (which starts
 // at the first tile that no wave owns).  The pops of one counter are served one after
 // the other, about 67 ns each, so a launch of 4096 waves that popped their first tiles
-// too had its last wave start 270 us late, and 8192 small tiles took 550 us.  A launch
-// that shares tiles pops nothing: a workgroup takes every gridDim-th tile.
+// too had its last wave start 270 us late, and 8192 small tiles took 550 us.
 template <int OWN> struct TileWalk {
-    int32_t q, exhausted, own, rounds;
+    int32_t q, exhausted;
+    int32_t own;         // the owned tile that is next; -1: none left
     __device__ inline TileWalk(const ConvArgs &A, int wid) {
         const uint32_t nq = (uint32_t)A.n_queues;
         exhausted = 0;
-        rounds = OWN;
-        if (A.share_tiles) {
-            q = 0;
-            own = (int32_t)blockIdx.x;
-        } else {
-            q = nq > 1 ? (int32_t)(blockIdx.x % nq) : 0;
-            own = (int32_t)(nq > 1 ? blockIdx.x / nq : blockIdx.x) * (int32_t)(blockDim.x / WAVE) +
-                  __builtin_amdgcn_readfirstlane(wid);
-        }
+        q = nq > 1 ? (int32_t)(blockIdx.x % nq) : 0;
+        own = (int32_t)(nq > 1 ? blockIdx.x / nq : blockIdx.x) * (int32_t)(blockDim.x / WAVE) +
+              __builtin_amdgcn_readfirstlane(wid);
     }
     // The next tile of the wave, or false when every queue is drained.  A plain load
     // goes before the pop, so waves that find a queue drained add nothing to the
     // atomics; the counter only grows, so a stale load at worst leads to the atomic.
     __device__ inline bool next(const ConvArgs &A, int lane, Tile &tl) {
         while (exhausted < A.n_queues) {
-            const int32_t len = A.queue_len[q];
+            const int32_t len = A.queue_len[q], nq = A.n_queues;
+            // a round of queue q: the waves of its workgroups
+            const int32_t round = ((int32_t)gridDim.x + nq - 1 - q) / nq * (int32_t)(blockDim.x / WAVE);
             int32_t ti = own;
-            if (A.share_tiles) {
-                own += (int32_t)gridDim.x;
+            if (own >= 0) {
+                own = own < (OWN - 1) * round ? own + round : -1;
             } else {
-                // a round of queue q: the waves of its workgroups
-                const int32_t nq = A.n_queues;
-                const int32_t round = ((int32_t)gridDim.x + nq - 1 - q) / nq * (int32_t)(blockDim.x / WAVE);
-                if (rounds > 0) {
-                    --rounds;
-                    own += round;
-                } else {
-                    ti = len;
-                    if (lane == 0 && __hip_atomic_load(&A.counters[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
-                                             OWN * round < len)
-                        ti = OWN * round + atomicAdd(&A.counters[q], 1);
-                    ti = __builtin_amdgcn_readfirstlane(ti);
-                }
+                ti = len;
+                if (lane == 0 &&
+                    __hip_atomic_load(&A.counters[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + OWN * round < len)
+                    ti = OWN * round + atomicAdd(&A.counters[q], 1);
             }
+            ti = __builtin_amdgcn_readfirstlane(ti);
             if (ti < len) {
-                tl = A.tiles[(int64_t)q * A.tiles_per_queue + ti];
+                tl = uniform_tile(A.tiles[(int64_t)q * A.tiles_per_queue + ti]);
                 return true;
             }
-            own = (int32_t)blockIdx.x;
-            rounds = 0;
+            own = -1;
             q = (q + 1 == A.n_queues) ? 0 : q + 1;
             ++exhausted;
         }
@@ -1999,21 +2000,31 @@ __global__ void __launch_bounds__(512, (pixel_waves_per_simd(sizeof(T) == 8))) c
     }
 }
 
-template <int MODE, int BEAM, int CH, bool PS, bool HWP>
+template <int MODE, int BEAM, int CH, bool PS, bool HWP, bool SHARE>
 __global__ void __launch_bounds__(512, (tile_min_waves<MODE, BEAM>())) tile_kernel(ConvArgs A) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int lane = threadIdx.x & (WAVE - 1);
-    const int wid = threadIdx.x / WAVE;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     TileLds<CH> &L = reinterpret_cast<TileLds<CH> *>(lds_raw)[wid];
     float *vrec = (BEAM == BEAM_FULL && MODE == MODE_TOD && A.vbeam)
                       ? reinterpret_cast<float *>(lds_raw + sizeof(TileLds<CH>) * (blockDim.x / WAVE)) + wid * CH
                       : nullptr;
-    const int32_t part = A.share_tiles ? __builtin_amdgcn_readfirstlane(wid) : 0;
-    const int32_t parts = A.share_tiles ? (int32_t)(blockDim.x / WAVE) : 1;
-    TileWalk<1> walk(A, wid);
-    Tile tl;
-    while (walk.next(A, lane, tl))
-        convolve_tile<MODE, BEAM, CH, PS, HWP>(A, A.dets[tl.det], tl.begin, tl.count, L, vrec, lane, part, parts);
+    if constexpr (SHARE) {
+        // the workgroup takes every gridDim-th tile of each queue: no pops
+        const int32_t part = wid, parts = (int32_t)(blockDim.x / WAVE);
+        for (int32_t q = 0; q < A.n_queues; ++q) {
+            for (int32_t i = (int32_t)blockIdx.x; i < A.queue_len[q]; i += (int32_t)gridDim.x) {
+                const Tile tl = A.tiles[(int64_t)q * A.tiles_per_queue + i];
+                convolve_tile<MODE, BEAM, CH, PS, HWP, true>(A, A.dets[tl.det], tl.begin, tl.count, L, vrec, lane, part,
+                                                             parts);
+            }
+        }
+    } else {
+        TileWalk<1> walk(A, wid);
+        Tile tl;
+        while (walk.next(A, lane, tl))
+            convolve_tile<MODE, BEAM, CH, PS, HWP, false>(A, A.dets[tl.det], tl.begin, tl.count, L, vrec, lane, 0, 1);
+    }
 }
 
 template <int MODE, int BEAM, int CH, bool PS>
@@ -2214,22 +2225,26 @@ static hipError_t launch_pixel(const ConvArgs &a, int waves, int groups, hipStre
     return hipGetLastError();
 }
 
-template <int MODE, int BEAM, int CH, bool PS, bool HWP>
-static hipError_t launch_tile_h(const ConvArgs &a, int waves, int groups, hipStream_t s) {
+template <int MODE, int BEAM, int CH, bool PS, bool HWP, bool SHARE>
+static hipError_t launch_tile_s(const ConvArgs &a, int waves, int groups, hipStream_t s) {
     const bool v = BEAM == BEAM_FULL && MODE == MODE_TOD && a.vbeam;
-    if (a.share_tiles) {
-        waves = a.share_tiles;
-        groups = a.share_groups;
-    }
     const size_t lds = (sizeof(TileLds<CH>) + (v ? sizeof(float) * CH : 0)) * (size_t)waves;
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     if (lds > 64 * 1024) {  // allow the larger LDS allocations of gfx950 (160 KiB per CU)
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tile_kernel<MODE, BEAM, CH, PS, HWP>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const hipError_t e =
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&tile_kernel<MODE, BEAM, CH, PS, HWP, SHARE>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((tile_kernel<MODE, BEAM, CH, PS, HWP>), dim3(groups), dim3(WAVE * waves), lds, s, a);
+    hipLaunchKernelGGL((tile_kernel<MODE, BEAM, CH, PS, HWP, SHARE>), dim3(groups), dim3(WAVE * waves), lds, s, a);
     return hipGetLastError();
+}
+
+// A launch that shares tiles stages 64 records at a time, the finest split.
+template <int MODE, int BEAM, int CH, bool PS, bool HWP>
+static hipError_t launch_tile_h(const ConvArgs &a, int waves, int groups, hipStream_t s) {
+    if (a.share_tiles) return launch_tile_s<MODE, BEAM, 64, PS, HWP, true>(a, a.share_tiles, a.share_groups, s);
+    return launch_tile_s<MODE, BEAM, CH, PS, HWP, false>(a, waves, groups, s);
 }
 
 template <int MODE, int BEAM, int CH, bool PS>

@@ -16,3 +16,14 @@ def test_synthesis_sums_stay_in_registers():
     lane: 44 ms for nside 1024, lmax 3071)."""
     for name, k in _of("alm2ring_kernel").items():
         assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, name
+
+
+def test_unshared_tile_loop_spills():
+    """The pair loop of one-grid TOD fills the 128 registers of four waves a SIMD; what
+    its launches keep around it (the walk over the queues) may cost it a few spills a
+    tile, as before launches could share tiles (at most 11 without a plate, 18 with
+    one), and no scalar ones."""
+    for name, k in _of("tile_kernel<0, 1, ").items():
+        if name.endswith(", false>"):
+            plate = name.split(", ")[4] == "true"
+            assert k[".vgpr_spill_count"] <= (18 if plate else 11) and k[".sgpr_spill_count"] == 0, name
