@@ -2010,14 +2010,20 @@ __global__ void __launch_bounds__(512, (tile_min_waves<MODE, BEAM>())) tile_kern
                       ? reinterpret_cast<float *>(lds_raw + sizeof(TileLds<CH>) * (blockDim.x / WAVE)) + wid * CH
                       : nullptr;
     if constexpr (SHARE) {
-        // the workgroup takes every gridDim-th tile of each queue: no pops
+        // the workgroup takes every gridDim-th tile, counted through the queues one after
+        // the other: no pops, and as many workgroups at work for any number of queues
+        // (each queue counted from its start, the first eighth of the workgroups took all
+        // tiles of eight queues: 1024 tiles of 2 deg discs, nside 1024, 1341 us against 347)
         const int32_t part = wid, parts = (int32_t)(blockDim.x / WAVE);
+        int32_t i = (int32_t)blockIdx.x;
         for (int32_t q = 0; q < A.n_queues; ++q) {
-            for (int32_t i = (int32_t)blockIdx.x; i < A.queue_len[q]; i += (int32_t)gridDim.x) {
+            const int32_t len = A.queue_len[q];
+            for (; i < len; i += (int32_t)gridDim.x) {
                 const Tile tl = A.tiles[(int64_t)q * A.tiles_per_queue + i];
                 convolve_tile<MODE, BEAM, CH, PS, HWP, true>(A, A.dets[tl.det], tl.begin, tl.count, L, vrec, lane, part,
                                                              parts);
             }
+            i -= len;
         }
     } else {
         TileWalk<1> walk(A, wid);
