@@ -262,7 +262,12 @@ int64_t pisco_output_samples(const pisco_ctx *ctx, int32_t det);
  *                    waits on the matrix results).
  *   samples_per_tile consecutive samples a wavefront takes per queue pop (1..65536)
  *   waves_per_group  wavefronts per workgroup (1, 2, 4 or 8)
- *   groups_per_cu    workgroups launched per compute unit (1..16)
+ *   groups_per_cu    workgroups launched per compute unit (1..16).  The pixel path
+ *                    launches no more than run at the same time.  A tile-path launch
+ *                    of few tiles (up to 12 a compute unit; not the matrix-core form)
+ *                    may give each tile to a workgroup of its own, of 2, 4 or 8
+ *                    wavefronts: waves_per_group, groups_per_cu and chunk then do
+ *                    not apply.
  *   xcd_queues       1: one shared work queue; 8: one queue per accelerator
  *                    die, each holding a contiguous block of tiles (a
  *                    workgroup starts on its die's queue and takes from the

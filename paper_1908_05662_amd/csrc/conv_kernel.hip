@@ -1225,64 +1225,132 @@ __device__ __forceinline__ PairOut tile_pairs(const typename Cond<QF, PixRecQ, P
     return o;
 }
 
+// Records of a step of consume_records: pairs whose beam loads are in flight together,
+// four for one-grid beams (one 16-byte cell record each), two for four-channel beams
+// (four node records each), so that a step's loaded records stay in registers.
+__host__ __device__ constexpr int step_records(int beam) { return beam == BEAM_SCALAR ? TILE_NP : 2; }
+
+// Where consume_records puts its FP32 pre-sums: into the lane's FP64 sums, or, in a
+// tile that waves share, into LDS until the wave's turn to add them (see convolve_tile).
+struct SumsHere {
+    AccWide &a0, &a1, &a2, &an;
+    template <int MODE, bool PS>
+    __device__ inline void add(float v0, float v1, float v2, float vn) {
+        a0.add(v0);
+        if (MODE == MODE_STOKES) {
+            a1.add(v1);
+            a2.add(v2);
+        }
+        if (PS) an.add(vn);
+    }
+};
+__host__ __device__ constexpr int sum_count(int mode, bool ps) { return (mode == MODE_STOKES ? 3 : 1) + (ps ? 1 : 0); }
+template <int BEAM>
+struct SumsShared {
+    // the lane's words of the next group: sum 0 over its own records where they take
+    // more than its 256 bytes (they and the groups before are done with), the others,
+    // [group][sum][lane], behind the records
+    float *first, *rest;
+    static constexpr bool IN_PLACE = BEAM == BEAM_SCALAR;
+    template <int MODE, bool PS>
+    __device__ inline void add(float v0, float v1, float v2, float vn) {
+        const float v[4] = {v0, MODE == MODE_STOKES ? v1 : vn, v2, vn};
+        put<sum_count(MODE, PS)>(v);
+    }
+    template <int N>
+    __device__ inline void put(const float *v) {
+        if (IN_PLACE) {
+            *first = v[0];
+            first += WAVE;
+        }
+#pragma unroll
+        for (int k = IN_PLACE ? 1 : 0; k < N; ++k) {
+            *rest = v[k];
+            rest += WAVE;
+        }
+    }
+    // sum k of group j, of N
+    template <int N>
+    __device__ inline float get(int j, int k) const {
+        return IN_PLACE && k == 0 ? first[j * WAVE] : rest[(j * (N - IN_PLACE) + k - IN_PLACE) * WAVE];
+    }
+};
+
 // Every lane (sample) against the staged records [0, m_end): TILE_NP records
 // per step, then the remainder one by one.  CLIP (the disc-versus-grid test)
 // and INNER (the inner-disc test of an annulus) are uniform per detector and
 // template switches, so the common case runs a loop without either.
-template <int MODE, int BEAM, bool PS, bool HWP, bool CLIP, bool INNER, int SC = 0, bool QF = false>
+template <int MODE, int BEAM, bool PS, bool HWP, bool CLIP, bool INNER, int SC = 0, bool QF = false, class Sums>
 __device__ __forceinline__ void consume_records(const typename Cond<QF, PixRecQ, PixRec>::type *rec,
                                                 const float *vrec, int32_t m_end, const PairCtx &C,
-                                                const BeamRsrc &beam, const BeamRsrc &vbeam, AccWide &acc0,
-                                                AccWide &acc1, AccWide &acc2, AccWide &accn) {
-    // pairs whose beam loads are in flight together: four for one-grid beams (one
-    // 16-byte cell record each), two for four-channel beams (four node records
-    // each), so that a step's loaded records stay in registers
-    constexpr int NP = BEAM == BEAM_SCALAR ? TILE_NP : 2;
+                                                const BeamRsrc &beam, const BeamRsrc &vbeam, Sums &sums) {
+    constexpr int NP = step_records(BEAM);
     int32_t m = 0;
-    // two groups per compensated add: 2 NP masked terms summed in FP32
+    // two groups per FP64 add: 2 NP masked terms summed in FP32
     for (; m + 2 * NP - 1 < m_end; m += 2 * NP) {
         const PairOut a = tile_pairs<MODE, BEAM, PS, NP, HWP, CLIP, INNER, SC, QF>(
             &rec[m], vrec ? &vrec[m] : nullptr, C, beam, vbeam);
         const PairOut b = tile_pairs<MODE, BEAM, PS, NP, HWP, CLIP, INNER, SC, QF>(
             &rec[m + NP], vrec ? &vrec[m + NP] : nullptr, C, beam, vbeam);
-        acc0.add(a.v0 + b.v0);
-        if (MODE == MODE_STOKES) {
-            acc1.add(a.v1 + b.v1);
-            acc2.add(a.v2 + b.v2);
-        }
-        if (PS) accn.add(a.vn + b.vn);
+        sums.template add<MODE, PS>(a.v0 + b.v0, a.v1 + b.v1, a.v2 + b.v2, a.vn + b.vn);
     }
     for (; m + NP - 1 < m_end; m += NP) {
         const PairOut a = tile_pairs<MODE, BEAM, PS, NP, HWP, CLIP, INNER, SC, QF>(
             &rec[m], vrec ? &vrec[m] : nullptr, C, beam, vbeam);
-        acc0.add(a.v0);
-        if (MODE == MODE_STOKES) {
-            acc1.add(a.v1);
-            acc2.add(a.v2);
-        }
-        if (PS) accn.add(a.vn);
+        sums.template add<MODE, PS>(a.v0, a.v1, a.v2, a.vn);
     }
     for (; m < m_end; ++m) {
         const PairOut a = tile_pairs<MODE, BEAM, PS, 1, HWP, CLIP, INNER, SC, QF>(&rec[m], vrec ? &vrec[m] : nullptr, C,
                                                                               beam, vbeam);
-        acc0.add(a.v0);
-        if (MODE == MODE_STOKES) {
-            acc1.add(a.v1);
-            acc2.add(a.v2);
-        }
-        if (PS) accn.add(a.vn);
+        sums.template add<MODE, PS>(a.v0, a.v1, a.v2, a.vn);
     }
 }
 
-// SHARE: the waves of a workgroup share the tile: wave `part` takes every
-// parts-th chunk of each ring batch (the groups of records whose terms are summed in
-// FP32 stay the same; only the FP64 sums are split), and the first wave adds the
-// waves' sums in order.  L is this wave's slice, the others' lie beside it.  (A form
+// LDS of a launch that shares tiles: per wave a slice of rings, records of a 64-record
+// chunk and the chunk's pre-sums (the lane frames overlay these two; one-grid beams keep
+// one pre-sum over the records, so that a CU holds as many waves as it does of an
+// unshared launch); per workgroup the tile's sums and whose turn it is to add to them.
+constexpr int SHARE_CH = 64;
+constexpr int SHARE_SUMS_OFF = 4352 + SHARE_CH * (int)sizeof(PixRec);
+__host__ __device__ constexpr int share_slice(int mode, int beam, bool ps) {
+    const int words = SHARE_CH / (2 * step_records(beam)) * (sum_count(mode, ps) - (beam == BEAM_SCALAR ? 1 : 0)) * WAVE;
+    const int sums = words * 4, least = sizeof(TileLds<SHARE_CH>);
+    return mode == MODE_COUNT || SHARE_SUMS_OFF + sums < least ? least : SHARE_SUMS_OFF + sums;
+}
+__host__ __device__ constexpr int share_block(int mode, bool ps) { return 16 + sum_count(mode, ps) * WAVE * 8; }
+// The workgroup's block: the turn, then [sum][lane] in FP64 (pair counts: [lane]).
+struct ShareTurn {
+    int32_t turn, pad[3];
+    double sum[1];
+};
+
+// Waits until the workgroup's chunks before number c are added.  They are the chunks of
+// the wave's own and its workgroup's other waves, which run at the same time; each wave
+// takes its chunks in order and waits for lower numbers only, so the wave with the lowest
+// number never waits.
+__device__ inline void wait_turn(ShareTurn *B, int32_t c) {
+    while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&B->turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != c)
+        __builtin_amdgcn_s_sleep(1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+__device__ inline void pass_turn(ShareTurn *B, int32_t c, int lane) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    if (lane == 0) __hip_atomic_store(&B->turn, c + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// SHARE: the waves of a workgroup share the tile, wave `part` every parts-th chunk of
+// records.  The value of a sample is that of an unshared launch, bit for bit, for any
+// number of waves: the pre-sums of a chunk are the same, and they are added in FP64 in
+// the same order, the running sums going from wave to wave with the turn (LDS; `chunk0`
+// counts the workgroup's chunks).  A turn takes a few hundred clocks and the waves take
+// theirs one after the other while the rest work on their chunks.  (FP64 sums by wave,
+// added at the end, made a value depend on the number of tiles in its launch.)  A form
 // of its own: carried as run-time values the sharing took the pair loop of unshared
-// launches from 11 to 24 spilled registers.)
+// launches from 11 to 24 spilled registers.
 template <int MODE, int BEAM, int CH, bool PS, bool HWP, bool SHARE>
 __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin, int32_t cnt, TileLds<CH> &L,
-                              float *vrec, int lane, int32_t part, int32_t parts) {
+                              float *vrec, int lane, int32_t part, int32_t parts, ShareTurn *B, int32_t &chunk0) {
     static_assert(CH % WAVE == 0, "chunks are whole waves of records");
     const float4 *__restrict__ sky = reinterpret_cast<const float4 *>(A.sky);
     const int32_t N = (int32_t)A.nside;
@@ -1346,7 +1414,9 @@ __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin
     const float ih2 = (float)(D.inv_h * D.inv_h);
 
     AccWide acc0, acc1, acc2, accn;
+    SumsHere here{acc0, acc1, acc2, accn};
     int32_t npairs = 0;
+    int32_t done = 0;        // SHARE: chunks of the ring batches before
 
     const int32_t r_lo = __builtin_amdgcn_readfirstlane(T.r_lo), r_hi = __builtin_amdgcn_readfirstlane(T.r_hi);
 
@@ -1372,7 +1442,7 @@ __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin
         // ring of the chunk's first record, or an earlier one: each lane's search
         // starts there instead of at the batch's first ring
         int32_t seg0 = 0;
-        for (int32_t pb = SHARE ? part * CH : 0; pb < total; pb += SHARE ? parts * CH : CH) {
+        for (int32_t pb = SHARE ? ((part - done) & (parts - 1)) * CH : 0; pb < total; pb += SHARE ? parts * CH : CH) {
             const int32_t m_end = min(CH, total - pb);
             // fill: one pixel record per lane, FP32 differences from the centre
             int32_t seg = seg0;
@@ -1454,92 +1524,100 @@ __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin
             // the wave; only the batch's last chunk is partial)
             seg0 = __builtin_amdgcn_readlane(seg, WAVE - 1);
             wave_sync();
-
-            // consume: every lane (sample) against every staged pixel
-            if (valid) {
-                if (MODE == MODE_COUNT) {
+            // consume: every lane (sample) against every staged pixel of [m0, m1)
+            const float *vr = has_v ? vrec : nullptr;
+            auto consume = [&](int32_t m0, int32_t m1, auto &sums) {
+                const PairCtx C{Fg, omax, omin, clip, inv_h, c0 + ringoff, tmax + ringoff, cmax, row, row_bytes,
+                                sg4, (float)(n - 1), ringoff, (uint32_t)row};
+                const float *vm = vr ? vr + m0 : nullptr;
+                const int32_t m = m1 - m0;
+                if constexpr (MODE == MODE_TOD && BEAM == BEAM_SCALAR) {
+                    if (qf) {
+                        const PixRecQ *rq = reinterpret_cast<const PixRecQ *>(L.rec) + m0;
+                        if (tiny_q)
+                            consume_records<MODE, BEAM, PS, HWP, false, false, 2, true>(rq, vm, m, C, beam, vbeam, sums);
+                        else if (small_q)
+                            consume_records<MODE, BEAM, PS, HWP, false, false, 1, true>(rq, vm, m, C, beam, vbeam, sums);
+                        else
+                            consume_records<MODE, BEAM, PS, HWP, false, false, 0, true>(rq, vm, m, C, beam, vbeam, sums);
+                        return;
+                    }
+                }
+                const PixRec *rec = L.rec + m0;
+                if (clip) {
+                    if (inner)
+                        consume_records<MODE, BEAM, PS, HWP, true, true>(rec, vm, m, C, beam, vbeam, sums);
+                    else
+                        consume_records<MODE, BEAM, PS, HWP, true, false>(rec, vm, m, C, beam, vbeam, sums);
+                } else {
+                    if (inner)
+                        consume_records<MODE, BEAM, PS, HWP, false, true>(rec, vm, m, C, beam, vbeam, sums);
+                    else if (tiny_cap)
+                        consume_records<MODE, BEAM, PS, HWP, false, false, 2>(rec, vm, m, C, beam, vbeam, sums);
+                    else if (small_cap)
+                        consume_records<MODE, BEAM, PS, HWP, false, false, 1>(rec, vm, m, C, beam, vbeam, sums);
+                    else
+                        consume_records<MODE, BEAM, PS, HWP, false, false>(rec, vm, m, C, beam, vbeam, sums);
+                }
+            };
+            if constexpr (MODE == MODE_COUNT) {
+                if (SHARE) npairs = 0;
+                if (valid) {
                     for (int32_t m = 0; m < m_end; ++m) {
                         const PixRec R = L.rec[m];
                         const float omg = fmaf(-R.Y, F.p2, fmaf(-R.X, F.p1, fmaf(R.W, F.p3, F.om)));
                         npairs += ((omg <= omax) & (omg > omin)) ? 1 : 0;
                     }
-                } else {
-                    // two records per step: their masked terms are added in FP32
-                    // and the pair enters the compensated sums (halves the
-                    // compensation work; each pre-sum rounds once)
-                    const PairCtx C{Fg, omax, omin, clip, inv_h, c0 + ringoff, tmax + ringoff, cmax, row, row_bytes,
-                                    sg4, (float)(n - 1), ringoff, (uint32_t)row};
-                    const float *vr = has_v ? vrec : nullptr;
-                    if constexpr (MODE == MODE_TOD && BEAM == BEAM_SCALAR) {
-                        if (qf) {
-                            const PixRecQ *rq = reinterpret_cast<const PixRecQ *>(L.rec);
-                            if (tiny_q)
-                                consume_records<MODE, BEAM, PS, HWP, false, false, 2, true>(rq, vr, m_end, C, beam, vbeam,
-                                                                                            acc0, acc1, acc2, accn);
-                            else if (small_q)
-                                consume_records<MODE, BEAM, PS, HWP, false, false, 1, true>(rq, vr, m_end, C, beam, vbeam,
-                                                                                            acc0, acc1, acc2, accn);
-                            else
-                                consume_records<MODE, BEAM, PS, HWP, false, false, 0, true>(rq, vr, m_end, C, beam, vbeam,
-                                                                                            acc0, acc1, acc2, accn);
-                            goto consumed;
-                        }
-                    }
-                    if (clip) {
-                        if (inner)
-                            consume_records<MODE, BEAM, PS, HWP, true, true>(L.rec, vr, m_end, C, beam, vbeam, acc0,
-                                                                             acc1, acc2, accn);
-                        else
-                            consume_records<MODE, BEAM, PS, HWP, true, false>(L.rec, vr, m_end, C, beam, vbeam, acc0,
-                                                                              acc1, acc2, accn);
-                    } else {
-                        if (inner)
-                            consume_records<MODE, BEAM, PS, HWP, false, true>(L.rec, vr, m_end, C, beam, vbeam, acc0,
-                                                                              acc1, acc2, accn);
-                        else if (tiny_cap)
-                            consume_records<MODE, BEAM, PS, HWP, false, false, 2>(L.rec, vr, m_end, C, beam, vbeam,
-                                                                                  acc0, acc1, acc2, accn);
-                        else if (small_cap)
-                            consume_records<MODE, BEAM, PS, HWP, false, false, 1>(L.rec, vr, m_end, C, beam, vbeam,
-                                                                                  acc0, acc1, acc2, accn);
-                        else
-                            consume_records<MODE, BEAM, PS, HWP, false, false>(L.rec, vr, m_end, C, beam, vbeam, acc0,
-                                                                               acc1, acc2, accn);
-                    }
                 }
+                if constexpr (SHARE) {
+                    const int32_t c = chunk0 + done + pb / CH;
+                    int32_t *count = reinterpret_cast<int32_t *>(B->sum) + lane;
+                    wait_turn(B, c);
+                    if (c != chunk0) npairs += *count;
+                    *count = npairs;
+                    pass_turn(B, c, lane);
+                }
+            } else if constexpr (SHARE) {
+                constexpr int NSUM = sum_count(MODE, PS), GR = 2 * step_records(BEAM);
+                const int32_t full = m_end / GR * GR, c = chunk0 + done + pb / CH;
+                const SumsShared<BEAM> mine{
+                    reinterpret_cast<float *>(L.rec) + lane,
+                    reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(&L) + SHARE_SUMS_OFF) + lane};
+                SumsShared<BEAM> there = mine;
+                if (valid) consume(0, full, there);
+                wave_sync();
+                float x[CH / GR][NSUM];
+#pragma unroll
+                for (int j = 0; j < CH / GR; ++j)
+#pragma unroll
+                    for (int k = 0; k < NSUM; ++k) x[j][k] = mine.template get<NSUM>(j, k);
+                AccWide *const acc[4] = {&acc0, MODE == MODE_STOKES ? &acc1 : &accn, &acc2, &accn};
+                wait_turn(B, c);
+#pragma unroll
+                for (int k = 0; k < NSUM; ++k) acc[k]->s = c == chunk0 ? 0.0 : B->sum[k * WAVE + lane];
+#pragma unroll
+                for (int j = 0; j < CH / GR; ++j)
+                    if (j * GR < full) {
+#pragma unroll
+                        for (int k = 0; k < NSUM; ++k) acc[k]->add(x[j][k]);
+                    }
+                // (fewer records than a group: the end of the tile's last chunk or a batch's)
+                if (valid && full < m_end) consume(full, m_end, here);
+#pragma unroll
+                for (int k = 0; k < NSUM; ++k) B->sum[k * WAVE + lane] = acc[k]->s;
+                pass_turn(B, c, lane);
+            } else {
+                if (valid) consume(0, m_end, here);
             }
-        consumed:
             wave_sync();
         }
+        if (SHARE) done += (total + CH - 1) / CH;
     }
 
     if constexpr (SHARE) {
-        // the waves' sums meet in their own slices (free now)
-        struct Sums {
-            double a0[WAVE], a1[WAVE], a2[WAVE], an[WAVE];
-            int32_t np[WAVE];
-        };
-        static_assert(sizeof(Sums) <= sizeof(TileLds<CH>), "the sums fit a slice");
-        Sums &mine = reinterpret_cast<Sums &>(L);
-        wave_sync();
-        mine.a0[lane] = acc0.s;
-        mine.a1[lane] = acc1.s;
-        mine.a2[lane] = acc2.s;
-        mine.an[lane] = accn.s;
-        mine.np[lane] = npairs;
-        __syncthreads();
-        if (part == 0) {
-            for (int32_t w = 1; w < parts; ++w) {
-                const Sums &o = reinterpret_cast<const Sums &>(*(&L + w));
-                acc0.s += o.a0[lane];
-                acc1.s += o.a1[lane];
-                acc2.s += o.a2[lane];
-                accn.s += o.an[lane];
-                npairs += o.np[lane];
-            }
-        }
-        __syncthreads();   // the next tile overwrites the slices
-        if (part != 0) return;
+        // the wave of the tile's last chunk holds its sums
+        chunk0 += done;
+        if (part != (done ? (done - 1) & (parts - 1) : 0)) return;
     }
     if (!valid) return;
     float *out = reinterpret_cast<float *>(A.out);
@@ -2005,31 +2083,39 @@ __global__ void __launch_bounds__(512, (tile_min_waves<MODE, BEAM>())) tile_kern
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    TileLds<CH> &L = reinterpret_cast<TileLds<CH> *>(lds_raw)[wid];
+    constexpr int SLICE = SHARE ? share_slice(MODE, BEAM, PS) : (int)sizeof(TileLds<CH>);
+    TileLds<CH> &L = *reinterpret_cast<TileLds<CH> *>(lds_raw + wid * SLICE);
     float *vrec = (BEAM == BEAM_FULL && MODE == MODE_TOD && A.vbeam)
-                      ? reinterpret_cast<float *>(lds_raw + sizeof(TileLds<CH>) * (blockDim.x / WAVE)) + wid * CH
+                      ? reinterpret_cast<float *>(lds_raw + SLICE * (blockDim.x / WAVE)) + wid * CH
                       : nullptr;
     if constexpr (SHARE) {
-        // the workgroup takes every gridDim-th tile, counted through the queues one after
+        // a workgroup a tile (or every gridDim-th), counted through the queues one after
         // the other: no pops, and as many workgroups at work for any number of queues
         // (each queue counted from its start, the first eighth of the workgroups took all
         // tiles of eight queues: 1024 tiles of 2 deg discs, nside 1024, 1341 us against 347)
         const int32_t part = wid, parts = (int32_t)(blockDim.x / WAVE);
+        const int32_t block = (SLICE + (vrec ? 4 * CH : 0)) * parts;
+        ShareTurn *B = reinterpret_cast<ShareTurn *>(lds_raw + block);
+        if (threadIdx.x == 0) B->turn = 0;
+        __syncthreads();
+        int32_t chunk0 = 0;
         int32_t i = (int32_t)blockIdx.x;
         for (int32_t q = 0; q < A.n_queues; ++q) {
             const int32_t len = A.queue_len[q];
             for (; i < len; i += (int32_t)gridDim.x) {
                 const Tile tl = A.tiles[(int64_t)q * A.tiles_per_queue + i];
                 convolve_tile<MODE, BEAM, CH, PS, HWP, true>(A, A.dets[tl.det], tl.begin, tl.count, L, vrec, lane, part,
-                                                             parts);
+                                                             parts, B, chunk0);
             }
             i -= len;
         }
     } else {
         TileWalk<1> walk(A, wid);
         Tile tl;
+        int32_t chunk0 = 0;
         while (walk.next(A, lane, tl))
-            convolve_tile<MODE, BEAM, CH, PS, HWP, false>(A, A.dets[tl.det], tl.begin, tl.count, L, vrec, lane, 0, 1);
+            convolve_tile<MODE, BEAM, CH, PS, HWP, false>(A, A.dets[tl.det], tl.begin, tl.count, L, vrec, lane, 0, 1,
+                                                          nullptr, chunk0);
     }
 }
 
@@ -2206,19 +2292,42 @@ hipError_t launch_zero_counters(int32_t *counters, int n, hipStream_t s) {
     return hipGetLastError();
 }
 
-// A wave takes a tile, and four waves fit a SIMD: with fewer tiles than that the chip
-// is partly idle and the time is one wave's walk through one tile.  Then 8, 4 or 2
-// waves share each tile (each does the tile's set-up again).  Measured at nside
-// 1024, 2 deg, one-grid beams, us for T tiles with 1 / 2 / 4 / 8 waves a tile: T = 64:
-// 602 / 306 / 171 / 118; 256: 632 / 318 / 183 / 133; 512: 644 / 336 / 213 / 209; 1024:
-// 715 / 371 / 347 / 397; 2048: 1088 / 633 / 675 / 797; and with 1 / 2 waves, 3072: 910 /
-// 889; 3584: 1074 / 1174; 4096: 1133 / 1215; 5120: 1465 / 1469 (256 compute units;
-// four-channel beams, Stokes pickups and 6 deg discs cross at the same places).
+// A wave takes a tile, and a CU holds 16 waves of one-grid TODs, 8 of the forms with more
+// registers: with fewer tiles than that the chip is partly idle and the time is one
+// wave's walk through one tile.  Then 8, 4 or 2 waves share each tile (each does the
+// tile's set-up again, and its chunks wait their turn).  us with 1 / 2 / 4 / 8 waves a
+// tile, for T tiles on 256 compute units:
+//   one-grid TOD, nside 1024, 2 deg   256: 530 329 181 125; 512: 532 351 204 192;
+//     1024: 551 357 330 367; 1280: 605 434 433 457; 1792: 618 565 550 626;
+//     2048: 617 593 623 712; 2560: 785 847 764 881; 3072: 844 946 907 1051
+//   the same, nside 512               1024: 150 107 109 136; 1792: 168 166 181 227;
+//     2048: 170 173 203 258; 2304: 211 231 234 288; 3072: 231 275 295 381
+//   four channels, nside 512, 2 deg   256: 239 146 94 79; 512: 240 157 129 150;
+//     1024: 241 198 233 294; 1536: 391 370 349 446; 2048: 383 470 450 574;
+//     2304: 550 513 531 648; 2816: 670 553 629 796; 3072: 684 639 671 872
+//   Stokes, annulus 5 to 20 deg, nside 256 (8 waves do not fit)   256: 4074 2283 1173;
+//     512: 4084 2651 1396; 1024: 4063 2708 2726; 1536: 4870 5349 4036; 2048: 4858 6935
+//     5346; 2304: 8552 7148 6081; 2816: 8453 7962 7344; 3072: 8436 9252 7947
+// So: as many waves as fit at once (4 up to four tiles a unit for the larger forms too,
+// where tiles differ: an annulus at random pointings, 900 tiles, 6.5 ms, with 2 waves
+// 7.6), and for the larger forms also where one wave a tile would leave a second round
+// mostly empty (5, 6 and 9 to 11 tiles a unit, 12 of four-channel TOD).  LDS has its say
+// (Stokes pickups of four channels with per-sample normalisation: at most 4 waves, and 4
+// only for one tile a unit).
 void share_tiles(ConvArgs &a, int64_t n, int num_cu) {
-    // (the matrix-core path's waves take a tile each)
-    const int w = a.algo != ALGO_TILE ? 0 : n <= num_cu ? 8 : n <= 4 * num_cu ? 4 : n <= 12 * num_cu ? 2 : 0;
+    a.share_tiles = a.share_groups = 0;
+    if (a.algo != ALGO_TILE || n > 12LL * num_cu) return;   // (the matrix-core path's waves take a tile each)
+    const int slice = share_slice(a.out_mode, a.beam_kind, a.per_sample != 0) +
+                      (a.beam_kind == BEAM_FULL && a.out_mode == MODE_TOD && a.vbeam ? 4 * SHARE_CH : 0);
+    const int block = share_block(a.out_mode, a.per_sample != 0);
+    auto fit = [&](int w) { return 160 * 1024 / (w * slice + block); };   // workgroups of w waves that LDS holds
+    const bool large = a.out_mode == MODE_STOKES || (a.out_mode == MODE_TOD && a.beam_kind == BEAM_FULL);
+    const int u = (int)((n + num_cu - 1) / num_cu);
+    const bool fours = fit(4) >= (large ? 2 : 4);
+    int w = u <= 1 && fit(8) >= 1 ? 8 : u <= 1 || (u <= 4 && fours) ? 4 : u <= (large ? 4 : 8) ? 2 : 0;
+    if (large && u > 4) w = u <= 6 ? (fours ? 4 : 2) : u > 8 && u <= (a.out_mode == MODE_TOD ? 12 : 11) ? 2 : 0;
     a.share_tiles = w;
-    a.share_groups = w ? (int32_t)std::min<int64_t>(n, (int64_t)num_cu * (16 / w)) : 0;
+    a.share_groups = w ? (int32_t)n : 0;   // a workgroup a tile
 }
 
 template <typename T, int MODE>
@@ -2234,7 +2343,8 @@ static hipError_t launch_pixel(const ConvArgs &a, int waves, int groups, hipStre
 template <int MODE, int BEAM, int CH, bool PS, bool HWP, bool SHARE>
 static hipError_t launch_tile_s(const ConvArgs &a, int waves, int groups, hipStream_t s) {
     const bool v = BEAM == BEAM_FULL && MODE == MODE_TOD && a.vbeam;
-    const size_t lds = (sizeof(TileLds<CH>) + (v ? sizeof(float) * CH : 0)) * (size_t)waves;
+    const size_t slice = SHARE ? share_slice(MODE, BEAM, PS) : sizeof(TileLds<CH>);
+    const size_t lds = (slice + (v ? sizeof(float) * CH : 0)) * (size_t)waves + (SHARE ? share_block(MODE, PS) : 0);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     if (lds > 64 * 1024) {  // allow the larger LDS allocations of gfx950 (160 KiB per CU)
         const hipError_t e =
@@ -2249,7 +2359,7 @@ static hipError_t launch_tile_s(const ConvArgs &a, int waves, int groups, hipStr
 // A launch that shares tiles stages 64 records at a time, the finest split.
 template <int MODE, int BEAM, int CH, bool PS, bool HWP>
 static hipError_t launch_tile_h(const ConvArgs &a, int waves, int groups, hipStream_t s) {
-    if (a.share_tiles) return launch_tile_s<MODE, BEAM, 64, PS, HWP, true>(a, a.share_tiles, a.share_groups, s);
+    if (a.share_tiles) return launch_tile_s<MODE, BEAM, SHARE_CH, PS, HWP, true>(a, a.share_tiles, a.share_groups, s);
     return launch_tile_s<MODE, BEAM, CH, PS, HWP, false>(a, waves, groups, s);
 }
 
