@@ -2053,7 +2053,10 @@ template <int OWN> struct TileWalk {
     }
 };
 
-template <typename T, int MODE, int BEAM>
+// ROWS: four samples a wave, for detectors with small discs (DetDesc::pixel_rows, of
+// every tile of the launch).  Two kernels: in one, the form with a sample a wave kept
+// the other's registers and code (8 to 10 spilled in FP32) and ran 5 to 15% longer.
+template <typename T, int MODE, int BEAM, bool ROWS>
 __global__ void __launch_bounds__(512, (pixel_waves_per_simd(sizeof(T) == 8))) conv_kernel(ConvArgs A) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int lane = threadIdx.x & (WAVE - 1);
@@ -2065,15 +2068,15 @@ __global__ void __launch_bounds__(512, (pixel_waves_per_simd(sizeof(T) == 8))) c
         const DetDesc &D = A.dets[tl.det];
         const int64_t end = tl.begin + tl.count;
         PixTile P{};
-        if (!D.pixel_rows) {
+        if constexpr (ROWS) {
+            sincos(D.zeta, &P.sz, &P.cz);
+            P.sr = sqrt(D.omega_max * (2.0 - D.omega_max));
+            for (int64_t t = tl.begin; t < end; t += 4) {
+                const int64_t mine = t + lane / 16;
+                convolve_sample<T, MODE, BEAM, 16>(A, D, P, min(mine, end - 1), mine < end, L, lane);
+            }
+        } else {
             for (int64_t t = tl.begin; t < end; ++t) convolve_sample<T, MODE, BEAM, WAVE>(A, D, P, t, true, L, lane);
-            continue;
-        }
-        sincos(D.zeta, &P.sz, &P.cz);
-        P.sr = sqrt(D.omega_max * (2.0 - D.omega_max));
-        for (int64_t t = tl.begin; t < end; t += 4) {
-            const int64_t mine = t + lane / 16;
-            convolve_sample<T, MODE, BEAM, 16>(A, D, P, min(mine, end - 1), mine < end, L, lane);
         }
     }
 }
@@ -2330,14 +2333,20 @@ void share_tiles(ConvArgs &a, int64_t n, int num_cu) {
     a.share_groups = w ? (int32_t)n : 0;   // a workgroup a tile
 }
 
+template <typename T, int MODE, int BEAM>
+static hipError_t launch_pixel_b(const ConvArgs &a, int waves, int groups, hipStream_t s) {
+    const size_t lds = sizeof(WaveLds<T>) * (size_t)waves;
+    if (a.pixel_rows)
+        hipLaunchKernelGGL((conv_kernel<T, MODE, BEAM, true>), dim3(groups), dim3(WAVE * waves), lds, s, a);
+    else
+        hipLaunchKernelGGL((conv_kernel<T, MODE, BEAM, false>), dim3(groups), dim3(WAVE * waves), lds, s, a);
+    return hipGetLastError();
+}
+
 template <typename T, int MODE>
 static hipError_t launch_pixel(const ConvArgs &a, int waves, int groups, hipStream_t s) {
-    const size_t lds = sizeof(WaveLds<T>) * (size_t)waves;
-    if (a.beam_kind == BEAM_FULL)
-        hipLaunchKernelGGL((conv_kernel<T, MODE, BEAM_FULL>), dim3(groups), dim3(WAVE * waves), lds, s, a);
-    else
-        hipLaunchKernelGGL((conv_kernel<T, MODE, BEAM_SCALAR>), dim3(groups), dim3(WAVE * waves), lds, s, a);
-    return hipGetLastError();
+    return a.beam_kind == BEAM_FULL ? launch_pixel_b<T, MODE, BEAM_FULL>(a, waves, groups, s)
+                                    : launch_pixel_b<T, MODE, BEAM_SCALAR>(a, waves, groups, s);
 }
 
 template <int MODE, int BEAM, int CH, bool PS, bool HWP, bool SHARE>
@@ -2564,7 +2573,7 @@ void *static_scratch(int device) {
 }
 
 hipError_t launch_static(ConvArgs tile, ConvArgs pix, const DetDesc &D, bool tile_path, bool f64, int waves,
-                         int groups, int num_cu, void *base, hipStream_t s) {
+                         int groups, int pixel_groups, int num_cu, void *base, hipStream_t s) {
     unsigned char *b = static_cast<unsigned char *>(base);
     int32_t *ctrl = reinterpret_cast<int32_t *>(b);
     const int64_t ng = (D.n_samples + WAVE - 1) / WAVE;
@@ -2590,12 +2599,14 @@ hipError_t launch_static(ConvArgs tile, ConvArgs pix, const DetDesc &D, bool til
     pix.tiles = reinterpret_cast<const Tile *>(b + STATIC_PQ_OFF);
     pix.counters = ctrl + 16;
     pix.queue_len = ctrl + 24;
+    // (at most ng tiles, a wave each, in either queue)
+    const int most = (int)((ng + waves - 1) / waves);
     if (tile_path) {
         share_tiles(tile, ng, num_cu);
-        e = launch_conv(tile, f64, waves, (int)std::min<int64_t>(groups, ng), s);
+        e = launch_conv(tile, f64, waves, std::min(groups, most), s);
         if (e != hipSuccess) return e;
     }
-    return launch_conv(pix, f64, waves, (int)std::min<int64_t>(groups, ng * WAVE), s);
+    return launch_conv(pix, f64, waves, std::min(pixel_groups, most), s);
 }
 
 }  // namespace pisco

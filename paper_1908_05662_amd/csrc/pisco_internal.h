@@ -47,9 +47,8 @@ struct DetDesc {
 constexpr int32_t pixel_rows(int64_t nside, double rho_max) {
     return 3.0 * (double)nside * rho_max <= 16.0 ? 1 : 0;
 }
-// Waves of the pixel path that a compute unit holds at once (set by its registers).
+// Waves of the pixel path that a SIMD holds at once (set by its registers).
 constexpr int pixel_waves_per_simd(bool f64) { return f64 ? 2 : 3; }
-constexpr int pixel_waves_per_cu(bool f64) { return 4 * pixel_waves_per_simd(f64); }
 
 // A tile: `count` consecutive samples of detector `det` starting at `begin`.
 struct Tile {
@@ -76,6 +75,7 @@ struct ConvArgs {
     int32_t per_sample;      // some detector of the launch uses per-sample normalisation
     int32_t hwp;             // some detector of the launch has a half-wave plate
     int32_t vbeam;           // some detector of the launch has a full beam with a V column
+    int32_t pixel_rows;      // pixel path: the launch's detectors take four samples a wave
     int32_t share_tiles;     // tile path: waves that share a tile (0: a wave takes a tile)
     int32_t share_groups;    // workgroups of a launch that shares tiles
 };
@@ -124,7 +124,7 @@ void *static_scratch(int device);
 // device, then run the tile and pixel kernels with args tile / pix (their plan
 // pointers are filled in here).
 hipError_t launch_static(ConvArgs tile, ConvArgs pix, const DetDesc &D, bool tile_path, bool f64, int waves,
-                         int groups, int num_cu, void *base, hipStream_t s);
+                         int groups, int pixel_groups, int num_cu, void *base, hipStream_t s);
 
 }  // namespace pisco
 

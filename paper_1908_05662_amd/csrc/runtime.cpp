@@ -92,6 +92,10 @@ struct SlApply {
     double coef[3];
 };
 
+// What a tile of samples runs through: the tile path (coherent 64-sample groups), the
+// pixel path with a sample a wave, the pixel path with four (DetDesc::pixel_rows).
+enum Path { PATH_TILE = 0, PATH_PIXEL = 1, PATH_ROWS = 2 };
+
 // A device-side launch plan: detector descriptors, the tile-path and
 // pixel-path work queues, and (for the batched plan) the captured graph.  The
 // context keeps one plan for single-detector launches and one for the batched
@@ -99,8 +103,8 @@ struct SlApply {
 struct Plan {
     DetDesc *d_dets = nullptr;
     size_t d_dets_cap = 0;
-    Queues tq, pq;              // tile path (coherent 64-sample groups), pixel path
-    int32_t *d_ctrl = nullptr;  // [0,8) tq counters, [8,16) tq lengths, [16,24) pq counters, [24,32) pq lengths
+    Queues q[3];                // by Path
+    int32_t *d_ctrl = nullptr;  // 8 counters and 8 lengths per path
     int32_t *d_scratch = nullptr;
     size_t scratch_cap = 0;     // bytes
     uint64_t gen = 0;
@@ -268,8 +272,7 @@ void drop_graph(Plan &p) {
 void free_plan(pisco_ctx *c, Plan &p) {
     drop_graph(p);
     dfree(c, p.d_dets);
-    dfree(c, p.tq.d_tiles);
-    dfree(c, p.pq.d_tiles);
+    for (Queues &q : p.q) dfree(c, q.d_tiles);
     dfree(c, p.d_ctrl);
     dfree(c, p.d_scratch);
     p = Plan();
@@ -399,7 +402,7 @@ DetDesc make_desc(const DetState &d, int64_t nside, bool sub) {
 
 // Workgroups of a pixel-path launch: those its registers let run at the same time.
 int32_t pixel_groups(const pisco_ctx *c) {
-    const int32_t fit = pisco::pixel_waves_per_cu(c->sky_dtype == PISCO_F64) / c->wpg;
+    const int32_t fit = 4 * pisco::pixel_waves_per_simd(c->sky_dtype == PISCO_F64) / c->wpg;
     return std::min(c->gpc, std::max<int32_t>(1, fit)) * c->num_cu;
 }
 
@@ -424,7 +427,7 @@ pisco_status build_plan(pisco_ctx *c, Plan &p, std::vector<DetDesc> &descs, cons
     if (e != hipSuccess) return fail(c, PISCO_EDEVICE, "synchronise failed: %s", hipGetErrorString(e));
     p.gen = 0;  // the plan is incomplete until the end of this function
     drop_graph(p);
-    if (!p.d_ctrl && !dmalloc(c, reinterpret_cast<void **>(&p.d_ctrl), 32 * sizeof(int32_t)))
+    if (!p.d_ctrl && !dmalloc(c, reinterpret_cast<void **>(&p.d_ctrl), 48 * sizeof(int32_t)))
         return fail(c, PISCO_ENOMEM, "plan allocation failed");
     if (!grow(c, &p.d_dets, &p.d_dets_cap, std::max<size_t>(descs.size(), 1)))
         return fail(c, PISCO_ENOMEM, "plan allocation failed");
@@ -501,47 +504,52 @@ pisco_status build_plan(pisco_ctx *c, Plan &p, std::vector<DetDesc> &descs, cons
         }
     }
     // pixel path: runs of incoherent groups of one detector merged, then cut into
-    // tiles of at most spt samples, and of fewer when the pixel path has fewer
-    // samples than twice the launch's waves hold at spt each (a wave takes one
-    // sample at a time, so small tiles spread a few incoherent groups -- scan
-    // discontinuities -- over the whole chip instead of a few waves)
-    int64_t pix_samples = 0;
-    for (size_t g = 0; g < groups.size(); ++g)
-        if (!flag[g]) pix_samples += groups[g].count;
-    // (under a memory budget at least 16 samples a tile: the block sizing allows
-    // about 2 bytes of queues per sample)
+    // equal tiles of at most spt samples, as many as fill whole rounds of the launch's
+    // waves: two at least (a wave takes one sample at a time, so small tiles spread a few
+    // incoherent groups -- scan discontinuities -- over the whole chip instead of a few
+    // waves; 400,000 FP32 samples of 2 deg discs at nside 512 in tiles of spt = 64, 2.03
+    // rounds: 3832 us, in three rounds 3195).  Samples of small discs go four at a time:
+    // whole steps of four, and one round at least.  (Under a memory budget at least 16
+    // samples a tile: the block sizing allows about 2 bytes of queues per sample.)
+    int64_t pix_samples[3] = {0, 0, 0};
+    auto path_of = [&](size_t g) { return flag[g] ? PATH_TILE : descs[groups[g].det].pixel_rows ? PATH_ROWS : PATH_PIXEL; };
+    for (size_t g = 0; g < groups.size(); ++g) pix_samples[path_of(g)] += groups[g].count;
     const int64_t waves = std::max<int64_t>(1, (int64_t)pixel_groups(c) * c->wpg);
     const int64_t min_pspt = c->budget > 0 ? 16 : 1;
-    // (samples of small discs go four at a time: whole steps of four, and a tile a wave)
-    bool rows = true;
-    for (const DetDesc &x : descs) rows = rows && x.pixel_rows;
-    int64_t pspt64 = rows ? ((pix_samples + waves - 1) / waves + 3) / 4 * 4 : (pix_samples + 2 * waves - 1) / (2 * waves);
-    pspt64 = std::max<int64_t>(min_pspt, pspt64);
-    const int32_t pspt = (int32_t)std::min<int64_t>(c->spt, pspt64);
-    std::vector<Tile> ttiles, ptiles;
+    auto pspt_of = [&](Path k) {
+        const int64_t n = pix_samples[k], full = waves * c->spt;
+        const int64_t all = waves * std::max<int64_t>(k == PATH_ROWS ? 1 : 2, (n + full - 1) / full);
+        const int64_t x = (n + all - 1) / all + (k == PATH_ROWS ? 3 : 0);
+        return (int32_t)std::min<int64_t>(c->spt, std::max<int64_t>(min_pspt, k == PATH_ROWS ? x / 4 * 4 : x));
+    };
+    const int32_t pspt[3] = {0, pspt_of(PATH_PIXEL), pspt_of(PATH_ROWS)};
+    std::vector<Tile> tiles[3];
     for (size_t g = 0; g < groups.size(); ++g) {
-        if (flag[g]) {
-            ttiles.push_back(groups[g]);
+        const Path k = path_of(g);
+        std::vector<Tile> &to = tiles[k];
+        if (k == PATH_TILE) {
+            to.push_back(groups[g]);
             continue;
         }
         Tile x = groups[g];
         while (x.count > 0) {
-            if (!ptiles.empty() && ptiles.back().det == x.det && ptiles.back().begin + ptiles.back().count == x.begin &&
-                ptiles.back().count < pspt) {
-                Tile &b = ptiles.back();
-                const int32_t take = std::min(pspt - b.count, x.count);
+            if (!to.empty() && to.back().det == x.det && to.back().begin + to.back().count == x.begin &&
+                to.back().count < pspt[k]) {
+                Tile &b = to.back();
+                const int32_t take = std::min(pspt[k] - b.count, x.count);
                 b.count += take;
                 x.begin += take;
                 x.count -= take;
             } else {
                 Tile t = x;
-                t.count = std::min(pspt, x.count);
-                ptiles.push_back(t);
+                t.count = std::min(pspt[k], x.count);
+                to.push_back(t);
                 x.begin += t.count;
                 x.count -= t.count;
             }
         }
     }
+    std::vector<Tile> &ttiles = tiles[PATH_TILE];
     // each detector's coherent tiles in the Hilbert order of their first samples:
     // tiles that run at the same time then share more of their union caps in
     // L2 (the order of tiles does not change any output)
@@ -562,18 +570,18 @@ pisco_status build_plan(pisco_ctx *c, Plan &p, std::vector<DetDesc> &descs, cons
         ttiles.swap(sorted);
     }
     const int nq = std::max<int32_t>(1, std::min<int32_t>(c->xq, 8));
-    int32_t lens[32] = {0};
-    std::vector<Tile> tq, pq;
-    fill_queues(ttiles, nq, tq, lens + 8, p.tq.per);
-    fill_queues(ptiles, nq, pq, lens + 24, p.pq.per);
-    if (!grow(c, &p.tq.d_tiles, &p.tq.cap, tq.size()) || !grow(c, &p.pq.d_tiles, &p.pq.cap, pq.size()))
-        return fail(c, PISCO_ENOMEM, "plan allocation failed");
-    HIP_TRY(c, hipMemcpy(p.tq.d_tiles, tq.data(), tq.size() * sizeof(Tile), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(p.pq.d_tiles, pq.data(), pq.size() * sizeof(Tile), hipMemcpyHostToDevice));
+    int32_t lens[48] = {0};
+    for (int k = 0; k < 3; ++k) {
+        Queues &to = p.q[k];
+        std::vector<Tile> q;
+        fill_queues(tiles[k], nq, q, lens + 16 * k + 8, to.per);
+        to.nq = nq;
+        to.ntiles = (int64_t)tiles[k].size();
+        if (to.ntiles == 0) continue;
+        if (!grow(c, &to.d_tiles, &to.cap, q.size())) return fail(c, PISCO_ENOMEM, "plan allocation failed");
+        HIP_TRY(c, hipMemcpy(to.d_tiles, q.data(), q.size() * sizeof(Tile), hipMemcpyHostToDevice));
+    }
     HIP_TRY(c, hipMemcpy(p.d_ctrl, lens, sizeof(lens), hipMemcpyHostToDevice));
-    p.tq.nq = p.pq.nq = nq;
-    p.tq.ntiles = (int64_t)ttiles.size();
-    p.pq.ntiles = (int64_t)ptiles.size();
     p.out_samples = out_end;
     return PISCO_OK;
 }
@@ -633,22 +641,24 @@ pisco_status prepare_plan(pisco_ctx *c, Plan &p, int32_t det, int out_mode) {
     return PISCO_OK;
 }
 
-ConvArgs make_args(pisco_ctx *c, const Plan &p, void *out, int out_mode, bool tile) {
+ConvArgs make_args(pisco_ctx *c, const Plan &p, void *out, int out_mode, Path path) {
     ConvArgs a{};
-    const Queues &q = tile ? p.tq : p.pq;
+    const Queues &q = p.q[path];
     a.sky = c->sky;
     a.dets = p.d_dets;
     a.tiles = q.d_tiles;
-    a.counters = p.d_ctrl + (tile ? 0 : 16);
-    a.queue_len = p.d_ctrl + (tile ? 8 : 24);
+    a.counters = p.d_ctrl + 16 * path;
+    a.queue_len = a.counters + 8;
     a.out = out;
     a.nside = c->nside;
     a.n_queues = q.nq;
     a.tiles_per_queue = q.per;
     a.out_mode = out_mode;
     a.beam_kind = p.beam_kind;
-    a.algo = tile ? ((c->algo == PISCO_ALGO_TILE_MX && !p.extended) ? pisco::ALGO_TILE_MX : pisco::ALGO_TILE)
-                  : pisco::ALGO_PIXEL;
+    a.algo = path != PATH_TILE                                ? pisco::ALGO_PIXEL
+             : c->algo == PISCO_ALGO_TILE_MX && !p.extended ? pisco::ALGO_TILE_MX
+                                                            : pisco::ALGO_TILE;
+    a.pixel_rows = path == PATH_ROWS;
     a.chunk = c->chunk;
     a.coherence = c->coherence;
     a.per_sample = p.per_sample;
@@ -658,19 +668,20 @@ ConvArgs make_args(pisco_ctx *c, const Plan &p, void *out, int out_mode, bool ti
 }
 
 hipError_t enqueue(pisco_ctx *c, const Plan &p, void *out, int out_mode, hipStream_t s) {
-    hipError_t e = pisco::launch_zero_counters(p.d_ctrl, 32, s);
+    hipError_t e = pisco::launch_zero_counters(p.d_ctrl, 48, s);
     if (e != hipSuccess) return e;
     const bool f64 = c->sky_dtype == PISCO_F64;
-    if (p.tq.ntiles > 0) {
-        pisco::ConvArgs a = make_args(c, p, out, out_mode, true);
-        pisco::share_tiles(a, p.tq.ntiles, c->num_cu);
+    if (p.q[PATH_TILE].ntiles > 0) {
+        pisco::ConvArgs a = make_args(c, p, out, out_mode, PATH_TILE);
+        pisco::share_tiles(a, p.q[PATH_TILE].ntiles, c->num_cu);
         e = pisco::launch_conv(a, f64, c->wpg, c->gpc * c->num_cu, s);
         if (e != hipSuccess) return e;
     }
-    if (p.pq.ntiles > 0) {
-        // no more workgroups than the pixel path has tiles for (a wave takes a tile)
-        const int64_t g = std::min<int64_t>(pixel_groups(c), (p.pq.ntiles + c->wpg - 1) / c->wpg);
-        e = pisco::launch_conv(make_args(c, p, out, out_mode, false), f64, c->wpg, (int)std::max<int64_t>(1, g), s);
+    for (const Path k : {PATH_PIXEL, PATH_ROWS}) {
+        if (p.q[k].ntiles == 0) continue;
+        // no more workgroups than the path has tiles for (a wave takes a tile)
+        const int64_t g = std::min<int64_t>(pixel_groups(c), (p.q[k].ntiles + c->wpg - 1) / c->wpg);
+        e = pisco::launch_conv(make_args(c, p, out, out_mode, k), f64, c->wpg, (int)g, s);
         if (e != hipSuccess) return e;
     }
     // far-sidelobe network of surrogate-enabled detectors, added to their TOD
@@ -1668,10 +1679,11 @@ pisco_status pisco_convolve_static(pisco_ctx *c, int32_t det, int out_mode, void
     ConvArgs tile = a, pix = a;
     tile.algo = (c->algo == PISCO_ALGO_TILE_MX && !extended) ? pisco::ALGO_TILE_MX : pisco::ALGO_TILE;
     pix.algo = pisco::ALGO_PIXEL;
+    pix.pixel_rows = x.pixel_rows;
     const bool tile_path = (c->algo == PISCO_ALGO_TILE || c->algo == PISCO_ALGO_TILE_MX) && c->sky_dtype == PISCO_F32;
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = pisco::launch_static(tile, pix, x, tile_path, c->sky_dtype == PISCO_F64, c->wpg,
-                                        c->gpc * c->num_cu, c->num_cu, base, s);
+                                        c->gpc * c->num_cu, pixel_groups(c), c->num_cu, base, s);
     if (e == hipSuccess && sub) {
         const SlApply ap = sl_apply_of(d, d.th, d.ph, d.ps, d.nsamp, 0);
         e = pisco::mlp_apply_pointing(ap.net, ap.th, ap.ph, ap.ps, ap.n, ap.mean, ap.stdv, ap.coef,

@@ -27,3 +27,10 @@ def test_unshared_tile_loop_spills():
         if name.endswith(", false>"):
             plate = name.split(", ")[4] == "true"
             assert k[".vgpr_spill_count"] <= (18 if plate else 11) and k[".sgpr_spill_count"] == 0, name
+
+
+def test_pixel_path_stays_in_registers():
+    """Each form of the pixel path (a sample a wave, four samples a wave) keeps its own
+    registers: with both in one kernel the first spilled 8 to 10 in FP32."""
+    for name, k in _of("conv_kernel<").items():
+        assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, name
