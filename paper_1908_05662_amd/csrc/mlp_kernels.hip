@@ -821,7 +821,9 @@ hipError_t mlp_wgrad(const __bf16 *a, const __bf16 *b, int64_t ld, int64_t opera
 
 // 64 rows a workgroup when that still gives every CU one (the weights are then read
 // from L2 once per 64 rows), 32 otherwise.  A whole gradient of 512 x 10, us with 32 and
-// 64 rows: 8192 rows 488 / 510, where 64 leave half the CUs idle.
+// 64 rows: 8192 rows 488 / 510, where 64 leave half the CUs idle.  Width 64 keeps 32: its
+// workgroup is one wave, and a SIMD wants several (forward of 64 x 2, us with 32 and 64
+// rows: 16,384 rows 16.2 / 17.9, 65,536 36.2 / 39.0, 262,144 105 / 106).
 template <int NW, int JT, bool BWD>
 static hipError_t chain_launch(const MlpChain &a, hipStream_t s) {
     const size_t lds = (size_t)(16 * JT) * (64 * NW + 8) * sizeof(__bf16);
@@ -836,7 +838,8 @@ static hipError_t chain_launch(const MlpChain &a, hipStream_t s) {
 
 template <int NW>
 static hipError_t chain_rows(const MlpChain &a, bool bwd, int num_cu, hipStream_t s) {
-    if (a.n >= 64 * num_cu) return bwd ? chain_launch<NW, 4, true>(a, s) : chain_launch<NW, 4, false>(a, s);
+    if constexpr (NW > 1)
+        if (a.n >= 64 * num_cu) return bwd ? chain_launch<NW, 4, true>(a, s) : chain_launch<NW, 4, false>(a, s);
     return bwd ? chain_launch<NW, 2, true>(a, s) : chain_launch<NW, 2, false>(a, s);
 }
 
