@@ -662,8 +662,8 @@ struct LaneFrame {
     float om, p1, p2, p3;   // 1 - p.c and p
     float a1, a2, a3;       // theta'_0
     float b1, b2, b3;       // phi'_0
-    float g1, g2, g3;       // co-polar direction at the boresight (matrix-core variant); pair loop with a
-                            // plate: theta'_0 turned by 2 phi_t, first two components, grid units
+    float g1, g2, g3;       // co-polar direction at the boresight (matrix-core variant); of a detector
+                            // with a plate: theta'_0 turned by 2 phi_t (pair loop's quadratic form)
     float c2p, s2p;         // cos, sin of 2 phi_t (half-wave plate; 1, 0 without one)
 };
 
@@ -760,6 +760,11 @@ __device__ __attribute__((noinline)) TileFrame tile_setup(const DetDesc &D, int3
         sincos(2.0 * D.hwp[t], &sh2, &ch2);
         F.c2p = (float)ch2;
         F.s2p = (float)sh2;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) tg[i] = ch2 * ta[i] + sh2 * tb[i];
+        F.g1 = (float)(tg[0] * e1[0] + tg[1] * e1[1] + tg[2] * e1[2]);
+        F.g2 = (float)(tg[0] * e2[0] + tg[1] * e2[1]);
+        F.g3 = (float)(tg[0] * c[0] + tg[1] * c[1] + tg[2] * c[2]);
     }
     *out = F;
     double dist = valid ? 2.0 * asin(fmin(1.0, 0.5 * sqrt(2.0 * om))) : 0.0;  // angle from the centre
@@ -1149,8 +1154,12 @@ __device__ __forceinline__ PairOut tile_pairs(const typename Cond<QF, PixRecQ, P
         // grid scale (1/h, 1/h^2); the records carry h^2.
         // (a plate turns gamma by 2 phi_t.  In the quadratic form the vector that is
         // carried is turned instead: g = cos(2 phi_t) theta'_0 + sin(2 phi_t) phi'_0,
-        // with g.n from the same two products that give the grid coordinates.)
-        const float q = (QF && HWP ? fmaf(F.s2p, yp[k], F.c2p * xp[k]) : xp[k]) * rq[k];
+        // formed in FP64 and rounded once, and g.n / n_z in two products like the grid
+        // coordinates: turned in FP32, from these, the TOD of a polarised sky was a
+        // quarter further off than on the plain records.)
+        float gn = xp[k];
+        if constexpr (QF && HWP) gn = fmaf(R[k].G2, F.g2, fmaf(R[k].G1, F.g1, F.g3));
+        const float q = gn * rq[k];
         if constexpr (QF) {
             // e is normal to n, so its first two tile-frame components fix it:
             // for vectors v, w normal to n, v.w = v_xy . (w_xy - (w_z / n_z) n_xy),
@@ -1382,9 +1391,10 @@ __device__ void convolve_tile(const ConvArgs &A, const DetDesc &D, int64_t begin
     Fg.b1 *= inv_h;
     Fg.b2 *= inv_h;
     Fg.b3 *= inv_h;
-    if (HWP) {   // theta'_0 turned by 2 phi_t, for the quadratic form
-        Fg.g1 = fmaf(F.s2p, Fg.b1, F.c2p * Fg.a1);
-        Fg.g2 = fmaf(F.s2p, Fg.b2, F.c2p * Fg.a2);
+    if (HWP) {   // (a detector without a plate in the launch of one that has: not turned)
+        Fg.g1 = (D.hwp ? F.g1 : F.a1) * inv_h;
+        Fg.g2 = (D.hwp ? F.g2 : F.a2) * inv_h;
+        Fg.g3 = (D.hwp ? F.g3 : F.a3) * inv_h;
     }
     // omin = -1 without an inner disc, so `omg > omin` holds for every pixel (omg >= 0)
     const float omax = (float)D.omega_max, omin = D.has_inner ? (float)D.omega_min : -1.0f;
