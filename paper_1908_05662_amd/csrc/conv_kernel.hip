@@ -157,7 +157,7 @@ __device__ inline void half_sincos(float x, float &s, float &c) {
     c = fmaf(x2, pc, 1.0f);
 }
 // FP64: the device math library, and for |x| <= 1/4 the Taylor series to x^11 and x^12
-// (truncation 1e-17 and 3e-20 relative).  Lane by lane: a value may not depend on what
+// (truncation 1e-17 and 5e-20 relative).  Lane by lane: a value may not depend on what
 // the wave's other lanes hold.
 __device__ inline void half_sincos(double x, double &s, double &c) {
     const double x2 = x * x;

@@ -591,8 +591,8 @@ struct PairState {
 };
 
 // Powers of two: the values' window is [2^-HALF, 2^HALF) at the start and after
-// each rescaling, so a lane with e < 0 holds numbers below 2^-HALF (3e-39 of
-// the O(1) values its ring reaches later): they add nothing in FP64.
+// each rescaling, so a lane with e < 0 holds lambda below 2^-HALF and f^+- below 2^24
+// times that (5e-32 of the O(1) values its ring reaches later): they add nothing in FP64.
 constexpr int HALF = SCALE / 2;
 
 // c s^m, split into a mantissa and a multiple of SCALE in the exponent
@@ -837,8 +837,8 @@ struct WaveSums {
 // and next to the poles that moves this evaluation and the one by f^+- apart: by
 // 5e-12 of the largest a_lm at m = 0, 1e-12 at m = 3 and 3e-13 at m = 17 at nside
 // 1024 (f^+- is the nearer to the exact harmonics: 2e-12 against 1e-11 at m = 0),
-// 5e-13 at nside 256.  These few a_lm stay what the definition's own evaluation
-// gives.  They are the longest chains of l, so a workgroup takes one m and 64 NW
+// 5e-13 at nside 256.  These few a_lm keep the definition's own evaluation, so that they
+// do not move by that.  They are the longest chains of l, so a workgroup takes one m and 64 NW
 // ring pairs, one a lane; with more parts than one, wx_reduce_kernel adds them.
 // ----------------------------------------------------------------------
 constexpr int WX_M = 16, WX_NSIDE = 256;
