@@ -36,6 +36,10 @@ def kernels() -> dict:
     """Demangled kernel name (namespaces and arguments dropped) -> metadata dict."""
     if _CACHE:
         return _CACHE
+    if not os.path.exists(LIB):
+        from paper_1908_05662_amd.build import build
+
+        build()
     with open(LIB, "rb") as f:
         data = f.read()
     found = []
